@@ -30,6 +30,11 @@ __device__ __forceinline__ void gst(void* p, T v) {
   *(GLOBAL_AS T*)p = v;
 }
 
+// The same vectors at any element address (2-byte aligned bf16, 4-byte aligned fp32): gfx950 runs
+// in unaligned access mode, so these stay single 16-byte instructions.
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int V>
 struct IntC {
   static constexpr int value = V;
@@ -452,19 +457,30 @@ __device__ __forceinline__ void buffer_load_lds16_block(i32x4 rsrc, const uint32
 #undef TPP_LDS16_STEP
 #undef TPP_LDS16_LAST
 
-// 16 bytes of bf16 from global memory, aligned or not; zeroing without branches.
+// 16 bytes of bf16 from global memory, 16-byte aligned or at any element; zeroing without branches.
 __device__ __forceinline__ u32x4 ld16(const uint16_t* ptr) { return gld<u32x4>(ptr); }
 
 __device__ __forceinline__ u32x4 ld16_unaligned(const uint16_t* ptr) {
-  uint32_t h[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = gld<uint16_t>(ptr + e);
-  return (u32x4){h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
-                 h[6] | (h[7] << 16)};
+  return gld<u32x4_a2>(ptr);
 }
 
 __device__ __forceinline__ u32x4 keep_if(u32x4 v, bool ok) {
   return (u32x4){ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+}
+
+// v moved down by d elements (d >= 0): element e of the result is element e + d of v, zero past the
+// end.
+__device__ __forceinline__ u32x4 shift_down(u32x4 v, int32_t d) {
+  uint64_t lo = ((uint64_t)v.y << 32) | v.x, hi = ((uint64_t)v.w << 32) | v.z;
+  if (d >= 4) {
+    lo = d >= 8 ? 0 : hi;
+    hi = 0;
+    d -= 4;
+  }
+  const int s = (d & 3) * 16;
+  lo = (lo >> s) | ((hi << 1) << (63 - s));   // two shifts: 64 - s may be 64
+  hi >>= s;
+  return (u32x4){(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -475,7 +491,9 @@ __device__ __forceinline__ u32x4 keep_if(u32x4 v, bool ok) {
 // The accumulator layout of a 32x32 MFMA tile: lane l holds column l%32, and in register v the
 // row 8*(v/4) + 4*(l/32) + v%4.
 // ---------------------------------------------------------------------------------------------
-template <int WTM, int WTN, int TM, int TN, bool FULL>
+// RAGGED: m is any size; the virtual rows of an instance are padded to whole 8-row chunks (p.vm of
+// them), and the last chunk of an instance stores its first m % 8 rows one by one.
+template <int WTM, int WTN, int TM, int TN, bool FULL, bool RAGGED = false>
 __device__ __forceinline__ void epilogue_via_lds(const BrgemmParams& p, const Instance& in,
                                                  const TileCoord& tc, int wm, int wn, int lane,
                                                  int wave, float* lds_f, f32x16 (&acc)[TM][TN]) {
@@ -488,21 +506,26 @@ __device__ __forceinline__ void epilogue_via_lds(const BrgemmParams& p, const In
   const int32_t R = tc.row0 + wm * WTM + my_chunk * 8;
   bool row_ok = true;
   int64_t row_off, bias_idx;
+  int32_t nr = 8;                                    // valid rows of the lane's chunk
   if (p.fused) {
-    const int32_t gi = R / p.m, r = R - gi * p.m;
+    const int32_t im = RAGGED ? p.vm : p.m;
+    const int32_t gi = R / im, r = R - gi * im;
     row_ok = FULL || R < p.vrows;
     row_off = (int64_t)gi * p.c_step_m + r;
     bias_idx = (int64_t)gi * p.bias_step_m + r;
+    if (RAGGED) nr = p.m - r < 8 ? p.m - r : 8;
   } else {
     row_ok = FULL || R < p.m;
     row_off = R;
     bias_idx = in.bias + R;
+    if (RAGGED) nr = p.m - R < 8 ? p.m - R : 8;
   }
   float bias8[8];
   const bool has_bias = (p.flags & TPP_EPI_BIAS) != 0;
 #pragma unroll
   for (int e = 0; e < 8; ++e)
-    bias8[e] = (has_bias && row_ok) ? gld<float>(p.bias + bias_idx + e) : 0.0f;
+    bias8[e] = (has_bias && row_ok && (!RAGGED || e < nr)) ? gld<float>(p.bias + bias_idx + e)
+                                                           : 0.0f;
 
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
@@ -535,54 +558,67 @@ __device__ __forceinline__ void epilogue_via_lds(const BrgemmParams& p, const In
         col_ok = FULL || C < p.n;
         col_off = (int64_t)C * p.ldc;
       }
-      if (row_ok && col_ok) {
-        float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        const int64_t e0 = in.c + row_off + col_off;
-        if (p.c_bf16) {
-          uint16_t* cp = static_cast<uint16_t*>(p.c) + e0;
-          const bool vec = (reinterpret_cast<uintptr_t>(cp) & 15) == 0;
-          if (p.beta != 0.0f) {
-            const u32x4 w = vec ? ld16(cp) : ld16_unaligned(cp);
-            const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+      if (!row_ok || !col_ok) continue;
+      float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      const int64_t e0 = in.c + row_off + col_off;
+      if (RAGGED && nr < 8) {
+        // the instance's last rows
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              v[2 * e] = p.beta * bf16_bits_to_f32(d[e] & 0xffffu) + v[2 * e];
-              v[2 * e + 1] = p.beta * bf16_bits_to_f32(d[e] >> 16) + v[2 * e + 1];
-            }
-          }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] += bias8[e];
-          if (p.flags & EPI_AUX_MASK) epi_aux<8>(p, e0, v);
-          uint32_t o[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = f32_to_bf16_bits(activate(v[e], p.flags));
-          if (vec) {
-            gst<u32x4>(cp, (u32x4){o[0] | (o[1] << 16), o[2] | (o[3] << 16),
-                                   o[4] | (o[5] << 16), o[6] | (o[7] << 16)});
+        for (int e = 0; e < 8; ++e) {
+          if (e >= nr) break;
+          float x[1] = {v[e]};
+          if (p.c_bf16) {
+            uint16_t* cp = static_cast<uint16_t*>(p.c) + e0 + e;
+            if (p.beta != 0.0f) x[0] = p.beta * bf16_bits_to_f32(gld<uint16_t>(cp)) + x[0];
+            x[0] += bias8[e];
+            if (p.flags & EPI_AUX_MASK) epi_aux<1>(p, e0 + e, x);
+            gst<uint16_t>(cp, f32_to_bf16_bits(activate(x[0], p.flags)));
           } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) gst<uint16_t>(cp + e, (uint16_t)o[e]);
-          }
-        } else {
-          float* cp = static_cast<float*>(p.c) + e0;
-          const bool vec = (reinterpret_cast<uintptr_t>(cp) & 15) == 0;
-          if (p.beta != 0.0f) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = p.beta * gld<float>(cp + e) + v[e];
-          }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] += bias8[e];
-          if (p.flags & EPI_AUX_MASK) epi_aux<8>(p, e0, v);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = activate(v[e], p.flags);
-          if (vec) {
-            gst<f32x4>(cp, (f32x4){v[0], v[1], v[2], v[3]});
-            gst<f32x4>(cp + 4, (f32x4){v[4], v[5], v[6], v[7]});
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) gst<float>(cp + e, v[e]);
+            float* cp = static_cast<float*>(p.c) + e0 + e;
+            if (p.beta != 0.0f) x[0] = p.beta * gld<float>(cp) + x[0];
+            x[0] += bias8[e];
+            if (p.flags & EPI_AUX_MASK) epi_aux<1>(p, e0 + e, x);
+            gst<float>(cp, activate(x[0], p.flags));
           }
         }
+        continue;
+      }
+      if (p.c_bf16) {
+        uint16_t* cp = static_cast<uint16_t*>(p.c) + e0;
+        if (p.beta != 0.0f) {
+          const u32x4 w = ld16_unaligned(cp);
+          const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[2 * e] = p.beta * bf16_bits_to_f32(d[e] & 0xffffu) + v[2 * e];
+            v[2 * e + 1] = p.beta * bf16_bits_to_f32(d[e] >> 16) + v[2 * e + 1];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bias8[e];
+        if (p.flags & EPI_AUX_MASK) epi_aux<8>(p, e0, v);
+        uint32_t o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = f32_to_bf16_bits(activate(v[e], p.flags));
+        gst<u32x4_a2>(cp, (u32x4){o[0] | (o[1] << 16), o[2] | (o[3] << 16), o[4] | (o[5] << 16),
+                                  o[6] | (o[7] << 16)});
+      } else {
+        float* cp = static_cast<float*>(p.c) + e0;
+        if (p.beta != 0.0f) {
+          const f32x4 c0 = gld<f32x4_a4>(cp), c1 = gld<f32x4_a4>(cp + 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[e] = p.beta * c0[e] + v[e];
+            v[e + 4] = p.beta * c1[e] + v[e + 4];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bias8[e];
+        if (p.flags & EPI_AUX_MASK) epi_aux<8>(p, e0, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = activate(v[e], p.flags);
+        gst<f32x4_a4>(cp, (f32x4){v[0], v[1], v[2], v[3]});
+        gst<f32x4_a4>(cp + 4, (f32x4){v[4], v[5], v[6], v[7]});
       }
     }
     __syncthreads();
@@ -827,8 +863,7 @@ __device__ __forceinline__ void epilogue_bf16_act(const BrgemmParams& p, const I
       walk([&](char* sp, int64_t off, bool ok) {
         if (!ok) return;
         const uint16_t* ap = a16 + off;
-        *reinterpret_cast<u32x4*>(sp) =
-            (reinterpret_cast<uintptr_t>(ap) & 15) == 0 ? ld16(ap) : ld16_unaligned(ap);
+        *reinterpret_cast<u32x4*>(sp) = ld16_unaligned(ap);
       });
     }
   }

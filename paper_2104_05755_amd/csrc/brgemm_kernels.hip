@@ -360,12 +360,20 @@ __global__ __launch_bounds__(NT) void brgemm_bf16_kernel(BrgemmParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// bf16 16-byte-load kernel.  Preconditions (checked on the host): m, k, lda, ldb and every
-// element step of the grid are multiples of 8, so each 8-element chunk a thread moves is
-// contiguous and, when the pair's block bases are 16-byte aligned (checked per stage, uniform
-// over the workgroup), aligned.  FULL: every tile is complete (no row, column or k tail), so
-// the loads carry no bounds logic at all; otherwise out-of-range chunks read a clamped,
-// in-range address and are replaced by zeros without branching.
+// bf16 16-byte-load kernel, for m and k of at least 8, any strides and any alignment (a 16-byte
+// load takes any element address).  Every 8-element chunk a thread moves is contiguous in one
+// block.  FULL: every tile is complete (no row, column or k tail), so the loads carry no bounds
+// logic at all; otherwise out-of-range chunks read a clamped, in-range address and k past the end
+// is replaced by zeros without branching (rows and columns past the end only reach outputs that
+// are not stored).
+// RAGGED: m or k is no multiple of 8.  The virtual rows of each instance are padded to whole
+// chunks (p.vm of them), so a chunk still lies in one block, and the last chunk of a block's rows
+// or k-run reads the 8-element window that ends with the block instead of passing it: a row window
+// goes d rows higher in the LDS panel (where it writes the d rows below it once more, the same
+// values; the panel has 8 spare rows in front for a tile that starts with such a chunk), a k
+// window is shifted down by d elements.  A classifier layer of 1000 outputs on 777 features and
+// 1533 tokens (384 tiles of 64 x 64, bound by its chain of 13 stages) took 107 us through the
+// element-load kernel above, one stage of element loads at a time, and takes 18 us here.
 // ---------------------------------------------------------------------------------------------
 // Transpose an 8 x SK bf16 sub-block held as SK k-columns of 8 rows into 8 rows of SK k, and
 // store the rows (2*SK bytes each) into the K-contiguous LDS panel.
@@ -387,8 +395,9 @@ __device__ __forceinline__ void store_a_transposed_v(uint16_t* dst_row0, const u
   }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool FULL, int KIND, bool ALIGNED>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool FULL, int KIND, bool RAGGED>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel(BrgemmParams p) {
+  static_assert(!(FULL && RAGGED), "a ragged block has tails");
   // Register prefetch depth: two stages ahead with one wave per SIMD, one stage ahead with two
   // waves per SIMD (the second wave hides the latency, and the registers are needed for it).
   constexpr int DEPTH = (WAVES_M * WAVES_N > 4) ? 1 : 2;
@@ -403,7 +412,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
   constexpr int A_REP = (A_SUB + NTH - 1) / NTH;
   constexpr int B_CH = BN * KCH;                     // 16-byte chunks of the B panel
   constexpr int B_REP = (B_CH + NTH - 1) / NTH;
-  constexpr int STAGE = (BM + BN) * LDS_ROW;
+  constexpr int GUARD = RAGGED ? 8 * LDS_ROW : 0;    // spare rows in front of the A panel
+  constexpr int STAGE = GUARD + (BM + BN) * LDS_ROW;
   constexpr int EP_ROW = WTM + 4;                    // epilogue slab: 32 columns x WTM rows fp32
   static_assert(TM >= 1 && TN >= 1, "wave tile at least 32x32");
   static_assert(WAVES_M * WAVES_N * 32 * EP_ROW * 4 <= 2 * STAGE * 2,
@@ -429,8 +439,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
     a_kc[rep] = q % KCA;
     a_row[rep] = (q / KCA) * 8;
     a_off[rep] = 0;
-    a_ok[rep] = (q < A_SUB) && row_in_a(p, tc.row0 + a_row[rep], a_off[rep]);
-    if (!a_ok[rep]) a_off[rep] = 0;
+    if constexpr (RAGGED) {
+      const int32_t R = tc.row0 + a_row[rep];
+      const int32_t gi = p.fused ? R / p.vm : 0, r = R - gi * p.vm;
+      a_ok[rep] = q < A_SUB && R < p.vrows;
+      if (a_ok[rep]) {
+        const int32_t d = r + 8 > p.m ? r + 8 - p.m : 0;   // the window ends with the block
+        a_off[rep] = (p.fused ? (int64_t)gi * p.a_step_m : 0) + r - d;
+        a_row[rep] -= d;
+      }
+    } else {
+      a_ok[rep] = (q < A_SUB) && row_in_a(p, tc.row0 + a_row[rep], a_off[rep]);
+      if (!a_ok[rep]) a_off[rep] = 0;
+    }
   }
   int64_t b_off[B_REP];
   bool b_ok[B_REP];
@@ -461,52 +482,41 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
     const uint16_t* pa;
     const uint16_t* pb;
     pair_bases_k<KIND, uint16_t>(p, in, i, pa, pb);
-    const bool aligned =
-        ALIGNED || ((reinterpret_cast<uintptr_t>(pa) | reinterpret_cast<uintptr_t>(pb)) & 15) == 0;
-    if (ALIGNED || aligned) {
+    const bool ktail = !FULL && kk + BK > p.k;   // uniform: the block's last, partial stage
 #pragma unroll
-      for (int rep = 0; rep < A_REP; ++rep) {
-        const int32_t k0 = kk + a_kc[rep] * SK;
-        const bool ok = FULL || (a_ok[rep] && k0 < p.k);
-        const int32_t kc = (FULL || k0 < p.k) ? k0 : 0;
-        const uint16_t* base = pa + a_off[rep] + (int64_t)kc * p.lda;
-#pragma unroll
-        for (int j = 0; j < SK; ++j) {
-          const u32x4 v = ld16(base + (int64_t)j * p.lda);
-          r.a[rep][j] = FULL ? v : keep_if(v, ok);
-        }
-      }
-#pragma unroll
-      for (int rep = 0; rep < B_REP; ++rep) {
-        const int32_t k0 = kk + b_kc[rep] * 8;
-        const bool ok = FULL || (b_ok[rep] && k0 < p.k);
-        const int32_t kc = (FULL || k0 < p.k) ? k0 : 0;
-        const u32x4 v = ld16(pb + b_off[rep] + kc);
-        r.b[rep] = FULL ? v : keep_if(v, ok);
-      }
-    } else {
-#pragma unroll
-      for (int rep = 0; rep < A_REP; ++rep) {
-        const int32_t k0 = kk + a_kc[rep] * SK;
-        const bool ok = FULL || (a_ok[rep] && k0 < p.k);
-        const int32_t kc = (FULL || k0 < p.k) ? k0 : 0;
-        const uint16_t* base = pa + a_off[rep] + (int64_t)kc * p.lda;
+    for (int rep = 0; rep < A_REP; ++rep) {
+      const int32_t k0 = kk + a_kc[rep] * SK;
+      const uint16_t* base = pa + a_off[rep];
+      if (!ktail) {
 #pragma unroll
         for (int j = 0; j < SK; ++j)
-          r.a[rep][j] = keep_if(ld16_unaligned(base + (int64_t)j * p.lda), ok);
-      }
+          r.a[rep][j] = ld16_unaligned(base + (int64_t)(k0 + j) * p.lda);
+      } else {
 #pragma unroll
-      for (int rep = 0; rep < B_REP; ++rep) {
-        const int32_t k0 = kk + b_kc[rep] * 8;
-        const bool ok = FULL || (b_ok[rep] && k0 < p.k);
-        const int32_t kc = (FULL || k0 < p.k) ? k0 : 0;
-        r.b[rep] = keep_if(ld16_unaligned(pb + b_off[rep] + kc), ok);
+        for (int j = 0; j < SK; ++j) {
+          const bool ok = k0 + j < p.k;
+          r.a[rep][j] = keep_if(ld16_unaligned(base + (int64_t)(ok ? k0 + j : 0) * p.lda), ok);
+        }
+      }
+    }
+#pragma unroll
+    for (int rep = 0; rep < B_REP; ++rep) {
+      const int32_t k0 = kk + b_kc[rep] * 8;
+      const uint16_t* base = pb + b_off[rep];
+      if (!ktail) {
+        r.b[rep] = ld16_unaligned(base + k0);
+      } else if constexpr (RAGGED) {
+        const int32_t w = k0 + 8 > p.k ? p.k - 8 : k0;   // the window's first k
+        r.b[rep] = shift_down(ld16_unaligned(base + w), k0 - w);
+      } else {
+        const bool ok = k0 < p.k;
+        r.b[rep] = keep_if(ld16_unaligned(base + (ok ? k0 : 0)), ok);
       }
     }
   };
 
   auto store_a = [&](int buf, const Staged& r) {
-    uint16_t* As = lds + buf * STAGE;
+    uint16_t* As = lds + buf * STAGE + GUARD;
 #pragma unroll
     for (int rep = 0; rep < A_REP; ++rep) {
       if (A_SUB % NTH == 0 || t + NTH * rep < A_SUB)
@@ -514,7 +524,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
     }
   };
   auto store_b = [&](int buf, const Staged& r) {
-    uint16_t* Bs = lds + buf * STAGE + BM * LDS_ROW;
+    uint16_t* Bs = lds + buf * STAGE + GUARD + BM * LDS_ROW;
 #pragma unroll
     for (int rep = 0; rep < B_REP; ++rep) {
       if (B_CH % NTH == 0 || t + NTH * rep < B_CH)
@@ -536,7 +546,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
   // MFMAs of one LDS buffer: the fragments of k-step kq+1 are read while the MFMAs of kq run;
   // hook(kq) runs after the MFMAs of k-step kq are issued.
   auto compute = [&](int buf, auto&& hook) {
-    const uint16_t* As = lds + buf * STAGE;
+    const uint16_t* As = lds + buf * STAGE + GUARD;
     const uint16_t* Bs = As + BM * LDS_ROW;
     bf16x8 fa[2][TM], fb[2][TN];
     auto frags = [&](int kq, bf16x8* a, bf16x8* b) {
@@ -602,8 +612,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
     if (s < stages) step(IntC<0>());
   }
 
-  epilogue_via_lds<WTM, WTN, TM, TN, FULL>(p, in, tc, wm, wn, lane, wave,
-                                          reinterpret_cast<float*>(lds), acc);
+  epilogue_via_lds<WTM, WTN, TM, TN, FULL, RAGGED>(p, in, tc, wm, wn, lane, wave,
+                                                  reinterpret_cast<float*>(lds), acc);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -923,28 +933,28 @@ namespace {
 
 const char* tf(bool v) { return v ? "true" : "false"; }
 
-template <int BM, int BN, int WM, int WN, bool FULL, int KIND, bool ALIGNED>
+template <int BM, int BN, int WM, int WN, bool FULL, int KIND, bool RAGGED>
 void launch_vec_kk(const BrgemmParams& p, dim3 grid, hipStream_t stream, std::string* name_out) {
   if (name_out) {
     char buf[128];
     std::snprintf(buf, sizeof buf, "brgemm_bf16_vec_kernel<%d, %d, %d, %d, %s, %d, %s>", BM, BN,
-                  WM, WN, tf(FULL), KIND, tf(ALIGNED));
+                  WM, WN, tf(FULL), KIND, tf(RAGGED));
     *name_out = buf;
     return;
   }
-  hipLaunchKernelGGL((brgemm_bf16_vec_kernel<BM, BN, WM, WN, FULL, KIND, ALIGNED>), grid,
+  hipLaunchKernelGGL((brgemm_bf16_vec_kernel<BM, BN, WM, WN, FULL, KIND, RAGGED>), grid,
                      dim3(64 * WM * WN), 0, stream, p);
 }
 
-template <int BM, int BN, int WM, int WN, bool FULL, int KIND>
-void launch_vec_k(const BrgemmParams& p, dim3 grid, hipStream_t stream, std::string* name_out) {
-  if constexpr (KIND == TPP_BR_STRIDE) {
-    if (p.aligned) {
-      launch_vec_kk<BM, BN, WM, WN, FULL, KIND, true>(p, grid, stream, name_out);
-      return;
-    }
-  }
-  launch_vec_kk<BM, BN, WM, WN, FULL, KIND, false>(p, grid, stream, name_out);
+template <int BM, int BN, int WM, int WN, int KIND>
+void launch_vec_k(const BrgemmParams& p, bool full, dim3 grid, hipStream_t stream,
+                  std::string* name_out) {
+  if (p.ragged)
+    launch_vec_kk<BM, BN, WM, WN, false, KIND, true>(p, grid, stream, name_out);
+  else if (full)
+    launch_vec_kk<BM, BN, WM, WN, true, KIND, false>(p, grid, stream, name_out);
+  else
+    launch_vec_kk<BM, BN, WM, WN, false, KIND, false>(p, grid, stream, name_out);
 }
 
 template <int BM, int BN, int WM, int WN>
@@ -952,16 +962,13 @@ void launch_vec(const BrgemmParams& p, bool full, dim3 grid, hipStream_t stream,
                 std::string* name_out) {
   switch (p.kind) {
     case TPP_BR_STRIDE:
-      full ? launch_vec_k<BM, BN, WM, WN, true, TPP_BR_STRIDE>(p, grid, stream, name_out)
-           : launch_vec_k<BM, BN, WM, WN, false, TPP_BR_STRIDE>(p, grid, stream, name_out);
+      launch_vec_k<BM, BN, WM, WN, TPP_BR_STRIDE>(p, full, grid, stream, name_out);
       break;
     case TPP_BR_OFFSET:
-      full ? launch_vec_k<BM, BN, WM, WN, true, TPP_BR_OFFSET>(p, grid, stream, name_out)
-           : launch_vec_k<BM, BN, WM, WN, false, TPP_BR_OFFSET>(p, grid, stream, name_out);
+      launch_vec_k<BM, BN, WM, WN, TPP_BR_OFFSET>(p, full, grid, stream, name_out);
       break;
     default:
-      full ? launch_vec_k<BM, BN, WM, WN, true, TPP_BR_ADDRESS>(p, grid, stream, name_out)
-           : launch_vec_k<BM, BN, WM, WN, false, TPP_BR_ADDRESS>(p, grid, stream, name_out);
+      launch_vec_k<BM, BN, WM, WN, TPP_BR_ADDRESS>(p, full, grid, stream, name_out);
       break;
   }
 }

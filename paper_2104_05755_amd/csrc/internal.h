@@ -47,6 +47,9 @@ struct BrgemmParams {
   const int64_t* b_off;
   const int64_t* c_off;
   const int64_t* bias_off;
+  // Ragged instances of the 16-byte-load kernel (ragged = 1: m or k is no multiple of 8): the
+  // virtual rows of an instance, m padded to whole 8-row chunks (p.m otherwise); vrows counts them.
+  int32_t ragged, vm;
   // Tiling, filled by the launcher.
   int32_t vrows, vcols;      // virtual C extent of one tile group
   int32_t tiles_m, tiles_n;  // tiles per group
@@ -62,15 +65,18 @@ struct BrgemmParams {
   void* aux;
 };
 
+// m padded to whole 8-row chunks.
+inline int64_t padded_rows(int64_t m) { return (m + 7) / 8 * 8; }
+
 // Epilogue bits that use the aux tensor.
 constexpr uint32_t EPI_AUX_MASK = TPP_EPI_RELU_INV | TPP_EPI_GELU_TANH_INV | TPP_EPI_SAVE_PREACT;
 
 // Kernel instances of the bf16 family (tile shape + load path) and the fp32 kernel.
 enum KernelId : int32_t {
-  K_BF16_256x256 = 0,   // 8 waves, 128x64 per wave, 16-byte loads
+  K_BF16_256x256 = 0,   // 8 waves, 128x64 per wave, 16-byte loads (any strides, m and k >= 8)
   K_BF16_128x128 = 1,   // 4 waves, 64x64 per wave, 16-byte loads (two workgroups per CU)
   K_BF16_64x64 = 2,     // 4 waves, 32x32 per wave, 16-byte loads
-  K_BF16_GENERIC = 3,   // 64x64, element loads with full bounds checks (any shape / alignment)
+  K_BF16_GENERIC = 3,   // 64x64, element loads with full bounds checks (m or k below 8)
   K_F32_GENERIC = 4,    // 64x64 fp32 MFMA, element loads with full bounds checks
   K_BF16_DL_256x256 = 5,  // direct global->LDS staging, 8 waves (k a multiple of 32)
   K_BF16_DL_128x128 = 6,  // direct global->LDS staging, 4 waves

@@ -84,7 +84,9 @@ bool dl_offsets_fit(const tpp_brgemm_kernel_s& h, const tpp::BrgemmParams& p, in
 // Kernel choice for one launch.  bf16 inputs take a 16-byte-load instance when the descriptor
 // and the grid keep every 8-element chunk contiguous and aligned (m, k, lda, ldb and all element
 // steps multiples of 8); the tile shape is the largest that still gives two tiles per compute
-// unit (512 tiles on the 256 CUs).  Anything else takes the element-load instance.
+// unit (512 tiles on the 256 CUs).  Other strides and sizes take the register-staged instances,
+// whose 16-byte loads need no alignment, by the same tile rule; a block narrower than one 8-element
+// chunk in m or k takes the element-load instance.
 int32_t choose_kernel(const tpp_brgemm_kernel_s& h, const tpp::BrgemmParams& p) {
   if (!h.bf16) return (p.a_trans || p.b_trans) ? -1 : tpp::K_F32_GENERIC;
   bool vec = h.vec_ok;
@@ -113,7 +115,28 @@ int32_t choose_kernel(const tpp_brgemm_kernel_s& h, const tpp::BrgemmParams& p) 
     }
     return -1;
   }
-  if (!vec) return tpp::K_BF16_GENERIC;
+  if (!vec) {
+    // Windows of 8 elements inside every block, and a virtual C of padded row chunks that still
+    // counts in 32 bits.  Below 8 rows or k the element-load instance: it lays whole rows of
+    // several instances in one tile where the padded chunks would leave most of it empty.
+    const int64_t vr = tpp::padded_rows(h.desc.m) * (p.fused ? p.gm : 1);
+    const bool windows = h.desc.m >= 8 && h.desc.k >= 8 && vr < (1LL << 31) - 512;
+    if (const char* env = std::getenv("TPP_FORCE_KERNEL")) {
+      const int id = std::atoi(env);
+      if (id == tpp::K_BF16_GENERIC) return id;
+      if (windows && (id == tpp::K_BF16_256x256 || id == tpp::K_BF16_128x128 ||
+                      id == tpp::K_BF16_64x64))
+        return id;
+    }
+    if (!windows) return tpp::K_BF16_GENERIC;
+    for (int32_t id : {tpp::K_BF16_256x256, tpp::K_BF16_128x128}) {
+      const int bm = tpp::kernel_tile_m(id), bn = tpp::kernel_tile_n(id);
+      if (bm <= vr && bn <= p.vcols &&
+          p.groups * ((vr + bm - 1) / bm) * ((p.vcols + bn - 1) / bn) >= 512)
+        return id;
+    }
+    return tpp::K_BF16_64x64;
+  }
   // Direct buffer->LDS instances when k is a multiple of 32, with 64-k stages when it is a
   // multiple of 64 (whole 128-byte lines of B per load); pointer lists only with 64-k stages
   // (measured faster than register staging there, slower with 32-k stages); register staging
@@ -217,6 +240,11 @@ tpp_status plan_launch(const tpp_brgemm_kernel_s* h, tpp::BrgemmParams& p, Launc
                 "multiples of 8 and operand spans below 2^30 elements");
   lp = LaunchPlan();
   lp.id = id;
+  const bool reg_staged = id == tpp::K_BF16_256x256 || id == tpp::K_BF16_128x128 ||
+                          id == tpp::K_BF16_64x64;
+  p.ragged = reg_staged && (p.m % 8 != 0 || p.k % 8 != 0);
+  p.vm = p.ragged ? (int32_t)tpp::padded_rows(p.m) : p.m;
+  p.vrows = p.fused ? (int32_t)(p.gm * p.vm) : p.vm;
   const int bm = tpp::kernel_tile_m(id), bn = tpp::kernel_tile_n(id);
   if (id == tpp::K_F32_GENERIC && p.kind != TPP_BR_ADDRESS && p.count >= 2 &&
       !(p.flags & tpp::EPI_AUX_MASK)) {
