@@ -33,6 +33,7 @@ __device__ __forceinline__ void gst(void* p, T v) {
 // The same vectors at any element address (2-byte aligned bf16, 4-byte aligned fp32): gfx950 runs
 // in unaligned access mode, so these stay single 16-byte instructions.
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int V>

@@ -1,10 +1,11 @@
 // equation.hip -- TPP matrix equations (Sec. 4) for gfx950: the planner of Alg. 3 / Alg. 4 on the
 // host, and an executor that evaluates the planned instruction list per output element.
 //
-// Executor (see equation_kernel): eight output elements per thread; each instruction of the plan
-// dispatches once and then runs over the eight elements.  The temporaries of the plan are named
-// registers, so the plan's reuse of temporaries is register reuse: the paper's Strategy 2.  The
-// instruction list lives in the kernel arguments and is read with scalar loads.
+// Executor: eight output elements per thread.  Chains of steps onto one running value (the common
+// forms) have a kernel of their own (equation_chain_kernel).  In general each instruction of the plan
+// dispatches once and then runs over the eight elements (equation_vec_kernel); the temporaries of
+// the plan are named registers, so the plan's reuse of temporaries is register reuse: the paper's
+// Strategy 2.  The instruction list lives in the kernel arguments, one word per instruction.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -149,7 +150,6 @@ const char* equation_compile(const tpp_eq_node* nodes, int32_t n_nodes, int32_t 
   if (nodes[root].arity == TPP_EQ_LEAF) {   // the output is a copy of one leaf
     prog.n_instr = 1;
     prog.instr[0] = {TPP_EQ_IDENTITY, 1, 0, {EQ_LEAF_BASE + nodes[root].leaf, 0, 0}};
-    prog.result = 0;
     return nullptr;
   }
   if (n_tmps > EQ_MAX_TMPS) {
@@ -177,7 +177,6 @@ const char* equation_compile(const tpp_eq_node* nodes, int32_t n_nodes, int32_t 
     }
   }
   prog.n_instr = n_instr;
-  prog.result = plan[root].tmp;
   return nullptr;
 }
 
@@ -189,6 +188,7 @@ using namespace dev;
 constexpr int EQ_T = 256;   // threads per workgroup
 
 constexpr int EPT = 8;   // output elements per thread
+constexpr int64_t EQ_SMALL = 1 << 16;   // elements up to which few-row outputs run one per thread
 
 // v[k] = op(a[k], b[k], cc[k]) for the EPT elements, one dispatch on op.
 #define TPP_EQ_OP_CASE(op, expr) \
@@ -215,7 +215,28 @@ constexpr int EPT = 8;   // output elements per thread
     default: { _Pragma("unroll") for (int k = 0; k < EPT; ++k) v[k] = 0.0f; } break;            \
   }
 
+// Packed instruction word: op, arity, destination and three operand codes.
+__device__ __forceinline__ int32_t eq_op(uint32_t w) { return (int32_t)(w & 63u); }
+__device__ __forceinline__ int32_t eq_arity(uint32_t w) { return (int32_t)(w >> 6 & 3u); }
+__device__ __forceinline__ int32_t eq_dst(uint32_t w) { return (int32_t)(w >> 8 & 63u); }
+__device__ __forceinline__ int32_t eq_src(uint32_t w, int a) {
+  return (int32_t)(w >> (14 + 6 * a) & 63u);
+}
+// Entry j (wave-uniform) of a leaf table of which each lane holds entry lane % EQ_MAX_ARGS.
+__device__ __forceinline__ EqArg eq_arg_of(const EqArg& mine, int32_t j) {
+  const auto pick = [&](uint64_t v) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), j) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, j);
+  };
+  EqArg g;
+  g.ptr = reinterpret_cast<const void*>(pick(reinterpret_cast<uint64_t>(mine.ptr)));
+  g.ld = (int64_t)pick((uint64_t)mine.ld);
+  g.bf16 = __builtin_amdgcn_readlane(mine.bf16, j);
+  g.bcast = __builtin_amdgcn_readlane(mine.bcast, j);
+  return g;
+}
 
+// Outputs of fewer than 8 rows (and more than EQ_SMALL elements, not contiguous):
 // EPT output elements per thread, in column-major element order: element k of thread t in
 // workgroup b is e = (b * EPT + k) * EQ_T + t, so for every k a wavefront covers 64 consecutive
 // elements (contiguous runs of every full-tensor leaf and of the output, whatever the shape: a
@@ -225,7 +246,8 @@ constexpr int EPT = 8;   // output elements per thread
 // named register arrays (the plan's reuse of temporaries is register reuse).  WIDE: m * n does
 // not fit 32 bits.
 template <bool OUT_BF16, bool WIDE>
-__global__ __launch_bounds__(EQ_T) void equation_kernel(EqProgram p) {
+__global__ __launch_bounds__(EQ_T) void equation_kernel(EqArgs p) {
+  const uint32_t words = p.instr[threadIdx.x & 63];
   const int64_t total = (int64_t)p.m * p.n;
   const int64_t step = (int64_t)gridDim.x * EPT * EQ_T;
   for (int64_t e0 = (int64_t)blockIdx.x * EPT * EQ_T + threadIdx.x; e0 < total; e0 += step) {
@@ -250,7 +272,7 @@ __global__ __launch_bounds__(EQ_T) void equation_kernel(EqProgram p) {
       TPP_EQ_TMP_CASE(0, o) TPP_EQ_TMP_CASE(1, o) TPP_EQ_TMP_CASE(2, o) TPP_EQ_TMP_CASE(3, o)     \
       TPP_EQ_TMP_CASE(4, o) TPP_EQ_TMP_CASE(5, o) TPP_EQ_TMP_CASE(6, o) TPP_EQ_TMP_CASE(7, o)     \
       default: {                                                                                \
-        const EqArg& g = p.arg[(code) - EQ_LEAF_BASE];                                          \
+        const EqArg& g = p.varg[(code) - EQ_V_LEAF];                                          \
         _Pragma("unroll") for (int k = 0; k < EPT; ++k) {                                       \
           const int64_t at = g.bcast == TPP_BC_NONE ? (int64_t)r[k] + (int64_t)c[k] * g.ld      \
                              : g.bcast == TPP_BC_COL ? r[k] : g.bcast == TPP_BC_ROW ? c[k] : 0; \
@@ -267,17 +289,17 @@ __global__ __launch_bounds__(EQ_T) void equation_kernel(EqProgram p) {
       TPP_EQ_PUT_CASE(4) TPP_EQ_PUT_CASE(5) TPP_EQ_PUT_CASE(6) TPP_EQ_PUT_CASE(7)                \
       default: break;                                                                           \
     }
-    for (int32_t i = 0; i < p.n_instr; ++i) {
-      const EqInstr& in = p.instr[i];
+    for (int32_t i = 0; i < p.n_v; ++i) {
+      const uint32_t in = (uint32_t)__builtin_amdgcn_readlane((int)words, i);
       float a[EPT], b[EPT], cc[EPT], v[EPT];
-      FETCH(in.src[0], a)
-      if (in.arity > 1) { FETCH(in.src[1], b) }
-      if (in.arity > 2) { FETCH(in.src[2], cc) }
-      TPP_EQ_APPLY(in.op)
-      PUT(in.dst)
+      FETCH(eq_src(in, 0), a)
+      if (eq_arity(in) > 1) { FETCH(eq_src(in, 1), b) }
+      if (eq_arity(in) > 2) { FETCH(eq_src(in, 2), cc) }
+      TPP_EQ_APPLY(eq_op(in))
+      PUT(eq_dst(in))
     }
     float res[EPT];
-    FETCH(p.result, res)
+    FETCH(eq_dst((uint32_t)__builtin_amdgcn_readlane((int)words, p.n_v - 1)), res)
 #undef FETCH
 #undef PUT
 #undef TPP_EQ_TMP_CASE
@@ -293,13 +315,6 @@ __global__ __launch_bounds__(EQ_T) void equation_kernel(EqProgram p) {
     }
   }
 }
-
-// Small outputs (at most EQ_SMALL elements, e.g. a 1 x n row of statistics): one element per
-// thread, so that the grid has as many workgroups as the elements allow, and every leaf of the
-// element loaded before the first instruction runs, so that one memory latency replaces the
-// chain of leaf loads the interpreter would otherwise wait for one instruction at a time.  The
-// leaves and temporaries are named registers (indices dispatched by switch, never computed).
-constexpr int64_t EQ_SMALL = 1 << 16;
 
 __device__ __forceinline__ float eq_apply1(int32_t op, float a, float b, float c) {
   switch (op) {
@@ -324,77 +339,291 @@ __device__ __forceinline__ float eq_apply1(int32_t op, float a, float b, float c
   }
 }
 
+// Small outputs of fewer than 8 rows (at most EQ_SMALL elements, e.g. a 1 x n row of statistics):
+// one element per thread, so that the grid has as many workgroups as the elements allow, and every
+// leaf of the element loaded before the first instruction runs.  Bound by latency: the kernel
+// arguments (the program and the leaf table are each read by one load per wavefront, a word per
+// lane), one round of leaf loads, then the instructions.  Each thread's temporaries and leaves
+// live in its own column of LDS, so an operand is one LDS read at a computed address, no branches.
 template <bool OUT_BF16>
-__global__ __launch_bounds__(EQ_T) void equation_small_kernel(EqProgram p) {
+__global__ __launch_bounds__(EQ_T) void equation_small_kernel(EqArgs p) {
+  extern __shared__ float eq_file[];   // [EQ_V_LEAF + n_args][EQ_T]
+  const int lane = threadIdx.x & 63;
+  const uint32_t words = p.instr[lane];
+  const EqArg mine = p.varg[lane & (EQ_MAX_ARGS - 1)];
   const int32_t total = p.m * p.n;   // at most EQ_SMALL
   const int32_t e = (int32_t)blockIdx.x * EQ_T + (int32_t)threadIdx.x;
-  if (e >= total) return;
-  const int32_t c = e / p.m, r = e - c * p.m;
-  // every leaf of this element, all loads issued before any is used
-  float l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, l3 = 0.0f, l4 = 0.0f, l5 = 0.0f, l6 = 0.0f, l7 = 0.0f;
-  float l8 = 0.0f, l9 = 0.0f, l10 = 0.0f, l11 = 0.0f, l12 = 0.0f, l13 = 0.0f, l14 = 0.0f,
-        l15 = 0.0f;
-  auto leaf = [&](int j) -> float {
-    const EqArg& g = p.arg[j];
-    const int64_t at = g.bcast == TPP_BC_NONE ? (int64_t)r + (int64_t)c * g.ld
-                       : g.bcast == TPP_BC_COL ? r : g.bcast == TPP_BC_ROW ? c : 0;
-    return g.bf16 ? bf16_bits_to_f32(gld<uint16_t>(static_cast<const uint16_t*>(g.ptr) + at))
-                  : gld<float>(static_cast<const float*>(g.ptr) + at);
-  };
-#define TPP_EQ_LEAF_LOAD(j) \
-  if (j < p.n_args) l##j = leaf(j);
-  TPP_EQ_LEAF_LOAD(0) TPP_EQ_LEAF_LOAD(1) TPP_EQ_LEAF_LOAD(2) TPP_EQ_LEAF_LOAD(3)
-  TPP_EQ_LEAF_LOAD(4) TPP_EQ_LEAF_LOAD(5) TPP_EQ_LEAF_LOAD(6) TPP_EQ_LEAF_LOAD(7)
-  TPP_EQ_LEAF_LOAD(8) TPP_EQ_LEAF_LOAD(9) TPP_EQ_LEAF_LOAD(10) TPP_EQ_LEAF_LOAD(11)
-  TPP_EQ_LEAF_LOAD(12) TPP_EQ_LEAF_LOAD(13) TPP_EQ_LEAF_LOAD(14) TPP_EQ_LEAF_LOAD(15)
-#undef TPP_EQ_LEAF_LOAD
-  static_assert(EQ_MAX_ARGS == 16 && EQ_MAX_TMPS == 8 && EQ_LEAF_BASE == 16,
-                "one named register per leaf and temporary");
-  float t0 = 0.0f, t1 = 0.0f, t2 = 0.0f, t3 = 0.0f, t4 = 0.0f, t5 = 0.0f, t6 = 0.0f, t7 = 0.0f;
-  auto get = [&](int32_t code) -> float {
-    switch (code) {
-      case 0: return t0; case 1: return t1; case 2: return t2; case 3: return t3;
-      case 4: return t4; case 5: return t5; case 6: return t6; case 7: return t7;
-      case 16: return l0; case 17: return l1; case 18: return l2; case 19: return l3;
-      case 20: return l4; case 21: return l5; case 22: return l6; case 23: return l7;
-      case 24: return l8; case 25: return l9; case 26: return l10; case 27: return l11;
-      case 28: return l12; case 29: return l13; case 30: return l14; case 31: return l15;
-      default: return 0.0f;
+  const int32_t ee = e < total ? e : 0;
+  const int32_t c = ee / p.m, r = ee - c * p.m;
+  float* const file = eq_file + threadIdx.x;
+  // leaves in rounds of four, every load of a round issued before the first is stored
+  for (int32_t j0 = 0; j0 < p.n_varg; j0 += 4) {
+    float x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[k] = 0.0f;
+      const EqArg g = eq_arg_of(mine, j0 + k < p.n_varg ? j0 + k : j0);
+      const int64_t at = g.bcast == TPP_BC_NONE ? (int64_t)r + (int64_t)c * g.ld
+                         : g.bcast == TPP_BC_COL ? r : g.bcast == TPP_BC_ROW ? c : 0;
+      if (g.bf16)
+        x[k] = bf16_bits_to_f32(gld<uint16_t>(static_cast<const uint16_t*>(g.ptr) + at));
+      else
+        x[k] = gld<float>(static_cast<const float*>(g.ptr) + at);
     }
-  };
-  for (int32_t i = 0; i < p.n_instr; ++i) {
-    const EqInstr& in = p.instr[i];
-    const float a = get(in.src[0]);
-    const float b = in.arity > 1 ? get(in.src[1]) : 0.0f;
-    const float cc = in.arity > 2 ? get(in.src[2]) : 0.0f;
-    const float v = eq_apply1(in.op, a, b, cc);
-    switch (in.dst) {
-      case 0: t0 = v; break; case 1: t1 = v; break; case 2: t2 = v; break; case 3: t3 = v; break;
-      case 4: t4 = v; break; case 5: t5 = v; break; case 6: t6 = v; break; case 7: t7 = v; break;
-      default: break;
-    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (j0 + k < p.n_varg) file[(EQ_V_LEAF + j0 + k) * EQ_T] = x[k];
   }
-  const float res = get(p.result);
+  float v = 0.0f;
+  for (int32_t i = 0; i < p.n_v; ++i) {
+    const uint32_t in = (uint32_t)__builtin_amdgcn_readlane((int)words, i);
+    const int32_t ar = eq_arity(in);
+    const float a = file[eq_src(in, 0) * EQ_T];
+    const float b = ar > 1 ? file[eq_src(in, 1) * EQ_T] : 0.0f;
+    const float cc = ar > 2 ? file[eq_src(in, 2) * EQ_T] : 0.0f;
+    v = eq_apply1(eq_op(in), a, b, cc);
+    file[eq_dst(in) * EQ_T] = v;
+  }
+  // the last instruction is the root
+  if (e >= total) return;
   const int64_t at = (int64_t)r + (int64_t)c * p.ldo;
   if (OUT_BF16)
-    gst<uint16_t>(static_cast<uint16_t*>(p.out) + at, f32_to_bf16_bits(res));
+    gst<uint16_t>(static_cast<uint16_t*>(p.out) + at, f32_to_bf16_bits(v));
   else
-    gst<float>(static_cast<float*>(p.out) + at, res);
+    gst<float>(static_cast<float*>(p.out) + at, v);
 }
 
-// Vector path: m a multiple of 8, every full-tensor and column leaf and the output 16-byte
-// aligned with whole 16-byte units per column (checked on the host).  A thread takes 8 consecutive
-// rows of one column (one index split per thread), loads 8 entries of a full or column leaf with
-// 16-byte loads, one entry of a row or scalar leaf, and stores its 8 outputs with 16-byte stores.
+struct EqRaw {   // 8 entries of a leaf as loaded: 16 bytes of bf16 (lo), or 32 of fp32
+  u32x4 lo, hi;
+};
+__device__ __forceinline__ void eq_load8(EqRaw& w, const void* ptr, bool bf16) {
+  if (bf16) {
+    w.lo = gld<u32x4_a2>(ptr);
+  } else {
+    w.lo = gld<u32x4_a4>(ptr);
+    w.hi = gld<u32x4_a4>(static_cast<const char*>(ptr) + 16);
+  }
+}
+__device__ __forceinline__ void eq_widen8(const EqRaw& w, bool bf16, float (&o)[EPT]) {
+  if (bf16) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      o[2 * q] = __uint_as_float(w.lo[q] << 16);
+      o[2 * q + 1] = __uint_as_float(w.lo[q] & 0xffff0000u);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      o[q] = __uint_as_float(w.lo[q]);
+      o[q + 4] = __uint_as_float(w.hi[q]);
+    }
+  }
+}
+
+// The row-uniform part of a program (U): lane l computes it for column c0 + l (cn columns) into the
+// wavefront's file, slot by slot.
+__device__ __forceinline__ void eq_column_part(const EqArgs& p, uint32_t words, const EqArg& mine_u,
+                                               float* file, int32_t c0, int32_t cn) {
+  const int lane = threadIdx.x & 63;
+  const int32_t cu = c0 + (lane < cn ? lane : 0);
+  for (int32_t j0 = 0; j0 < p.n_uarg; j0 += 4) {
+    float x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const EqArg g = eq_arg_of(mine_u, j0 + k < p.n_uarg ? j0 + k : j0);
+      const int64_t e = g.bcast == TPP_BC_ROW ? cu : 0;
+      if (g.bf16)
+        x[k] = bf16_bits_to_f32(gld<uint16_t>(static_cast<const uint16_t*>(g.ptr) + e));
+      else
+        x[k] = gld<float>(static_cast<const float*>(g.ptr) + e);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (j0 + k < p.n_uarg) file[(j0 + k) * 64 + lane] = x[k];
+  }
+  for (int32_t i = 0; i < p.n_u; ++i) {
+    const uint32_t in = (uint32_t)__builtin_amdgcn_readlane((int)words, i);
+    const int32_t ar = eq_arity(in);
+    const float a = file[eq_src(in, 0) * 64 + lane];
+    const float b = ar > 1 ? file[eq_src(in, 1) * 64 + lane] : 0.0f;
+    const float cc = ar > 2 ? file[eq_src(in, 2) * 64 + lane] : 0.0f;
+    file[eq_dst(in) * 64 + lane] = eq_apply1(eq_op(in), a, b, cc);
+  }
+}
+
+// Chains, the programs of at least 8 rows whose per-element part is  x = leaf;  x = fma(x, X, Y) step
+// by step;  one unary operation at the end.  Add, sub, mul, neg and muladd onto the running value
+// are such steps with the same rounding (x + o = fma(x, 1, o), x o = fma(x, o, -0), and so on), X
+// and Y being values of the column (or 1 and -0) or V leaves.  These are the forms that norms,
+// softmaxes, biases, scalings and residuals take.  HBM-bound once nothing else is in the way:
+//   - No operand or operation dispatch per instruction (see equation_vec_kernel).  Steps on values
+//     of the column run in a loop of two LDS reads and eight fma; at most NVS steps have V leaves.
+//   - The part of the tree that is the same for all rows (its leaves are row or scalar leaves: a
+//     norm's mean, a softmax's reciprocal) runs once per column and not per element.  A wavefront
+//     owns one group of at most 64 row chunks (8 rows each) and cw consecutive columns: before its
+//     walk over them lane l computes that part for column c0 + l into the wavefront's LDS file.
+//   - A lane keeps its chunk for the whole walk (q columns a step when a column has fewer than 33
+//     chunks), so column leaves are loaded once; full leaves are loaded one step ahead.
+//   - Loads and stores are 16 bytes at any element alignment.  The last chunk of a column takes the
+//     8-row window that ends with it and stores its own rows one by one.
+// Layer norm's normalize step on 1024 x 8192 bf16: 20.5 us in equation_vec_kernel, 10.8 here;
+// softmax's exp(x - max) on 512 x 32768, bf16 to fp32: 26.0 and 21.6; its scaling by rcp(sum),
+// fp32 to bf16: 22.5 and 19.6 (100 MB each: 4.7 and 5.1 TB/s).
+// Order: n_step[0] column steps, V step A, n_step[1] column steps, V step B, n_step[2] column steps.
+struct EqWalk {   // the lane's part of a wavefront's region
+  int32_t c0, cn, sub, r, first;
+  bool mine;
+};
+__device__ __forceinline__ bool eq_walk(const EqArgs& p, int lane, int wave, EqWalk& k) {
+  const int64_t region = (int64_t)blockIdx.x * (EQ_T / 64) + wave;
+  const int64_t tile = region / p.ng;
+  if (tile >= p.tiles) return false;
+  const int32_t grp = (int32_t)(region - tile * p.ng);
+  k.c0 = (int32_t)(tile * p.cw);
+  k.cn = p.n - k.c0 < p.cw ? p.n - k.c0 : p.cw;
+  k.sub = lane / p.w;
+  const int32_t chunk = grp * p.w + (lane - k.sub * p.w);
+  k.mine = k.sub < p.q && chunk * 8 < p.m;
+  const int32_t r0 = k.mine ? chunk * 8 : 0;
+  k.first = r0 + 8 > p.m ? r0 + 8 - p.m : 0;
+  k.r = r0 - k.first;
+  return true;
+}
+
+template <bool OUT_BF16>
+__device__ __forceinline__ void eq_store8(void* out, int64_t o, int32_t first, const float (&v)[EPT]) {
+  if (first == 0) {
+    if (OUT_BF16) {
+      gst<u32x4_a2>(static_cast<uint16_t*>(out) + o,
+                    (u32x4){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
+                            pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])});
+    } else {
+      float* const q = static_cast<float*>(out) + o;
+      gst<f32x4_a4>(q, (f32x4){v[0], v[1], v[2], v[3]});
+      gst<f32x4_a4>(q + 4, (f32x4){v[4], v[5], v[6], v[7]});
+    }
+    return;
+  }
+#pragma unroll
+  for (int k = 1; k < EPT; ++k) {
+    if (k < first) continue;
+    if (OUT_BF16)
+      gst<uint16_t>(static_cast<uint16_t*>(out) + o + k, f32_to_bf16_bits(v[k]));
+    else
+      gst<float>(static_cast<float*>(out) + o + k, v[k]);
+  }
+}
+
+// v = op(a) for a unary operation, one dispatch for the 8 elements.
+__device__ __forceinline__ void eq_unary8(int32_t op, const float (&a)[EPT], float (&v)[EPT]) {
+  const float(&b)[EPT] = a, (&cc)[EPT] = a;
+  TPP_EQ_APPLY(op)
+}
+
+template <bool OUT_BF16, int NVS>
+__global__ __launch_bounds__(EQ_T) void equation_chain_kernel(EqArgs p) {
+  constexpr int NL = 1 + 2 * NVS;      // leaves: the first, then X and Y of each V step
+  extern __shared__ float eq_file[];   // [4 waves][uslots][64 columns]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  EqWalk k;
+  if (!eq_walk(p, lane, wave, k)) return;   // wave-uniform; no workgroup barrier below
+  float* const file = eq_file + wave * p.uslots * 64;
+
+  EqRaw raw[NL];
+  const char* at[NL];
+  int64_t step[NL];
+  int32_t ci = k.sub;                  // the lane's column is c0 + ci
+  bool ok = k.mine && ci < k.cn;
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const EqArg& g = p.varg[j];
+    const int64_t es = g.bf16 ? 2 : 4;
+    const bool full = g.bcast == TPP_BC_NONE;
+    at[j] = static_cast<const char*>(g.ptr) + (k.r + (full ? ((int64_t)k.c0 + ci) * g.ld : 0)) * es;
+    step[j] = full ? p.q * g.ld * es : 0;
+    if (ok && g.ptr) eq_load8(raw[j], at[j], g.bf16 != 0);
+  }
+  eq_column_part(p, p.n_u > 0 ? p.instr[lane] : 0u, p.uarg[lane & (EQ_MAX_ARGS - 1)], file, k.c0,
+                 k.cn);
+  file[(p.uslots - 2) * 64 + lane] = 1.0f;
+  file[(p.uslots - 1) * 64 + lane] = -0.0f;
+
+  for (int32_t cs = 0; cs < k.cn; cs += p.q) {   // uniform; ci = cs + sub
+    const bool ok_next = k.mine && ci + p.q < k.cn;
+    const float* const col = file + (ok ? ci : 0);
+    float x[EPT], op[2 * NVS > 0 ? 2 * NVS : 1][EPT];
+    eq_widen8(raw[0], p.varg[0].bf16 != 0, x);
+#pragma unroll
+    for (int j = 1; j < NL; ++j)
+      if (p.varg[j].ptr) eq_widen8(raw[j], p.varg[j].bf16 != 0, op[j - 1]);
+    // the next step's full leaves, in flight during this one
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      at[j] += step[j];
+      if (ok_next && step[j] != 0) eq_load8(raw[j], at[j], p.varg[j].bf16 != 0);
+    }
+    int32_t s = 0;
+#pragma unroll
+    for (int a = 0; a <= NVS; ++a) {
+      for (int32_t e = s + p.n_step[a]; s < e; ++s) {
+        const EqStep st = p.step[s];
+        const float X = __uint_as_float(__float_as_uint(col[st.x * 64]) ^ st.xsign);
+        const float Y = __uint_as_float(__float_as_uint(col[st.y * 64]) ^ st.ysign);
+#pragma unroll
+        for (int q = 0; q < EPT; ++q) x[q] = __builtin_fmaf(x[q], X, Y);
+      }
+      if (a < NVS) {
+        const EqStep st = p.vstep[a];
+        float(&X)[EPT] = op[2 * a < 2 * NVS ? 2 * a : 0];
+        float(&Y)[EPT] = op[2 * a + 1 < 2 * NVS ? 2 * a + 1 : 0];
+        if (!p.varg[1 + 2 * a].ptr) {
+          const float u = col[st.x * 64];
+#pragma unroll
+          for (int q = 0; q < EPT; ++q) X[q] = u;
+        }
+        if (!p.varg[2 + 2 * a].ptr) {
+          const float u = col[st.y * 64];
+#pragma unroll
+          for (int q = 0; q < EPT; ++q) Y[q] = u;
+        }
+#pragma unroll
+        for (int q = 0; q < EPT; ++q)
+          x[q] = __builtin_fmaf(x[q], __uint_as_float(__float_as_uint(X[q]) ^ st.xsign),
+                                __uint_as_float(__float_as_uint(Y[q]) ^ st.ysign));
+      }
+    }
+    const int64_t o = (int64_t)k.r + ((int64_t)k.c0 + ci) * p.ldo;
+    if (p.act == TPP_EQ_IDENTITY) {
+      if (ok) eq_store8<OUT_BF16>(p.out, o, k.first, x);
+    } else {
+      float v[EPT];
+      eq_unary8(p.act, x, v);
+      if (ok) eq_store8<OUT_BF16>(p.out, o, k.first, v);
+    }
+    ci += p.q;
+    ok = ok_next;
+  }
+}
+
+// Everything else of at least 8 rows: a thread takes 8 consecutive rows of one column (one index
+// split per thread), 8 entries of a full or column leaf as one 16-byte load or two, one entry of a
+// row or scalar leaf, and stores its 8 outputs the same way, at any element alignment; the last
+// rows of a column as in eq_walk.  Leaves are loaded when their instruction runs: preloading them
+// (and evaluating the row-uniform part once per column) in this interpreter, whose switches the
+// compiler structures over 8-element arrays, took 121 against 79 us on the 4096 x 4096 fp32 example
+// (164 registers against 82).
 // NTMP: the temporaries the plan uses are below NTMP (fewer registers, more waves in flight).
 template <bool OUT_BF16, int NTMP>
-__global__ __launch_bounds__(EQ_T) void equation_vec_kernel(EqProgram p) {
-  const int64_t groups = (int64_t)p.m * p.n / EPT;
+__global__ __launch_bounds__(EQ_T) void equation_vec_kernel(EqArgs p) {
+  const int32_t chunks = (p.m - 1) / EPT + 1;
+  const int64_t groups = (int64_t)chunks * p.n;
   for (int64_t gidx = (int64_t)blockIdx.x * EQ_T + threadIdx.x; gidx < groups;
        gidx += (int64_t)gridDim.x * EQ_T) {
-    const int64_t e0 = gidx * EPT;
-    const int32_t c = (int32_t)(e0 / p.m);
-    const int32_t r = (int32_t)(e0 - (int64_t)c * p.m);
+    const int32_t c = (int32_t)(gidx / chunks);
+    const int32_t r0 = (int32_t)(gidx - (int64_t)c * chunks) * EPT;
+    const int32_t first = r0 + EPT > p.m ? r0 + EPT - p.m : 0;
+    const int32_t r = r0 - first;
     float t0[EPT], t1[EPT], t2[EPT], t3[EPT], t4[EPT], t5[EPT], t6[EPT], t7[EPT];
 #define TPP_EQ_TMP_CASE(j, o) \
     case j: if constexpr (j < NTMP) { _Pragma("unroll") for (int k = 0; k < EPT; ++k) o[k] = t##j[k]; } break;
@@ -403,18 +632,18 @@ __global__ __launch_bounds__(EQ_T) void equation_vec_kernel(EqProgram p) {
       TPP_EQ_TMP_CASE(0, o) TPP_EQ_TMP_CASE(1, o) TPP_EQ_TMP_CASE(2, o) TPP_EQ_TMP_CASE(3, o)     \
       TPP_EQ_TMP_CASE(4, o) TPP_EQ_TMP_CASE(5, o) TPP_EQ_TMP_CASE(6, o) TPP_EQ_TMP_CASE(7, o)     \
       default: {                                                                                \
-        const EqArg& g = p.arg[(code) - EQ_LEAF_BASE];                                          \
+        const EqArg& g = p.varg[(code) - EQ_V_LEAF];                                            \
         if (g.bcast == TPP_BC_NONE || g.bcast == TPP_BC_COL) {                                  \
           const int64_t at = g.bcast == TPP_BC_NONE ? (int64_t)r + (int64_t)c * g.ld : r;       \
           if (g.bf16) {                                                                         \
-            const u32x4 w = gld<u32x4>(static_cast<const uint16_t*>(g.ptr) + at);              \
+            const u32x4 w = gld<u32x4_a2>(static_cast<const uint16_t*>(g.ptr) + at);           \
             _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                     \
               o[2 * q] = __uint_as_float(w[q] << 16);                                           \
               o[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);                               \
             }                                                                                   \
           } else {                                                                              \
-            const f32x4 lo = gld<f32x4>(static_cast<const float*>(g.ptr) + at);                \
-            const f32x4 hi = gld<f32x4>(static_cast<const float*>(g.ptr) + at + 4);            \
+            const f32x4 lo = gld<f32x4_a4>(static_cast<const float*>(g.ptr) + at);             \
+            const f32x4 hi = gld<f32x4_a4>(static_cast<const float*>(g.ptr) + at + 4);         \
             _Pragma("unroll") for (int q = 0; q < 4; ++q) { o[q] = lo[q]; o[q + 4] = hi[q]; }   \
           }                                                                                     \
         } else {                                                                                \
@@ -433,67 +662,243 @@ __global__ __launch_bounds__(EQ_T) void equation_vec_kernel(EqProgram p) {
       TPP_EQ_PUT_CASE(4) TPP_EQ_PUT_CASE(5) TPP_EQ_PUT_CASE(6) TPP_EQ_PUT_CASE(7)                \
       default: break;                                                                           \
     }
-    for (int32_t i = 0; i < p.n_instr; ++i) {
-      const EqInstr& in = p.instr[i];
+    for (int32_t i = 0; i < p.n_v; ++i) {
+      const uint32_t in = p.instr[i];
       float a[EPT], b[EPT], cc[EPT], v[EPT];
-      FETCH(in.src[0], a)
-      if (in.arity > 1) { FETCH(in.src[1], b) }
-      if (in.arity > 2) { FETCH(in.src[2], cc) }
-      TPP_EQ_APPLY(in.op)
-      PUT(in.dst)
+      FETCH(eq_src(in, 0), a)
+      if (eq_arity(in) > 1) { FETCH(eq_src(in, 1), b) }
+      if (eq_arity(in) > 2) { FETCH(eq_src(in, 2), cc) }
+      TPP_EQ_APPLY(eq_op(in))
+      PUT(eq_dst(in))
     }
     float res[EPT];
-    FETCH(p.result, res)
+    FETCH(eq_dst(p.instr[p.n_v - 1]), res)
 #undef FETCH
 #undef PUT
 #undef TPP_EQ_TMP_CASE
 #undef TPP_EQ_PUT_CASE
-    const int64_t at = (int64_t)r + (int64_t)c * p.ldo;
-    if (OUT_BF16) {
-      gst<u32x4>(static_cast<uint16_t*>(p.out) + at,
-                 (u32x4){pack_bf16x2(res[0], res[1]), pack_bf16x2(res[2], res[3]),
-                         pack_bf16x2(res[4], res[5]), pack_bf16x2(res[6], res[7])});
+    eq_store8<OUT_BF16>(p.out, (int64_t)r + (int64_t)c * p.ldo, first, res);
+  }
+}
+
+// ---- the kernels' form of a program (host) ---------------------------------------------------
+uint32_t eq_word(int32_t op, int32_t arity, int32_t dst, const int32_t (&src)[3]) {
+  return (uint32_t)op | (uint32_t)arity << 6 | (uint32_t)dst << 8 | (uint32_t)src[0] << 14 |
+         (uint32_t)src[1] << 20 | (uint32_t)src[2] << 26;
+}
+
+// The program as it is, every leaf in varg (the kernels for fewer than 8 rows).
+void pack_plain(const EqProgram& p, EqArgs& k) {
+  for (int32_t i = 0; i < p.n_instr; ++i) {
+    const EqInstr& in = p.instr[i];
+    int32_t src[3];
+    for (int a = 0; a < 3; ++a)
+      src[a] = in.src[a] >= EQ_LEAF_BASE ? EQ_V_LEAF + in.src[a] - EQ_LEAF_BASE : in.src[a];
+    k.instr[i] = eq_word(in.op, in.arity, in.dst, src);
+  }
+  k.n_v = p.n_instr;
+  k.n_varg = p.n_args;
+  for (int32_t j = 0; j < p.n_args; ++j) k.varg[j] = p.arg[j];
+}
+
+// Split into the part that is the same for all rows (U: leaves and operations that depend on row
+// and scalar leaves only, each in a slot of its own of the column file) and the rest (V: the plan's
+// temporaries; leaves in order of first use).
+void pack_split(const EqProgram& p, EqArgs& k) {
+  int32_t vslot[EQ_MAX_ARGS], uslot[EQ_MAX_ARGS], tmp_u[EQ_MAX_TMPS];
+  for (int32_t j = 0; j < EQ_MAX_ARGS; ++j) vslot[j] = uslot[j] = -1;
+  for (int32_t j = 0; j < EQ_MAX_TMPS; ++j) tmp_u[j] = -1;   // U slot of the temporary's value
+  // U leaves take the first slots, so that their loads can be counted; every leaf that is used
+  for (int32_t i = 0; i < p.n_instr; ++i)
+    for (int a = 0; a < p.instr[i].arity; ++a) {
+      const int32_t j = p.instr[i].src[a] - EQ_LEAF_BASE;
+      if (j < 0) continue;
+      const EqArg& g = p.arg[j];
+      if (g.bcast == TPP_BC_ROW || g.bcast == TPP_BC_SCALAR) {
+        if (uslot[j] < 0) {
+          uslot[j] = k.n_uarg;
+          k.uarg[k.n_uarg++] = g;
+        }
+      } else if (vslot[j] < 0) {
+        vslot[j] = k.n_varg;
+        k.varg[k.n_varg++] = g;
+      }
+    }
+  k.uslots = k.n_uarg;
+  int32_t n_v = 0;
+  uint32_t vword[EQ_MAX_NODES];
+  for (int32_t i = 0; i < p.n_instr; ++i) {
+    const EqInstr& in = p.instr[i];
+    const bool root = i + 1 == p.n_instr;
+    int32_t us[3] = {0, 0, 0}, vs[3] = {0, 0, 0};
+    bool uniform = !root && k.uslots < EQ_MAX_USLOTS;
+    for (int a = 0; a < in.arity; ++a) {
+      const int32_t s = in.src[a];
+      const int32_t u = s >= EQ_LEAF_BASE ? uslot[s - EQ_LEAF_BASE] : tmp_u[s];
+      us[a] = u;
+      vs[a] = u >= 0 ? EQ_U_SLOT + u : s >= EQ_LEAF_BASE ? EQ_V_LEAF + vslot[s - EQ_LEAF_BASE] : s;
+      uniform = uniform && u >= 0;
+    }
+    if (uniform) {
+      k.instr[k.n_u++] = eq_word(in.op, in.arity, k.uslots, us);
+      tmp_u[in.dst] = k.uslots++;
     } else {
-      float* q = static_cast<float*>(p.out) + at;
-      gst<f32x4>(q, (f32x4){res[0], res[1], res[2], res[3]});
-      gst<f32x4>(q + 4, (f32x4){res[4], res[5], res[6], res[7]});
+      vword[n_v++] = eq_word(in.op, in.arity, in.dst, vs);
+      tmp_u[in.dst] = -1;
     }
   }
+  for (int32_t i = 0; i < n_v; ++i) k.instr[k.n_u + i] = vword[i];
+  k.n_v = n_v;
+}
+
+// Whether the split program k (its n_v instructions) is a chain that equation_chain_kernel runs, and
+// then its steps; *n_vsteps: how many of them have V leaves.
+bool pack_chain(EqArgs& k, int32_t* n_vsteps) {
+  const auto is_leaf = [](int32_t c) { return c >= EQ_V_LEAF && c < EQ_U_SLOT; };
+  const auto is_u = [](int32_t c) { return c >= EQ_U_SLOT; };
+  if (k.uslots + 2 > EQ_MAX_USLOTS) return false;
+  const int32_t one = k.uslots, nzero = k.uslots + 1;
+  constexpr uint32_t NEG = 0x80000000u;
+  EqStep step[EQ_MAX_STEPS], vstep[2];
+  EqArg varg[5] = {};
+  int32_t n = 0, nv = 0, n_step[3] = {0, 0, 0};
+  int32_t act = TPP_EQ_IDENTITY, prev = -1;
+  for (int32_t i = 0; i < k.n_v; ++i) {
+    const uint32_t w = k.instr[k.n_u + i];
+    const int32_t op = (int32_t)(w & 63u), ar = (int32_t)(w >> 6 & 3u);
+    int32_t o[3], at = -1;
+    for (int a = 0; a < 3; ++a) o[a] = (int32_t)(w >> (14 + 6 * a) & 63u);
+    // the running value among the operands: the previous result, or (first) a V leaf, a full one
+    // if there is one
+    for (int a = 0; a < ar; ++a) {
+      if (i > 0) {
+        if (o[a] == prev) at = at < 0 ? a : 3;
+        else if (!is_leaf(o[a]) && !is_u(o[a])) return false;   // an older temporary
+      } else if (is_leaf(o[a])) {
+        const bool full = k.varg[o[a] - EQ_V_LEAF].bcast == TPP_BC_NONE;
+        if (at < 0 || (full && k.varg[o[at] - EQ_V_LEAF].bcast != TPP_BC_NONE)) at = a;
+      }
+    }
+    if (at < 0 || at > 2) return false;   // not there, or there twice
+    if (i == 0) varg[0] = k.varg[o[at] - EQ_V_LEAF];
+    prev = (int32_t)(w >> 8 & 63u);
+    // X and Y as operand codes; -1: the constant 1 (X) or -0 (Y)
+    int32_t X = -1, Y = -1;
+    uint32_t xs = 0, ys = 0;
+    if (op == TPP_EQ_IDENTITY) continue;
+    else if (op == TPP_EQ_NEG) xs = NEG;
+    else if (op == TPP_EQ_ADD) Y = o[1 - at];
+    else if (op == TPP_EQ_SUB) {
+      Y = o[1 - at];
+      if (at == 0) ys = NEG;
+      else xs = NEG;
+    } else if (op == TPP_EQ_MUL) X = o[1 - at];
+    else if (op == TPP_EQ_MULADD && at < 2) {
+      X = o[1 - at];
+      Y = o[2];
+    } else if (ar == 1 && i + 1 == k.n_v) {
+      act = op;
+      break;
+    } else return false;
+    EqStep st = {X < 0 ? one : is_u(X) ? X - EQ_U_SLOT : 0, Y < 0 ? nzero : is_u(Y) ? Y - EQ_U_SLOT : 0,
+                 xs, ys};
+    if (is_leaf(X) || is_leaf(Y)) {
+      if (nv == 2) return false;
+      if (is_leaf(X)) varg[1 + 2 * nv] = k.varg[X - EQ_V_LEAF];
+      if (is_leaf(Y)) varg[2 + 2 * nv] = k.varg[Y - EQ_V_LEAF];
+      vstep[nv++] = st;
+    } else {
+      if (n == EQ_MAX_STEPS) return false;
+      step[n++] = st;
+      ++n_step[nv];
+    }
+  }
+  for (int j = 0; j < 5; ++j) k.varg[j] = varg[j];
+  for (int j = 0; j < n; ++j) k.step[j] = step[j];
+  for (int j = 0; j < nv; ++j) k.vstep[j] = vstep[j];
+  for (int j = 0; j < 3; ++j) k.n_step[j] = n_step[j];
+  k.act = act;
+  k.uslots += 2;
+  *n_vsteps = nv;
+  return true;
 }
 
 }  // namespace
 
-// The vector path's conditions: m a multiple of 8; every full-tensor or column leaf and the
-// output 16-byte aligned, with column strides of whole 16-byte units.
-static bool prog_vec(const EqProgram& p) {
-  const auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  if (p.m % EPT != 0 || !al(p.out) || (p.ldo * (p.out_bf16 ? 2 : 4)) % 16 != 0) return false;
-  for (int32_t k = 0; k < p.n_args; ++k) {
-    const EqArg& g = p.arg[k];
-    if (g.bcast != TPP_BC_NONE && g.bcast != TPP_BC_COL) continue;
-    if (!al(g.ptr)) return false;
-    if (g.bcast == TPP_BC_NONE && (g.ld * (g.bf16 ? 2 : 4)) % 16 != 0) return false;
-  }
-  return true;
-}
-
 hipError_t launch_equation(const EqProgram& prog, hipStream_t stream) {
   if (prog.m == 0 || prog.n == 0) return hipSuccess;
+  EqArgs k = {};
+  k.m = prog.m;
+  k.n = prog.n;
+  k.ldo = prog.ldo;
+  k.out = prog.out;
+  EqProgram flat;
+  const EqProgram* use = &prog;
   const int64_t total = (int64_t)prog.m * prog.n;
-  // enough workgroups for every element once, at most 8 per CU on the 256 CUs (grid stride
-  // beyond)
-  int64_t blocks = (total + EPT * EQ_T - 1) / (EPT * EQ_T);
-  if (blocks > 8 * 256) blocks = 8 * 256;
-  const dim3 grid((unsigned)blocks);
-  const bool wide = total > 0xffffffffLL;
-  if (prog_vec(prog)) {
-    int64_t vblocks = (total / EPT + EQ_T - 1) / EQ_T;
-    if (vblocks > 8 * 256) vblocks = 8 * 256;
-    int32_t ntmp = prog.result + 1;
-    for (int32_t i = 0; i < prog.n_instr; ++i)
-      if (prog.instr[i].dst + 1 > ntmp) ntmp = prog.instr[i].dst + 1;
+  if (prog.m < 8 && total > EQ_SMALL && total <= 0x7fffffff) {
+    // Fewer than 8 contiguous rows (a long row of statistics): the same elements as one column.
+    // A row leaf of a single row is then a full one, a column leaf of a single row a scalar.
+    bool flattens = prog.ldo == prog.m;
+    for (int32_t j = 0; j < prog.n_args; ++j) {
+      const EqArg& g = prog.arg[j];
+      if (g.bcast == TPP_BC_NONE) flattens = flattens && g.ld == prog.m;
+      else if (g.bcast != TPP_BC_SCALAR) flattens = flattens && prog.m == 1;
+    }
+    if (flattens) {
+      flat = prog;
+      for (int32_t j = 0; j < prog.n_args; ++j) {
+        EqArg& g = flat.arg[j];
+        if (g.bcast == TPP_BC_COL) g.bcast = TPP_BC_SCALAR;
+        else if (g.bcast == TPP_BC_ROW) g.bcast = TPP_BC_NONE;
+        g.ld = total;
+      }
+      flat.m = k.m = (int32_t)total;
+      flat.n = k.n = 1;
+      flat.ldo = k.ldo = total;
+      use = &flat;
+    }
+  }
+  if (use->m >= 8) {
+    const int32_t chunks = (use->m - 1) / EPT + 1;
+    EqArgs ch = k;
+    int32_t n_vsteps = 0;
+    pack_split(*use, ch);
+    if (pack_chain(ch, &n_vsteps)) {
+      ch.ng = (chunks + 63) / 64;
+      ch.w = (chunks + ch.ng - 1) / ch.ng;
+      ch.q = 64 / ch.w;
+      // Columns per wavefront: enough steps to reuse its column leaves and its column values, while
+      // about 16 wavefronts per CU (4096) still share the work; at most the 64 columns of its file.
+      const int64_t steps = (int64_t)ch.ng * ((use->n + ch.q - 1) / ch.q);
+      int64_t per = steps / 4096;
+      if (per < 1) per = 1;
+      if (per > 64 / ch.q) per = 64 / ch.q;
+      ch.cw = (int32_t)per * ch.q;
+      ch.tiles = (use->n + ch.cw - 1) / ch.cw;
+      const dim3 grid((unsigned)((ch.tiles * ch.ng + EQ_T / 64 - 1) / (EQ_T / 64)));
+      const unsigned lds = (unsigned)(ch.uslots * 64 * 4 * (EQ_T / 64));
+#define TPP_EQ_CHAIN(B, N) \
+  hipLaunchKernelGGL((equation_chain_kernel<B, N>), grid, dim3(EQ_T), lds, stream, ch)
+      if (prog.out_bf16) {
+        if (n_vsteps == 0) TPP_EQ_CHAIN(true, 0);
+        else if (n_vsteps == 1) TPP_EQ_CHAIN(true, 1);
+        else TPP_EQ_CHAIN(true, 2);
+      } else {
+        if (n_vsteps == 0) TPP_EQ_CHAIN(false, 0);
+        else if (n_vsteps == 1) TPP_EQ_CHAIN(false, 1);
+        else TPP_EQ_CHAIN(false, 2);
+      }
+#undef TPP_EQ_CHAIN
+      return hipGetLastError();
+    }
+    pack_plain(*use, k);
+    int64_t vblocks = ((int64_t)chunks * use->n + EQ_T - 1) / EQ_T;
+    if (vblocks > 8 * 256) vblocks = 8 * 256;   // at most 8 per CU, grid stride beyond
+    int32_t ntmp = 0;
+    for (int32_t i = 0; i < use->n_instr; ++i)
+      if (use->instr[i].dst + 1 > ntmp) ntmp = use->instr[i].dst + 1;
     const dim3 vgrid((unsigned)vblocks);
-#define TPP_EQ_VEC(B, N) hipLaunchKernelGGL((equation_vec_kernel<B, N>), vgrid, dim3(EQ_T), 0, stream, prog)
+#define TPP_EQ_VEC(B, N) hipLaunchKernelGGL((equation_vec_kernel<B, N>), vgrid, dim3(EQ_T), 0, stream, k)
     if (prog.out_bf16) {
       if (ntmp <= 2) TPP_EQ_VEC(true, 2);
       else if (ntmp <= 4) TPP_EQ_VEC(true, 4);
@@ -504,18 +909,30 @@ hipError_t launch_equation(const EqProgram& prog, hipStream_t stream) {
       else TPP_EQ_VEC(false, EQ_MAX_TMPS);
     }
 #undef TPP_EQ_VEC
-  } else if (total <= EQ_SMALL) {
+    return hipGetLastError();
+  }
+  pack_plain(prog, k);
+  if (total <= EQ_SMALL) {
     const dim3 sgrid((unsigned)((total + EQ_T - 1) / EQ_T));
+    const unsigned lds = (unsigned)((EQ_V_LEAF + k.n_varg) * EQ_T * 4);
     if (prog.out_bf16)
-      hipLaunchKernelGGL((equation_small_kernel<true>), sgrid, dim3(EQ_T), 0, stream, prog);
+      hipLaunchKernelGGL((equation_small_kernel<true>), sgrid, dim3(EQ_T), lds, stream, k);
     else
-      hipLaunchKernelGGL((equation_small_kernel<false>), sgrid, dim3(EQ_T), 0, stream, prog);
-  } else if (prog.out_bf16) {
-    if (wide) hipLaunchKernelGGL((equation_kernel<true, true>), grid, dim3(EQ_T), 0, stream, prog);
-    else hipLaunchKernelGGL((equation_kernel<true, false>), grid, dim3(EQ_T), 0, stream, prog);
+      hipLaunchKernelGGL((equation_small_kernel<false>), sgrid, dim3(EQ_T), lds, stream, k);
+    return hipGetLastError();
+  }
+  // enough workgroups for every element once, at most 8 per CU on the 256 CUs (grid stride
+  // beyond)
+  int64_t blocks = (total + EPT * EQ_T - 1) / (EPT * EQ_T);
+  if (blocks > 8 * 256) blocks = 8 * 256;
+  const dim3 grid((unsigned)blocks);
+  const bool wide = total > 0xffffffffLL;
+  if (prog.out_bf16) {
+    if (wide) hipLaunchKernelGGL((equation_kernel<true, true>), grid, dim3(EQ_T), 0, stream, k);
+    else hipLaunchKernelGGL((equation_kernel<true, false>), grid, dim3(EQ_T), 0, stream, k);
   } else {
-    if (wide) hipLaunchKernelGGL((equation_kernel<false, true>), grid, dim3(EQ_T), 0, stream, prog);
-    else hipLaunchKernelGGL((equation_kernel<false, false>), grid, dim3(EQ_T), 0, stream, prog);
+    if (wide) hipLaunchKernelGGL((equation_kernel<false, true>), grid, dim3(EQ_T), 0, stream, k);
+    else hipLaunchKernelGGL((equation_kernel<false, false>), grid, dim3(EQ_T), 0, stream, k);
   }
   return hipGetLastError();
 }

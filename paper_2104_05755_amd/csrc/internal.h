@@ -175,9 +175,6 @@ constexpr int EQ_MAX_NODES = 64;
 constexpr int EQ_MAX_TMPS = 8;
 constexpr int EQ_MAX_ARGS = 16;
 constexpr int EQ_LEAF_BASE = 16;
-// The kernel reads these arrays at indices known only at run time, with scalar loads from the
-// kernel-argument block; every element is a whole number of dwords, so every such address stays
-// dword aligned (scalar loads drop the low address bits).
 struct EqInstr {
   int32_t op, arity, dst;
   int32_t src[3];
@@ -188,8 +185,7 @@ struct EqArg {
   int32_t bf16, bcast;
 };
 struct EqProgram {
-  int32_t n_instr;
-  int32_t result;                       // temporary holding the root's value
+  int32_t n_instr;                      // the last one is the root
   int32_t m, n;
   int64_t ldo;
   void* out;
@@ -197,20 +193,38 @@ struct EqProgram {
   EqInstr instr[EQ_MAX_NODES];
   EqArg arg[EQ_MAX_ARGS];
 };
-// Layout guards for the scalar-load reads above: every record, and every field the kernel reads
-// from a record, sits at a whole-dword offset, and the arrays start on dword boundaries.
-static_assert(sizeof(EqInstr) == 24 && sizeof(EqInstr) % 4 == 0, "EqInstr is 6 dwords");
-static_assert(offsetof(EqInstr, op) == 0 && offsetof(EqInstr, arity) == 4 &&
-                  offsetof(EqInstr, dst) == 8 && offsetof(EqInstr, src) == 12,
-              "EqInstr fields on dword boundaries");
-static_assert(sizeof(EqArg) == 24 && sizeof(EqArg) % 8 == 0, "EqArg is 3 qwords");
-static_assert(offsetof(EqArg, ptr) == 0 && offsetof(EqArg, ld) == 8 &&
-                  offsetof(EqArg, bf16) == 16 && offsetof(EqArg, bcast) == 20,
-              "EqArg fields on dword boundaries");
-static_assert(offsetof(EqProgram, instr) % 8 == 0 && offsetof(EqProgram, arg) % 8 == 0 &&
-                  offsetof(EqProgram, ldo) % 8 == 0 && offsetof(EqProgram, out) % 8 == 0,
-              "EqProgram arrays and 64-bit fields 8-byte aligned");
-static_assert(sizeof(EqProgram) % 8 == 0, "EqProgram a whole number of qwords");
+// A program as the executor kernels take it: one word per instruction (op 6 bits, arity 2,
+// destination 6, three operand codes of 6), n_u instructions that run once per column and then
+// n_v that run per element; leaf tables.  An operand code is a temporary, EQ_V_LEAF + a leaf of
+// varg, or EQ_U_SLOT + a slot of the column file (slots 0 .. n_uarg - 1 hold the leaves of uarg);
+// in the n_u instructions every code is a slot.
+constexpr int EQ_V_LEAF = EQ_MAX_TMPS;
+constexpr int EQ_U_SLOT = EQ_V_LEAF + EQ_MAX_ARGS;
+constexpr int EQ_MAX_USLOTS = 32;
+static_assert(EQ_U_SLOT + EQ_MAX_USLOTS <= 64, "operand codes fit 6 bits");
+// One step x = fma(x, X, Y) of a chain: slots of X and Y in the column file, sign bits to flip.
+struct EqStep {
+  int32_t x, y;
+  uint32_t xsign, ysign;
+};
+constexpr int EQ_MAX_STEPS = 8;
+struct EqArgs {
+  int32_t n_u, n_v, n_varg, n_uarg;
+  int32_t uslots, m, n;
+  // equation_chain_kernel: row-chunk groups per column, chunks of a group, columns per step and per
+  // wavefront, column tiles
+  int32_t ng, w, q, cw;
+  int64_t tiles;
+  int64_t ldo;
+  void* out;
+  uint32_t instr[EQ_MAX_NODES];
+  EqArg varg[EQ_MAX_ARGS], uarg[EQ_MAX_ARGS];
+  // equation_chain_kernel: steps on values of the column, steps with V leaves (varg[0] is the first
+  // leaf, varg[1 + 2 a] and varg[2 + 2 a] X and Y of V step a, ptr null where it is a slot), how
+  // many of the former come before, between and after the latter, and the last unary operation
+  EqStep step[EQ_MAX_STEPS], vstep[2];
+  int32_t n_step[3], act;
+};
 // nullptr on success, else what is wrong with the tree.
 const char* equation_plan(const tpp_eq_node* nodes, int32_t n_nodes, int32_t root,
                           tpp_eq_plan_node* plan, int32_t* n_tmps);
