@@ -12,7 +12,9 @@ The library must have been built (``__graft_entry__.build()`` or
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import struct
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libtpp_mi355x.so")
@@ -111,8 +113,8 @@ TPP_BC = {"none": 0, "col": 1, "row": 2, "scalar": 3}
 
 _sig("tpp_equation_plan", _i32, ctypes.POINTER(tpp_eq_node), _i32, _i32,
      ctypes.POINTER(tpp_eq_plan_node), ctypes.POINTER(_i32))
-_sig("tpp_equation_execute", _i32, ctypes.POINTER(tpp_eq_node), _i32, _i32, _i32, _i32,
-     ctypes.POINTER(tpp_eq_arg), _i32, _c_void_p, _i64, _i32, _c_void_p)
+_sig("tpp_equation_execute", _i32, _c_void_p, _i32, _i32, _i32, _i32, _c_void_p, _i32, _c_void_p,
+     _i64, _i32, _c_void_p)
 _sig("tpp_embedding_bag", _i32, _i64, _i32, _i32, _c_void_p, _i64, _i64, _c_void_p, _c_void_p,
      _i32, _c_void_p, _i64, _c_void_p)
 _sig("tpp_reduce_batched", _i32, _i32, _i32, _i64, _i32, _c_void_p, _i64, _i64, _i32,
@@ -275,14 +277,28 @@ def tpp_equation_plan(nodes, root):
     return ([p.score for p in plan], [p.timestamp for p in plan], [p.tmp for p in plan], nt.value)
 
 
+_EQ_ARG = struct.Struct("Pqii")   # tpp_eq_arg
+assert _EQ_ARG.size == ctypes.sizeof(tpp_eq_arg)
+
+
+@functools.lru_cache(maxsize=256)
+def _eq_node_bytes(nodes: tuple) -> bytes:
+    """The tpp_eq_node array of a tree, as bytes.  Kept by the tree's own content (a program runs
+    the same few trees on every call, and filling the array through ctypes fields took 5 us of the
+    11 us that a layer norm's equation call took on the host, where its kernel takes as long)."""
+    return bytes(eq_nodes(nodes))
+
+
 def tpp_equation_execute(nodes, root, m, n, args, out, ldo, out_type, stream=None):
     """args: list of (tensor or address, ld, dtype code, broadcast name)."""
-    arr = eq_nodes(nodes)
-    ga = (tpp_eq_arg * max(1, len(args)))()
-    for i, (x, ld, dt, bc) in enumerate(args):
-        ga[i].ptr, ga[i].ld, ga[i].dtype, ga[i].bcast = _p(x), ld, dt, TPP_BC[bc]
-    _check(_lib.tpp_equation_execute(arr, len(nodes), root, m, n, ga, len(args), _p(out), ldo,
-                                     out_type, stream), "tpp_equation_execute")
+    try:
+        arr = _eq_node_bytes(tuple(nodes))
+    except TypeError:   # nodes given as lists
+        arr = bytes(eq_nodes(nodes))
+    pack = _EQ_ARG.pack
+    ga = b"".join([pack(_p(x) or 0, ld, dt, TPP_BC[bc]) for x, ld, dt, bc in args])
+    _check(_lib.tpp_equation_execute(arr, len(nodes), root, m, n, ga or None, len(args), _p(out),
+                                     ldo, out_type, stream), "tpp_equation_execute")
 
 
 def tpp_status_string(s: int) -> str:
