@@ -126,6 +126,7 @@ struct ReduceParams {
   int64_t G;
   int64_t in_stride;
   int64_t out_stride;
+  int32_t whole;   // 1: one partial per output whatever the shape (no work space)
 };
 // Number of floats of work space a reduce of this shape (and batch) needs: 0 if none, -1 if one
 // of its launches would need more than 2^31 - 1 workgroups.

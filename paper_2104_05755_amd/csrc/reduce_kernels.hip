@@ -4,12 +4,13 @@
 // columns with SUM / MUL / MIN / MAX, of x and/or of x*x, into fp32 outputs.  Reduction by
 // columns turns m x n into m x 1 (Sec. 3.1); reduction by rows gives 1 x n.
 //
-//   BY_ROWS (out[c] = fold over r): each column is contiguous, so one wavefront folds one
-//     column (or one row segment of it) with 16-byte loads per lane, then across its 64 lanes
-//     with cross-lane shuffles.
+//   BY_ROWS (out[c] = fold over r): each column is contiguous, so a group of 8 to 64 lanes folds a
+//     column (or a wavefront one row segment of it) with 16-byte loads, then across the lanes
+//     with register permutes.
 //   BY_COLS (out[r] = fold over c): a thread owns 16 bytes of consecutive rows and walks the
 //     columns of its workgroup's column range; the column lanes of a workgroup then meet in
 //     LDS.  Column ranges of different workgroups meet in a second, tiny pass.
+// 16-byte loads take any element alignment.  X2: x*x is wanted (else only x is folded).
 // A batch of G calls (the loop of Alg. 6 around the TPP) runs as one launch: each pass has its
 // per-call workgroups G times over, and workgroup b serves call b / per.
 // Arithmetic is fp32.  When a shape needs several partial results per output (row segments or
@@ -25,6 +26,11 @@ namespace tpp {
 namespace {
 
 constexpr int RT = 256;   // threads per workgroup
+
+template <int N>
+struct Count {
+  static constexpr int value = N;
+};
 
 template <int OP>
 __device__ __forceinline__ float fold(float acc, float v) {
@@ -42,11 +48,37 @@ __device__ __forceinline__ float fold_identity() {
   return -INFINITY;
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// Fold across groups of `lanes` (8, 16, 32 or 64) consecutive lanes; every lane gets the result.
+// Register permutes only: quad swaps and mirrors within a row of 16 lanes, then the row and half
+// swaps.  (Butterflies of shuffles go through the LDS unit, six waits on it per result.)
+template <int OP>
+__device__ __forceinline__ float lanes_fold(float v, int lanes) {
+  v = fold<OP>(v, dpp<0xB1>(v));    // lane ^ 1
+  v = fold<OP>(v, dpp<0x4E>(v));    // lane ^ 2
+  v = fold<OP>(v, dpp<0x141>(v));   // 7 - lane in each 8: the other quad
+  if (lanes >= 16) v = fold<OP>(v, dpp<0x140>(v));   // 15 - lane in each 16: the other 8
+  if (lanes >= 32) {
+    const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false,
+                                                    false);
+    v = fold<OP>(__uint_as_float(w[0]), __uint_as_float(w[1]));
+  }
+  if (lanes >= 64) {
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
+                                                    false);
+    v = fold<OP>(__uint_as_float(w[0]), __uint_as_float(w[1]));
+  }
+  return v;
+}
+
 template <int OP>
 __device__ __forceinline__ float wave_fold(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fold<OP>(v, __shfl_xor(v, off, 64));
-  return v;
+  return lanes_fold<OP>(v, 64);
 }
 
 template <bool BF16>
@@ -55,19 +87,20 @@ __device__ __forceinline__ float load1(const void* base, int64_t idx) {
   return static_cast<const float*>(base)[idx];
 }
 
-// V consecutive elements starting at idx (16 bytes, aligned): V = 8 for bf16, 4 for fp32.
+// V consecutive elements starting at idx (16 bytes): V = 8 for bf16, 4 for fp32.
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 template <bool BF16, int V>
 __device__ __forceinline__ void loadv(const void* base, int64_t idx, float out[V]) {
   if (BF16) {
-    const uint4 w = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + idx);
-    const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+    const u32x4_a2 w = *reinterpret_cast<const u32x4_a2*>(static_cast<const uint16_t*>(base) + idx);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      out[2 * e] = __uint_as_float(d[e] << 16);
-      out[2 * e + 1] = __uint_as_float(d[e] & 0xffff0000u);
+      out[2 * e] = __uint_as_float(w[e] << 16);
+      out[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
     }
   } else {
-    const float4 w = *reinterpret_cast<const float4*>(static_cast<const float*>(base) + idx);
+    const f32x4_a4 w = *reinterpret_cast<const f32x4_a4*>(static_cast<const float*>(base) + idx);
     out[0] = w.x; out[1] = w.y; out[2] = w.z; out[3] = w.w;
   }
 }
@@ -90,8 +123,8 @@ __device__ __forceinline__ int64_t batch_of(ReduceParams& p, int64_t per, float*
 }
 
 // BY_ROWS: wavefront wid folds rows [s*seg_rows, min(m, (s+1)*seg_rows)) of column c, where
-// c = wid % n, s = wid / n.  V == 1 means element loads.
-template <int OP, bool BF16, int V>
+// c = wid % n, s = wid / n.
+template <int OP, bool BF16, int V, bool X2>
 __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t seg_rows,
                                                          int32_t nseg, float* work, int64_t per) {
   const int lane = threadIdx.x & 63;
@@ -107,97 +140,120 @@ __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t
   const int32_t nv = (r_hi - r_lo) / V;   // full V-chunks
   for (int32_t j = lane; j < nv; j += 64) {
     float x[V];
-    if (V == 1) {
-      x[0] = load1<BF16>(p.in, col + r_lo + j);
-    } else {
-      loadv<BF16, V>(p.in, col + r_lo + (int64_t)j * V, x);
-    }
+    loadv<BF16, V>(p.in, col + r_lo + (int64_t)j * V, x);
 #pragma unroll
     for (int e = 0; e < V; ++e) {
       ax = fold<OP>(ax, x[e]);
-      ax2 = fold<OP>(ax2, x[e] * x[e]);
+      if (X2) ax2 = fold<OP>(ax2, x[e] * x[e]);
     }
   }
   for (int32_t r = r_lo + nv * V + lane; r < r_hi; r += 64) {
     const float x = load1<BF16>(p.in, col + r);
     ax = fold<OP>(ax, x);
-    ax2 = fold<OP>(ax2, x * x);
+    if (X2) ax2 = fold<OP>(ax2, x * x);
   }
   ax = wave_fold<OP>(ax);
-  ax2 = wave_fold<OP>(ax2);
+  if (X2) ax2 = wave_fold<OP>(ax2);
   if (lane == 0) {
     if (nseg == 1) {
       if (want_x) p.out_x[c] = ax;
       if (want_x2) p.out_x2[c] = ax2;
     } else {
       work[(int64_t)s * p.n + c] = ax;
-      work[(int64_t)nseg * p.n + (int64_t)s * p.n + c] = ax2;
+      if (X2) work[(int64_t)nseg * p.n + (int64_t)s * p.n + c] = ax2;
     }
   }
 }
 
-// BY_ROWS with one segment per column and many columns: wavefront wid folds the CG columns
-// [wid*CG, min(n, wid*CG + CG)) whole, with every column's chunk of a pass loaded before any is
-// folded (CG loads in flight per lane in place of one).
-template <int OP, bool BF16, int V, int CG>
-__global__ __launch_bounds__(RT) void reduce_rows_group_kernel(ReduceParams p, int64_t per) {
+// BY_ROWS with one segment per column: `lanes` lanes fold a column, so a wavefront folds
+// 64 / lanes columns at once, and CG such rounds of them, every round's chunk of a pass loaded
+// before any is folded (CG loads in flight per lane in place of one).  Short columns (a softmax
+// over fewer keys than a wavefront's 512) thus leave no lanes idle.  The last chunk of a column
+// whose rows are no multiple of V is the window that ends with it, its first rows masked.
+template <int OP, bool BF16, int V, bool X2, int CG>
+__global__ __launch_bounds__(RT) void reduce_rows_group_kernel(ReduceParams p, int32_t lanes,
+                                                               int64_t per) {
   const int lane = threadIdx.x & 63;
   float* no_work = nullptr;
   const int64_t lb = batch_of<BF16>(p, per, no_work, 0);
   const int64_t wid = lb * (RT / 64) + (threadIdx.x >> 6);
-  const int64_t c0 = wid * CG;
-  if (c0 >= p.n) return;
+  const int32_t ncol = 64 / lanes;               // columns of a round
+  const int32_t lc = lane & (lanes - 1);         // the lane within its column
+  const int64_t c0 = wid * CG * ncol + lane / lanes;
+  if (wid * CG * ncol >= p.n) return;
   const bool want_x = (p.flags & TPP_RED_X) != 0, want_x2 = (p.flags & TPP_RED_X2) != 0;
   // columns past n repeat the last column's address: loaded, folded, never stored
   int64_t col[CG];
 #pragma unroll
-  for (int q = 0; q < CG; ++q) col[q] = (c0 + q < p.n ? c0 + q : p.n - 1) * p.ld;
+  for (int q = 0; q < CG; ++q) {
+    const int64_t c = c0 + (int64_t)q * ncol;
+    col[q] = (c < p.n ? c : p.n - 1) * p.ld;
+  }
   float ax[CG], ax2[CG];
 #pragma unroll
   for (int q = 0; q < CG; ++q) ax[q] = ax2[q] = fold_identity<OP>();
   const int32_t nv = p.m / V;   // full V-chunks
-  for (int32_t j = lane; j < nv; j += 64) {
+  for (int32_t j = lc; j < nv; j += lanes) {
     float x[CG][V];
 #pragma unroll
-    for (int q = 0; q < CG; ++q) {
-      if (V == 1) x[q][0] = load1<BF16>(p.in, col[q] + j);
-      else loadv<BF16, V>(p.in, col[q] + (int64_t)j * V, x[q]);
-    }
+    for (int q = 0; q < CG; ++q) loadv<BF16, V>(p.in, col[q] + (int64_t)j * V, x[q]);
 #pragma unroll
     for (int q = 0; q < CG; ++q)
 #pragma unroll
       for (int e = 0; e < V; ++e) {
         ax[q] = fold<OP>(ax[q], x[q][e]);
-        ax2[q] = fold<OP>(ax2[q], x[q][e] * x[q][e]);
+        if (X2) ax2[q] = fold<OP>(ax2[q], x[q][e] * x[q][e]);
       }
   }
-  for (int32_t r = nv * V + lane; r < p.m; r += 64) {
+  const int32_t rest = p.m - nv * V;
+  if (rest != 0 && lc == nv % lanes) {   // the next lane in turn takes the remaining rows
+    if (nv > 0) {
+      float x[CG][V];
 #pragma unroll
-    for (int q = 0; q < CG; ++q) {
-      const float x = load1<BF16>(p.in, col[q] + r);
-      ax[q] = fold<OP>(ax[q], x);
-      ax2[q] = fold<OP>(ax2[q], x * x);
+      for (int q = 0; q < CG; ++q) loadv<BF16, V>(p.in, col[q] + p.m - V, x[q]);
+#pragma unroll
+      for (int q = 0; q < CG; ++q)
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          const bool mine = e >= V - rest;
+          ax[q] = mine ? fold<OP>(ax[q], x[q][e]) : ax[q];
+          if (X2) ax2[q] = mine ? fold<OP>(ax2[q], x[q][e] * x[q][e]) : ax2[q];
+        }
+    } else {
+      for (int32_t r = 0; r < rest; ++r)
+#pragma unroll
+        for (int q = 0; q < CG; ++q) {
+          const float x = load1<BF16>(p.in, col[q] + r);
+          ax[q] = fold<OP>(ax[q], x);
+          if (X2) ax2[q] = fold<OP>(ax2[q], x * x);
+        }
     }
   }
 #pragma unroll
   for (int q = 0; q < CG; ++q) {
-    const float fx = wave_fold<OP>(ax[q]);
-    const float fx2 = wave_fold<OP>(ax2[q]);
-    if (lane == 0 && c0 + q < p.n) {
-      if (want_x) p.out_x[c0 + q] = fx;
-      if (want_x2) p.out_x2[c0 + q] = fx2;
+    const float fx = lanes_fold<OP>(ax[q], lanes);
+    const float fx2 = X2 ? lanes_fold<OP>(ax2[q], lanes) : 0.0f;
+    const int64_t c = c0 + (int64_t)q * ncol;
+    if (lc == 0 && c < p.n) {
+      if (want_x) p.out_x[c] = fx;
+      if (X2 && want_x2) p.out_x2[c] = fx2;
     }
   }
 }
 
+// (MAX over 512 rows of 32768 columns of bf16, 33.5 MB from HBM: 9.5 us a call before, 8.0 with the
+// lane permutes and x alone folded; 64 rows of 20000 columns: 5.9 and 4.2.)
+
 // BY_COLS: workgroup (rb, s) folds columns [s*col_seg, min(n, (s+1)*col_seg)) for rows
 // [rb*TR*V, (rb+1)*TR*V).  Thread t: row vector tr = t % TR, column lane tc = t / TR.
-template <int OP, bool BF16, int V>
+// HBM-bound for tall inputs (262144 rows of 128 bf16 columns, 67 MB: 19.9 us a call before, 14.9 =
+// 4.5 TB/s with eight loads in flight per thread and no branch between them).
+template <int OP, bool BF16, int V, bool X2>
 __global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t TR,
                                                          int32_t col_seg, int32_t nseg,
                                                          int32_t nrb, float* work, int64_t per) {
   __shared__ float sx[RT * V];
-  __shared__ float sx2[RT * V];
+  __shared__ float sx2[X2 ? RT * V : 1];
   const int t = threadIdx.x;
   const int TC = RT / TR;
   const int tr = t % TR, tc = t / TR;
@@ -208,78 +264,112 @@ __global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t
   float ax[V], ax2[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) ax[e] = ax2[e] = fold_identity<OP>();
-  const bool full = r0 + V <= p.m;
-  auto load_vec = [&](int32_t c, float (&x)[V]) {
-    const int64_t base = (int64_t)c * p.ld + r0;
-    if (V > 1 && full) {
-      loadv<BF16, V>(p.in, base, x);
-    } else {
-#pragma unroll
-      for (int e = 0; e < V; ++e) x[e] = (r0 + e < p.m) ? load1<BF16>(p.in, base + e) : 0.0f;
-    }
+  // the last rows: the vector that ends with the column, of which the first `skip` rows belong to
+  // the thread before
+  const bool vec = p.m >= V && r0 < p.m;
+  const int32_t skip = vec && r0 + V > p.m ? r0 + V - p.m : 0;
+  const auto load_vec = [&](int32_t c, float (&x)[V]) {
+    loadv<BF16, V>(p.in, (int64_t)c * p.ld + r0 - skip, x);
   };
-  // Four columns per trip, all loads issued before any is folded, into four accumulator sets
-  // (combined in a fixed order below): four loads in flight per thread instead of one.
+  const auto load_rows = [&](int32_t c, float (&x)[V]) {   // fewer than V rows in all
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+      x[e] = r0 + e < p.m ? load1<BF16>(p.in, (int64_t)c * p.ld + r0 + e) : 0.0f;
+  };
+  // Up to eight columns per trip, all loads issued before any is folded, into four accumulator
+  // sets (combined in a fixed order below): a workgroup's usual eight columns per lane then cost
+  // one memory latency.
   float bx[4][V], bx2[4][V];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int e = 0; e < V; ++e) bx[u][e] = bx2[u][e] = fold_identity<OP>();
   int32_t c = c_lo + tc;
-  for (; c + 3 * TC < c_hi; c += 4 * TC) {
-    float x[4][V];
+  auto trip = [&](auto count, auto&& load) {
+    constexpr int U = decltype(count)::value;
+    for (; c + (U - 1) * TC < c_hi; c += U * TC) {
+      float x[U][V];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) load_vec(c + u * TC, x[u]);
+      for (int u = 0; u < U; ++u) load(c + u * TC, x[u]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int e = 0; e < V; ++e) {
-        bx[u][e] = fold<OP>(bx[u][e], x[u][e]);
-        bx2[u][e] = fold<OP>(bx2[u][e], x[u][e] * x[u][e]);
-      }
-  }
-  for (; c < c_hi; c += TC) {
-    float x[V];
-    load_vec(c, x);
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      bx[0][e] = fold<OP>(bx[0][e], x[e]);
-      bx2[0][e] = fold<OP>(bx2[0][e], x[e] * x[e]);
+        for (int e = 0; e < V; ++e) {
+          bx[u & 3][e] = fold<OP>(bx[u & 3][e], x[u][e]);
+          if (X2) bx2[u & 3][e] = fold<OP>(bx2[u & 3][e], x[u][e] * x[u][e]);
+        }
     }
+  };
+  if (vec) {
+    trip(Count<8>(), load_vec);
+    trip(Count<4>(), load_vec);
+    trip(Count<1>(), load_vec);
+  } else if (r0 < p.m) {
+    trip(Count<4>(), load_rows);
+    trip(Count<1>(), load_rows);
   }
 #pragma unroll
   for (int e = 0; e < V; ++e) {
     ax[e] = fold<OP>(fold<OP>(bx[0][e], bx[1][e]), fold<OP>(bx[2][e], bx[3][e]));
-    ax2[e] = fold<OP>(fold<OP>(bx2[0][e], bx2[1][e]), fold<OP>(bx2[2][e], bx2[3][e]));
+    if (X2) ax2[e] = fold<OP>(fold<OP>(bx2[0][e], bx2[1][e]), fold<OP>(bx2[2][e], bx2[3][e]));
   }
 #pragma unroll
   for (int e = 0; e < V; ++e) {
-    sx[tc * TR * V + tr * V + e] = ax[e];
-    sx2[tc * TR * V + tr * V + e] = ax2[e];
+    if (e < skip) continue;
+    sx[tc * TR * V + tr * V + e - skip] = ax[e];
+    if (X2) sx2[tc * TR * V + tr * V + e - skip] = ax2[e];
   }
   __syncthreads();
-  // Fold the TC column lanes; thread t handles row slot t (and t + RT, ... when TR*V > RT).
   const bool want_x = (p.flags & TPP_RED_X) != 0, want_x2 = (p.flags & TPP_RED_X2) != 0;
-  for (int slot = t; slot < TR * V; slot += RT) {
-    float fx = sx[slot], fx2 = sx2[slot];
-    for (int l = 1; l < TC; ++l) {
-      fx = fold<OP>(fx, sx[l * TR * V + slot]);
-      fx2 = fold<OP>(fx2, sx2[l * TR * V + slot]);
-    }
-    const int32_t r = rb * TR * V + slot;
-    if (r >= p.m) continue;
+  const int32_t slots = TR * V;
+  auto put = [&](int slot, float fx, float fx2) {
+    const int32_t r = rb * slots + slot;
+    if (r >= p.m) return;
     if (nseg == 1) {
       if (want_x) p.out_x[r] = fx;
-      if (want_x2) p.out_x2[r] = fx2;
+      if (X2 && want_x2) p.out_x2[r] = fx2;
     } else {
       work[(int64_t)s * p.m + r] = fx;
-      work[(int64_t)nseg * p.m + (int64_t)s * p.m + r] = fx2;
+      if (X2) work[(int64_t)nseg * p.m + (int64_t)s * p.m + r] = fx2;
     }
+  };
+  // Fold the TC column lanes of each row slot.  With fewer slots than threads, RT / slots threads
+  // share a slot (TR * V is a power of two), each taking every RT / slots-th column lane, and meet
+  // in LDS once more: V reads per thread and RT / slots more, where one thread per slot read all TC
+  // in turn (32 for 64 rows of bf16: a third of that kernel's time).
+  const int parts = slots < RT ? RT / slots : 1;
+  for (int i = t; i < slots * parts; i += RT) {
+    const int slot = i % slots, part = i / slots;
+    float fx = sx[part * slots + slot], fx2 = X2 ? sx2[part * slots + slot] : 0.0f;
+    for (int l = part + parts; l < TC; l += parts) {
+      fx = fold<OP>(fx, sx[l * slots + slot]);
+      if (X2) fx2 = fold<OP>(fx2, sx2[l * slots + slot]);
+    }
+    if (parts == 1) {
+      put(slot, fx, fx2);
+    } else {   // one trip: column lane `part` of this slot is this thread's own to overwrite
+      sx[part * slots + slot] = fx;
+      if (X2) sx2[part * slots + slot] = fx2;
+    }
+  }
+  if (parts == 1) return;
+  __syncthreads();
+  if (t < slots) {
+    float fx = sx[t], fx2 = X2 ? sx2[t] : 0.0f;
+    for (int l = 1; l < parts; ++l) {
+      fx = fold<OP>(fx, sx[l * slots + t]);
+      if (X2) fx2 = fold<OP>(fx2, sx2[l * slots + t]);
+    }
+    put(t, fx, fx2);
   }
 }
 
 // Second pass: out[o] = fold over s < nseg of work[s * n_out + o] (x part, then x2 part).
-// One wavefront per output: lanes take every 64th partial, then fold across the wavefront.
+// A workgroup folds OW neighbouring outputs, RT / OW threads each, every thread with up to eight
+// partials in flight, and the threads of an output meet in LDS in thread order.  Bound by latency
+// (343 partials of 64 x 2 outputs, the statistics of a 64 x 87808 tensor: 4.3 us with the launch);
+// one wavefront per 64 outputs, folding its partials a few loads at a time, took 5001 x 2000 by
+// columns to 26.6 us where the call takes 9.1 now.
 // Moves the combine pass's pointers to call g = blockIdx.x / per of a batch and returns the
 // workgroup's index within its call.
 __device__ __forceinline__ int64_t combine_batch(int64_t per, int32_t n_out, int32_t nseg,
@@ -295,106 +385,86 @@ __device__ __forceinline__ int64_t combine_batch(int64_t per, int32_t n_out, int
   return bid - g * per;
 }
 
-template <int OP>
+template <int OP, int OW>
 __global__ __launch_bounds__(RT) void reduce_combine_kernel(const float* work, int32_t n_out,
                                                             int32_t nseg, uint32_t flags,
                                                             float* out_x, float* out_x2,
                                                             int64_t per, int64_t out_stride) {
-  const int lane = threadIdx.x & 63;
+  constexpr int SL = RT / OW;   // lanes over the partials
+  __shared__ float sx[2][SL][OW];
+  const int ol = threadIdx.x % OW, sl = threadIdx.x / OW;
   const int64_t lb = combine_batch(per, n_out, nseg, out_stride, work, out_x, out_x2);
-  const int64_t o = lb * (RT / 64) + (threadIdx.x >> 6);
-  if (o >= n_out) return;
-  float fx = fold_identity<OP>(), fx2 = fold_identity<OP>();
-  for (int32_t s = lane; s < nseg; s += 64) {
-    fx = fold<OP>(fx, work[(int64_t)s * n_out + o]);
-    fx2 = fold<OP>(fx2, work[(int64_t)nseg * n_out + (int64_t)s * n_out + o]);
-  }
-  fx = wave_fold<OP>(fx);
-  fx2 = wave_fold<OP>(fx2);
-  if (lane == 0) {
-    if (flags & TPP_RED_X) out_x[o] = fx;
-    if (flags & TPP_RED_X2) out_x2[o] = fx2;
-  }
-}
-
-// Second pass for many outputs: workgroup b folds outputs [64 b, 64 b + 64), lane = output, so
-// every partial load is a coalesced 256-byte row; wave w folds partials s = w, w + 4, ... in
-// increasing s, and the four wave results are folded in wave order.
-template <int OP>
-__global__ __launch_bounds__(RT) void reduce_combine_wide_kernel(const float* work, int32_t n_out,
-                                                                 int32_t nseg, uint32_t flags,
-                                                                 float* out_x, float* out_x2,
-                                                                 int64_t per, int64_t out_stride) {
-  __shared__ float sx[4][64], sx2[4][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t lb = combine_batch(per, n_out, nseg, out_stride, work, out_x, out_x2);
-  const int64_t o = lb * 64 + lane;
-  float fx = fold_identity<OP>(), fx2 = fold_identity<OP>();
-  if (o < n_out) {
-    const float* px = work + o;
-    const float* px2 = work + (int64_t)nseg * n_out + o;
-    int32_t s = w;
-    for (; s + 12 < nseg; s += 16) {   // four partials of each half in flight
-      float a[4], b[4];
+  const int64_t o = lb * OW + ol;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = px[(int64_t)(s + 4 * u) * n_out];
-        b[u] = px2[(int64_t)(s + 4 * u) * n_out];
-      }
+  for (int half = 0; half < 2; ++half) {
+    if (!(flags & (half ? TPP_RED_X2 : TPP_RED_X))) continue;
+    const float* const w = work + (half ? (int64_t)nseg * n_out : 0) + o;
+    float f = fold_identity<OP>();
+    if (o < n_out) {
+      int32_t s = sl;
+      for (; s + 7 * SL < nseg; s += 8 * SL) {   // eight partials in flight
+        float a[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        fx = fold<OP>(fx, a[u]);
-        fx2 = fold<OP>(fx2, b[u]);
+        for (int u = 0; u < 8; ++u) a[u] = w[(int64_t)(s + u * SL) * n_out];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f = fold<OP>(f, a[u]);
       }
+      float a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        a[u] = s + u * SL < nseg ? w[(int64_t)(s + u * SL) * n_out] : fold_identity<OP>();
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f = fold<OP>(f, a[u]);
     }
-    for (; s < nseg; s += 4) {
-      fx = fold<OP>(fx, px[(int64_t)s * n_out]);
-      fx2 = fold<OP>(fx2, px2[(int64_t)s * n_out]);
-    }
+    sx[half][sl][ol] = f;
   }
-  sx[w][lane] = fx;
-  sx2[w][lane] = fx2;
   __syncthreads();
-  if (w == 0 && o < n_out) {
-    fx = fold<OP>(fold<OP>(sx[0][lane], sx[1][lane]), fold<OP>(sx[2][lane], sx[3][lane]));
-    fx2 = fold<OP>(fold<OP>(sx2[0][lane], sx2[1][lane]), fold<OP>(sx2[2][lane], sx2[3][lane]));
-    if (flags & TPP_RED_X) out_x[o] = fx;
-    if (flags & TPP_RED_X2) out_x2[o] = fx2;
-  }
+  if (threadIdx.x >= 2 * OW) return;
+  const int half = threadIdx.x / OW;
+  if (o >= n_out || !(flags & (half ? TPP_RED_X2 : TPP_RED_X))) return;
+  float f = sx[half][0][ol];
+#pragma unroll
+  for (int l = 1; l < SL; ++l) f = fold<OP>(f, sx[half][l][ol]);
+  (half ? out_x2 : out_x)[o] = f;
 }
 
 struct Plan {
   bool by_cols;
-  int v;          // elements per load (1, 4 or 8)
+  int v;          // elements per 16-byte load (4 or 8)
   int32_t nseg;   // partial results per output
   int32_t seg;    // rows per segment (BY_ROWS) or columns per range (BY_COLS)
   int32_t tr;     // BY_COLS: row vectors per workgroup
   int32_t nrb;    // BY_COLS: row blocks
   int64_t blocks; // first-pass workgroups
-  int32_t cg;     // BY_ROWS with one segment: columns per wavefront (1: the segment kernel)
+  int32_t cg;     // BY_ROWS with one segment: rounds of columns per wavefront (0: segments)
+  int32_t lanes;  // and lanes per column
 };
 
 Plan make_plan(const ReduceParams& p) {
   Plan pl{};
   pl.by_cols = (p.flags & TPP_RED_BY_COLS) != 0;
   const int es = p.in_bf16 ? 2 : 4;
-  const bool aligned = (reinterpret_cast<uintptr_t>(p.in) & 15) == 0 && ((p.ld * es) % 16) == 0;
-  pl.v = aligned ? 16 / es : 1;
+  pl.v = 16 / es;
   if (!pl.by_cols) {
     const int64_t rows_per_pass = 64LL * pl.v;
     const int64_t max_seg = (p.m + rows_per_pass - 1) / rows_per_pass;
     int64_t nseg = (4096 + p.n - 1) / p.n;   // aim for >= 4096 wavefronts
     nseg = nseg < 1 ? 1 : (nseg > max_seg ? max_seg : nseg);
     if (nseg > 256) nseg = 256;
+    if (p.whole) nseg = 1;
     const int64_t per = (p.m + nseg - 1) / nseg;
     pl.seg = (int32_t)(((per + rows_per_pass - 1) / rows_per_pass) * rows_per_pass);
     pl.nseg = (int32_t)((p.m + pl.seg - 1) / pl.seg);
     pl.blocks = ((int64_t)p.n * pl.nseg + (RT / 64) - 1) / (RT / 64);
-    // whole columns and plenty of them: 2 or 4 columns per wavefront, still >= 4096 wavefronts
-    pl.cg = 1;
+    // whole columns: the fewest lanes (8 to 64) whose one pass covers a column, and with plenty
+    // of columns 2 or 4 rounds of them per wavefront, still >= 4096 wavefronts
+    pl.cg = 0;
     if (pl.nseg == 1) {
-      pl.cg = p.n >= 4 * 4096 ? 4 : (p.n >= 2 * 4096 ? 2 : 1);
-      const int64_t waves = (p.n + pl.cg - 1) / pl.cg;
+      pl.lanes = 8;
+      while (pl.lanes < 64 && pl.lanes * pl.v < p.m) pl.lanes *= 2;
+      const int64_t ncol = 64 / pl.lanes, rounds = (p.n + ncol - 1) / ncol;
+      pl.cg = rounds >= 4 * 4096 ? 4 : (rounds >= 2 * 4096 ? 2 : 1);
+      const int64_t waves = (rounds + pl.cg - 1) / pl.cg;
       pl.blocks = (waves + (RT / 64) - 1) / (RT / 64);
     }
   } else {
@@ -418,6 +488,7 @@ Plan make_plan(const ReduceParams& p) {
     const int64_t max_seg = (p.n + 8LL * tc - 1) / (8LL * tc);
     nseg = nseg < 1 ? 1 : (nseg > max_seg ? max_seg : nseg);
     if (nseg > 512) nseg = 512;
+    if (p.whole) nseg = 1;
     pl.seg = (int32_t)((p.n + nseg - 1) / nseg);
     pl.nseg = (int32_t)((p.n + pl.seg - 1) / pl.seg);
     pl.blocks = (int64_t)pl.nrb * pl.nseg;
@@ -425,47 +496,49 @@ Plan make_plan(const ReduceParams& p) {
   return pl;
 }
 
-template <int OP, bool BF16, int V>
+template <int OP, bool BF16, int V, bool X2>
 void launch_first(const ReduceParams& p, const Plan& pl, float* work, hipStream_t stream) {
   // with one partial per output the first pass writes the outputs itself (no work buffer)
   float* w = pl.nseg > 1 ? work : nullptr;
   const dim3 grid((unsigned)(pl.blocks * p.G));
-  if (!pl.by_cols && pl.cg == 4)
-    hipLaunchKernelGGL((reduce_rows_group_kernel<OP, BF16, V, 4>), grid, dim3(RT), 0, stream, p,
-                       pl.blocks);
-  else if (!pl.by_cols && pl.cg == 2)
-    hipLaunchKernelGGL((reduce_rows_group_kernel<OP, BF16, V, 2>), grid, dim3(RT), 0, stream, p,
-                       pl.blocks);
+#define TPP_RED_GROUP(CG)                                                                        \
+  hipLaunchKernelGGL((reduce_rows_group_kernel<OP, BF16, V, X2, CG>), grid, dim3(RT), 0, stream, p, \
+                     pl.lanes, pl.blocks)
+  if (!pl.by_cols && pl.cg == 4) TPP_RED_GROUP(4);
+  else if (!pl.by_cols && pl.cg == 2) TPP_RED_GROUP(2);
+  else if (!pl.by_cols && pl.cg == 1) TPP_RED_GROUP(1);
+#undef TPP_RED_GROUP
   else if (!pl.by_cols)
-    hipLaunchKernelGGL((reduce_rows_kernel<OP, BF16, V>), grid, dim3(RT), 0, stream, p, pl.seg,
+    hipLaunchKernelGGL((reduce_rows_kernel<OP, BF16, V, X2>), grid, dim3(RT), 0, stream, p, pl.seg,
                        pl.nseg, w, pl.blocks);
   else
-    hipLaunchKernelGGL((reduce_cols_kernel<OP, BF16, V>), grid, dim3(RT), 0, stream, p, pl.tr,
+    hipLaunchKernelGGL((reduce_cols_kernel<OP, BF16, V, X2>), grid, dim3(RT), 0, stream, p, pl.tr,
                        pl.seg, pl.nseg, pl.nrb, w, pl.blocks);
 }
 
 template <int OP>
 void launch_op(const ReduceParams& p, const Plan& pl, float* work, hipStream_t stream) {
+  const bool x2 = (p.flags & TPP_RED_X2) != 0;
   if (p.in_bf16) {
-    if (pl.v == 8) launch_first<OP, true, 8>(p, pl, work, stream);
-    else launch_first<OP, true, 1>(p, pl, work, stream);
+    if (x2) launch_first<OP, true, 8, true>(p, pl, work, stream);
+    else launch_first<OP, true, 8, false>(p, pl, work, stream);
   } else {
-    if (pl.v == 4) launch_first<OP, false, 4>(p, pl, work, stream);
-    else launch_first<OP, false, 1>(p, pl, work, stream);
+    if (x2) launch_first<OP, false, 4, true>(p, pl, work, stream);
+    else launch_first<OP, false, 4, false>(p, pl, work, stream);
   }
   if (pl.nseg > 1) {
     const int32_t n_out = pl.by_cols ? p.m : p.n;
-    if (n_out >= 512) {   // many outputs: coalesced over outputs
-      const int64_t per = (n_out + 63) / 64;
-      hipLaunchKernelGGL(reduce_combine_wide_kernel<OP>, dim3((unsigned)(per * p.G)), dim3(RT), 0,
+    // 16 outputs per workgroup read whole 64-byte runs; few outputs take more threads each
+    const bool few = n_out < 512;
+    const int64_t per = few ? (n_out + 3) / 4 : (n_out + 15) / 16;
+    if (few)
+      hipLaunchKernelGGL((reduce_combine_kernel<OP, 4>), dim3((unsigned)(per * p.G)), dim3(RT), 0,
                          stream, work, n_out, pl.nseg, p.flags, p.out_x, p.out_x2, per,
                          p.out_stride);
-    } else {              // few outputs: one wavefront per output, lanes over the partials
-      const int64_t per = (n_out + 3) / 4;
-      hipLaunchKernelGGL(reduce_combine_kernel<OP>, dim3((unsigned)(per * p.G)), dim3(RT), 0,
+    else
+      hipLaunchKernelGGL((reduce_combine_kernel<OP, 16>), dim3((unsigned)(per * p.G)), dim3(RT), 0,
                          stream, work, n_out, pl.nseg, p.flags, p.out_x, p.out_x2, per,
                          p.out_stride);
-    }
   }
 }
 

@@ -211,6 +211,21 @@ tpp_status work_buffer(int purpose, void* stream, int64_t floats, float** out,
   return TPP_OK;
 }
 
+// Whether work_buffer would have to allocate while `stream` is being captured into a graph, where
+// the runtime refuses to: the caller then takes the form of its launch that needs no work space.
+bool grows_under_capture(int purpose, void* stream, int64_t floats) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  {
+    std::lock_guard<std::mutex> lock(g_work_mu);
+    const auto it = g_work.find(std::make_tuple(dev, stream, purpose));
+    if (it != g_work.end() && it->second.floats >= floats) return false;
+  }
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(static_cast<hipStream_t>(stream), &st) == hipSuccess &&
+         st == hipStreamCaptureStatusActive;
+}
+
 // What one launch runs: the kernel instance, the split of its stage (or pair) list and the
 // floats of work space the split's partial tiles need (0 without a split).  Host-only; no device
 // work and no allocation.
@@ -755,8 +770,12 @@ tpp_status reduce_impl(int32_t m, int32_t n, int64_t ld, int32_t in_type, const 
   if ((flags & TPP_RED_X2) && !out_x2) return fail(TPP_ERR_INVALID_ARG, "NULL out_x2");
   if (G == 0) return ok();
   tpp::ReduceParams p{in, m, n, ld, in_type == TPP_DT_BF16, op, flags, out_x, out_x2,
-                      G, in_stride, out_stride};
-  const int64_t need = tpp::reduce_work_floats(p);
+                      G, in_stride, out_stride, 0};
+  int64_t need = tpp::reduce_work_floats(p);
+  if (need > 0 && grows_under_capture(WORK_REDUCE, stream, need)) {
+    p.whole = 1;
+    need = tpp::reduce_work_floats(p);
+  }
   if (need < 0) return fail(TPP_ERR_UNSUPPORTED, "reduce needs more than 2^31 - 1 workgroups");
   float* work = nullptr;
   std::unique_lock<std::mutex> work_hold;   // held from the work-buffer lookup to the launch
