@@ -197,7 +197,7 @@ tpp_status tpp_brgemm_describe(tpp_brgemm_handle h, char* buf, size_t len);
  * correct use): TPP_FORCE_KERNEL=<instance id> takes that kernel instance wherever the shape,
  * alignment and layout allow it; TPP_SPLIT=<n> splits the reduction of every direct-to-LDS
  * launch of the stride or offset kind, and of every fp32 launch of fewer than 128 tiles, into n
- * chunks (capped by the stage or pair count); TPP_LOG prints each launch's instance and split to
+ * chunks (capped by the stage count); TPP_LOG prints each launch's instance and split to
  * stderr. */
 
 /* The kernels one tpp_brgemm_execute_batched call with these arguments would launch, named as

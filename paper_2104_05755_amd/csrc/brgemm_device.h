@@ -33,6 +33,7 @@ __device__ __forceinline__ void gst(void* p, T v) {
 // The same vectors at any element address (2-byte aligned bf16, 4-byte aligned fp32): gfx950 runs
 // in unaligned access mode, so these stay single 16-byte instructions.
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -214,7 +215,7 @@ __device__ __forceinline__ TileCoord decode_tile_at(const BrgemmParams& p, int b
   const int64_t t = xcd_tile(bid, p.total_tiles);
   const int64_t per_group = (int64_t)p.tiles_m * p.tiles_n;
   TileCoord tc;
-  tc.g = t / per_group;
+  tc.g = p.groups == 1 ? 0 : t / per_group;
   const int64_t tin = t - tc.g * per_group;
   // Bands of up to 8 tile rows: consecutive tiles walk down a band, then move one tile column
   // right, so the 32 tiles an XCD runs at once cover about 8 rows x 4 columns and share both

@@ -53,18 +53,36 @@ __device__ __forceinline__ void store_group(const BrgemmParams& p, const Instanc
   const float* bias = p.bias;
   const bool has_bias = (p.flags & TPP_EPI_BIAS) != 0;
   if (!GENERIC) {
-    // m % 4 == 0 and R0 % 4 == 0: the four rows R0..R0+3 are valid together and belong to one
-    // instance.
+    // Rows of an instance padded to whole groups (p.vm % 4 == 0) and R0 % 4 == 0: the four rows
+    // R0..R0+3 belong to one instance; its last group may have fewer than four rows.
     int64_t row_off, bias_idx;
+    int32_t nr;
     if (p.fused) {
       if (R0 >= p.vrows) return;
-      const int32_t gi = R0 / p.m, r = R0 - gi * p.m;
+      const int32_t gi = R0 / p.vm, r = R0 - gi * p.vm;
       row_off = (int64_t)gi * p.c_step_m + r;
       bias_idx = (int64_t)gi * p.bias_step_m + r;
+      nr = p.m - r;
     } else {
       if (R0 >= p.m) return;
       row_off = R0;
       bias_idx = in.bias + R0;
+      nr = p.m - R0;
+    }
+    if (nr < 4) {
+      for (int e = 0; e < nr; ++e) {
+        const int64_t ei = in.c + row_off + col_off + e;
+        float v1[1] = {v_in[e]};
+        if (p.beta != 0.0f)
+          v1[0] = p.beta * (p.c_bf16 ? bf16_bits_to_f32(static_cast<const uint16_t*>(p.c)[ei])
+                                     : static_cast<const float*>(p.c)[ei]) + v1[0];
+        if (has_bias) v1[0] += bias[bias_idx + e];
+        if (p.flags & EPI_AUX_MASK) epi_aux<1>(p, ei, v1);
+        const float o = activate(v1[0], p.flags);
+        if (p.c_bf16) static_cast<uint16_t*>(p.c)[ei] = f32_to_bf16_bits(o);
+        else static_cast<float*>(p.c)[ei] = o;
+      }
+      return;
     }
     const int64_t e0 = in.c + row_off + col_off;
     float v[4] = {v_in[0], v_in[1], v_in[2], v_in[3]};
@@ -617,214 +635,438 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 kernel: 64x64 tile, 4 waves of 32x32, v_mfma_f32_32x32x2f32, stages of 32 k.
-//   - VEC (stride kind; m, k, lda, ldb and the grid steps multiples of 4, every pair base 16-byte
-//     aligned and every block within 2 GB of its base, all checked on the host per launch): each
-//     thread moves two 16-byte vectors of A (4 rows of one k-column) and two of B (4 k of one
-//     column) per stage with buffer loads; otherwise element loads.  Out-of-range rows, columns
-//     and k read as zero (any shape).
-//   - Two LDS buffers (both panels k-major, rows padded against bank conflicts) fed from a ring
-//     of four register sets: the global loads of the next four stages are in flight while the
-//     MFMAs run on the current buffer; one barrier per stage.
-//   - Split launches (few tiles, long pair lists): workgroup b reduces chunk b % split of tile
-//     b / split's pair list into a partial tile of the work space, and brgemm_f32_split_finish
+// fp32 kernel: 64x64 tile, v_mfma_f32_32x32x2f32 (64 cycles each), stages of 64 k, two groups of four
+// waves (32x32 each): a group takes half of every stage's k and the groups' sums meet in LDS at the
+// end.  MFMA-bound on a full grid: a stage is 32 KB of loads per 2048 MFMA cycles of each SIMD, and
+// with two workgroups per CU four waves per SIMD cover each other's reads, stores and barriers.
+//   - Each thread moves two 16-byte vectors of A (4 rows of one k-column) and two of B (4 k of one
+//     column) per stage, at any alignment and for every batch kind (m and k of at least 4; fewer
+//     take brgemm_f32_kernel<false>, element loads).  The virtual rows of an instance are padded to
+//     whole 4-row chunks (p.vm); the last chunk of a block's rows or k-run loads the window of 4
+//     that ends with the block and is shifted into place in registers, k past the end as zeros.
+//   - Two register sets keep the loads of two stages in flight.  No branch surrounds a load (past
+//     the last stage the last one is read again, from the cache) and no step of the loop has a way
+//     out of its own, so that the compiler counts the loads in flight: otherwise it waits for the
+//     newest ones at every stage.
+//   - The sum over k runs in the order that LDS reads like: of each 8 k, lanes 0-31 take k 0-3 and
+//     lanes 32-63 k 4-7, one after the other, so a lane's four B values are one 16-byte read of its
+//     column and B is stored as it comes.  The fragments of 8 k are read during the MFMAs of the
+//     8 before them.
+// A 2048 x 1024 x 1024 layer (512 tiles): 50.2 us with one group, 32-k stages and a ring that the
+// waits emptied, 46.3 here (36 us per 1024 k, of which the MFMAs and their LDS reads are 29, and
+// 10 at its ends); 192 x 1600 x 510 with a padded row: 81.0 through element loads, 15.0 here.
+//   - Two LDS buffers, one barrier per stage.
+//   - Split launches (few tiles, long stage lists): workgroup b reduces chunk b % split of tile
+//     b / split's stages into a partial tile of the work space, and brgemm_f32_split_finish
 //     adds the chunks and applies the epilogue.  (Finishing in the same launch, by the last
 //     workgroup of a tile to arrive at a per-tile counter, measured 3.4 us slower per call on
 //     the single 64 x 64 instance: the returning device-scope atomic and one workgroup loading
 //     every chunk cost more than a second launch queued behind the first.)
 // ---------------------------------------------------------------------------------------------
-constexpr int F_BM = 64, F_BN = 64, F_BK = 32;
-constexpr int F_ROW = F_BM + 4;   // padded k-row of a panel (floats)
-constexpr int F_RING = 4;         // stages of global loads in flight (register sets)
-// Buffer descriptors of the vector path: F_RANGE bytes addressable from a pair base (the host
-// checks that every block fits), offsets at F_OUT_OF_RANGE and beyond read as zero.
-constexpr int32_t F_RANGE = 0x7fff0000;
-constexpr int32_t F_OUT_OF_RANGE = F_RANGE;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t f32_rsrc(const float* base) {
-  // pair bases are uniform over the workgroup: keep the descriptor in scalar registers
-  const uint64_t b = reinterpret_cast<uint64_t>(base);
-  const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
-                     ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32);
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, F_RANGE, 0x00020000);
+constexpr int F_BM = 64, F_BN = 64, F_BK = F32_STAGE_K;
+constexpr int F_NT = 512;            // threads: two groups of four waves
+constexpr int F_RING = 2;            // stages of global loads in flight (register sets)
+constexpr int F_BROW = F_BK + 4;     // padded column of the B panel (floats): conflict-free reads
+
+// v moved down by d elements (d >= 0), zeros past the end.
+__device__ __forceinline__ f32x4 shift_down(f32x4 v, int32_t d) {
+  if (d & 1) v = (f32x4){v.y, v.z, v.w, 0.0f};
+  if (d & 2) v = (f32x4){v.z, v.w, 0.0f, 0.0f};
+  if (d >= 4) v = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+  return v;
+}
+
+// Chunk of a split launch's stages, the tile and the instance of workgroup blockIdx.x.
+struct F32Work {
+  int64_t tile_bid;
+  int32_t split, chunk;
+  TileCoord tc;
+  Instance in;
+  int64_t s_lo, stages;   // first stage and how many (stage = pair * ksteps + k-step)
+  int32_t ksteps;
+};
+__device__ __forceinline__ F32Work f32_work(const BrgemmParams& p) {
+  F32Work w;
+  w.split = p.split > 1 ? p.split : 1;
+  w.tile_bid = (int64_t)blockIdx.x / w.split;
+  w.chunk = (int32_t)((int64_t)blockIdx.x - w.tile_bid * w.split);
+  w.tc = decode_tile_at(p, F_BM, F_BN, w.tile_bid);
+  w.in = instance_of(p, w.tc.g);
+  w.ksteps = (p.k + F_BK - 1) / F_BK;
+  const int64_t all = w.in.npairs * w.ksteps;
+  w.s_lo = all * w.chunk / w.split;
+  w.stages = all * (w.chunk + 1) / w.split - w.s_lo;
+  return w;
+}
+
+__device__ __forceinline__ void f32_finish_tile(const BrgemmParams& p, const F32Work& w, int wave,
+                                                int lane, const f32x16& acc) {
+  const int wm = wave & 1, wn = wave >> 1;
+  if (w.split > 1) {
+    // This chunk's partial tile, the accumulators in register order: thread t's group q at float
+    // ((wave * 4 + q) * 64 + lane) * 4 of the chunk's 64 x 64 block, so each wave-wide 16-byte
+    // store covers 1 KB of consecutive bytes.
+    float* const o = p.ws + ((size_t)w.tile_bid * w.split + w.chunk) * (F_BM * F_BN) +
+                     ((wave * 4) * 64 + lane) * 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      gst<f32x4>(o + q * 256,
+                 (f32x4){acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]});
+    return;
+  }
+  const int32_t C = w.tc.col0 + wn * 32 + (lane & 31);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int32_t R0 = w.tc.row0 + wm * 32 + q * 8 + (lane >> 5) * 4;
+    const float v[4] = {acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+    if (p.vm % 4 == 0)
+      store_group<false>(p, w.in, R0, C, v);
+    else
+      store_group<true>(p, w.in, R0, C, v);
+  }
+}
+
+// A thread's part of the fp32 kernel's output rows: one 4-row chunk (chunk t % 16 of the tile), its
+// bias loaded ahead of the main loop.
+struct F32Rows {
+  int64_t off;       // of the chunk's first row in C, from the instance base
+  int32_t nr;        // rows of the chunk that exist (0: none)
+  float bias[4];
+};
+__device__ __forceinline__ F32Rows f32_rows(const BrgemmParams& p, const F32Work& w, int chunk) {
+  F32Rows o;
+  const int32_t R = w.tc.row0 + chunk * 4;
+  const int32_t gi = p.fused ? R / p.vm : 0, r = R - gi * p.vm;
+  o.off = (p.fused ? (int64_t)gi * p.c_step_m : 0) + r;
+  o.nr = R >= p.vrows ? 0 : (p.m - r < 4 ? p.m - r : 4);
+  const int64_t bi = p.fused ? (int64_t)gi * p.bias_step_m + r : w.in.bias + r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    o.bias[e] = (p.flags & TPP_EPI_BIAS) && e < o.nr && w.split <= 1 ? gld<float>(p.bias + bi + e)
+                                                                      : 0.0f;
+  return o;
+}
+// The epilogue on four rows of virtual column C.
+__device__ __forceinline__ void f32_store4(const BrgemmParams& p, const F32Work& w,
+                                           const F32Rows& rows, int32_t C, f32x4 x) {
+  if (rows.nr == 0 || C >= (p.fused ? p.vcols : p.n)) return;
+  const int32_t gi = p.fused ? C / p.n : 0, c = C - gi * p.n;
+  const int64_t e0 = w.in.c + rows.off + (p.fused ? (int64_t)gi * p.c_step_n : 0) + c * p.ldc;
+  float v[4] = {x[0], x[1], x[2], x[3]};
+  if (rows.nr < 4) {
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      if (e >= rows.nr) break;
+      float u[1] = {v[e]};
+      if (p.beta != 0.0f)
+        u[0] = p.beta * (p.c_bf16 ? bf16_bits_to_f32(gld<uint16_t>(static_cast<uint16_t*>(p.c) + e0 + e))
+                                  : gld<float>(static_cast<float*>(p.c) + e0 + e)) + u[0];
+      u[0] += rows.bias[e];
+      if (p.flags & EPI_AUX_MASK) epi_aux<1>(p, e0 + e, u);
+      const float o = activate(u[0], p.flags);
+      if (p.c_bf16) gst<uint16_t>(static_cast<uint16_t*>(p.c) + e0 + e, f32_to_bf16_bits(o));
+      else gst<float>(static_cast<float*>(p.c) + e0 + e, o);
+    }
+    return;
+  }
+  if (p.c_bf16) {
+    uint16_t* const cp = static_cast<uint16_t*>(p.c) + e0;
+    if (p.beta != 0.0f) {
+      const u32x2 h = gld<u32x2_a2>(cp);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] = p.beta * bf16_bits_to_f32(h[e >> 1] >> (16 * (e & 1)) & 0xffffu) + v[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += rows.bias[e];
+    if (p.flags & EPI_AUX_MASK) epi_aux<4>(p, e0, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = activate(v[e], p.flags);
+    gst<u32x2_a2>(cp, (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])});
+  } else {
+    float* const cp = static_cast<float*>(p.c) + e0;
+    if (p.beta != 0.0f) {
+      const f32x4 h = gld<f32x4_a4>(cp);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = p.beta * h[e] + v[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += rows.bias[e];
+    if (p.flags & EPI_AUX_MASK) epi_aux<4>(p, e0, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = activate(v[e], p.flags);
+    gst<f32x4_a4>(cp, (f32x4){v[0], v[1], v[2], v[3]});
+  }
 }
 
 template <bool VEC>
-__global__ __launch_bounds__(NT) void brgemm_f32_kernel(BrgemmParams p) {
-  __shared__ __attribute__((aligned(16))) float As[2][F_BK * F_ROW];
-  __shared__ __attribute__((aligned(16))) float Bs[2][F_BK * F_ROW];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  // With a split, workgroup bid takes chunk bid % split of tile bid / split's pair list.
-  const int32_t split = p.split > 1 ? p.split : 1;
-  const int64_t tile_bid = (int64_t)blockIdx.x / split;
-  const int32_t chunk = (int32_t)((int64_t)blockIdx.x - tile_bid * split);
-  const TileCoord tc = decode_tile_at(p, F_BM, F_BN, tile_bid);
-  const Instance in = instance_of(p, tc.g);
-  const int64_t pair_lo = in.npairs * chunk / split;
-  const int64_t pair_hi = in.npairs * (chunk + 1) / split;
-  const int32_t ksteps = (p.k + F_BK - 1) / F_BK;
-  const int64_t stages = (pair_hi - pair_lo) * ksteps;
+__global__ __launch_bounds__(NT) void brgemm_f32_kernel(BrgemmParams p);
 
-  // Thread t moves A vectors q = t + 256 j (j < 2): k-column kq = q / 16, rows 4 (q % 16) .. +3;
-  // and B vectors q = t + 256 j: column q / 8, k 4 (q % 8) .. +3.
-  int64_t a_off[2][4], b_off[2];
-  bool a_ok[2][4], b_ok[2];
-  int a_k[2], a_r[2], b_c[2], b_k[2];
+template <>
+__global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams p) {
+  __shared__ __attribute__((aligned(16))) float As[2][F_BK * F_BM];     // [k][row]
+  __shared__ __attribute__((aligned(16))) float Bs[2][F_BN * F_BROW];   // [column][k]
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = (t >> 6) & 3, kgrp = t >> 8;   // wave of its group; the group's half of a stage
+  const int wm = wave & 1, wn = wave >> 1;
+  const F32Work w = f32_work(p);
+  const int64_t stages = w.stages;
+  const F32Rows rows = f32_rows(p, w, t & 15);
+
+  // Thread t moves A vectors q = t + 512 j (j < 2): k-column q / 16, rows 4 (q % 16) .. +3; and B
+  // vectors q = t + 512 j: column q / 16, k 4 (q % 16) .. +3.  Byte offsets from a stage's bases, in
+  // whole stages and in a block's last, partial one (_t).  Rows and columns outside C read the
+  // first ones: only outputs that are not stored see them.
+  const bool ragged = p.k % F_BK != 0 || p.vm != p.m;   // uniform
+  const int32_t ktail = p.k - (w.ksteps - 1) * F_BK;     // k of the last k-step
+  int64_t oa[2], ob[2], oa_t[2], ob_t[2];
+  int32_t sr[2], sk[2];       // shifts: rows of A, k of B in the partial stage
+  bool ka_ok[2];              // A's k-column exists in the partial stage
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int q = t + NT * j;
-    a_k[j] = q >> 4;
-    a_r[j] = (q & 15) * 4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      a_off[j][e] = 0;
-      a_ok[j][e] = row_in_a(p, tc.row0 + a_r[j] + e, a_off[j][e]);
+    const int q = t + F_NT * j;
+    const int ka = q >> 4, kb = (q & 15) * 4;
+    const int32_t R = w.tc.row0 + (q & 15) * 4;
+    const int32_t gi = p.fused ? R / p.vm : 0;
+    int32_t r = R - gi * p.vm;
+    int64_t base = p.fused ? gi * p.a_step_m : 0;
+    if (R >= p.vrows) {
+      r = 0;
+      base = 0;
     }
-    b_c[j] = q >> 3;
-    b_k[j] = (q & 7) * 4;
-    b_off[j] = 0;
-    b_ok[j] = col_in_b(p, tc.col0 + b_c[j], b_off[j]);
+    sr[j] = r + 4 > p.m ? r + 4 - p.m : 0;
+    base += r - sr[j];
+    ka_ok[j] = ka < ktail;
+    oa[j] = (base + (int64_t)ka * p.lda) * 4;
+    oa_t[j] = (base + (int64_t)(ka_ok[j] ? ka : 0) * p.lda) * 4;
+    int64_t col = 0;
+    if (!col_in_b(p, w.tc.col0 + (q >> 4), col)) col = 0;
+    // the window of 4 k ends with the block (k >= 4, so it may begin in the k-step before)
+    const int32_t kw = kb + 4 > ktail ? ktail - 4 : kb;
+    sk[j] = kb - kw;
+    ob[j] = (col + kb) * 4;
+    ob_t[j] = (col + kw) * 4;
   }
 
-  f32x16 acc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  // Ring of F_RING register sets: stage s is loaded into set s % F_RING about F_RING stages
-  // before it is written to LDS, so that many stages' global loads are in flight behind the MFMAs
-  // (a stage's MFMAs take far less time than a load's round trip to memory).
+  // Stages are loaded strictly in order by a cursor: pair i (bases pa, pb), k offset kk.  Offset
+  // and pointer lists: lane l holds the entries of pair 64 (i / 64) + l, taken with readlane.
+  int64_t ld_s = 0, ld_i = stages > 0 ? w.s_lo / w.ksteps : 0;
+  int32_t ld_kk = stages > 0 ? (int32_t)(w.s_lo - ld_i * w.ksteps) * F_BK : 0;
+  const char* pa = nullptr;
+  const char* pb = nullptr;
+  uint64_t list_a = 0, list_b = 0;
+  const auto uni = [](uint64_t v, int src) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), src) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, src);
+  };
+  const auto fill_list = [&]() {
+    const int64_t i = (ld_i & ~(int64_t)63) + lane;
+    if (i >= w.in.npairs) return;
+    const float *a, *b;
+    pair_bases<float>(p, w.in, i, a, b);
+    list_a = reinterpret_cast<uint64_t>(a);
+    list_b = reinterpret_cast<uint64_t>(b);
+    // the entries are waited for here, on this path alone, and not at every readlane
+    asm volatile("" : "+v"(list_a), "+v"(list_b));
+  };
+  const auto from_list = [&]() {
+    pa = reinterpret_cast<const char*>(uni(list_a, (int)(ld_i & 63)));
+    pb = reinterpret_cast<const char*>(uni(list_b, (int)(ld_i & 63)));
+  };
+  if (stages > 0) {
+    fill_list();
+    from_list();
+  }
   f32x4 ra[F_RING][2], rb[F_RING][2];
-  // Stages are loaded strictly in order, so a cursor walks them: pair ld_i (pair bases ld_pa /
-  // ld_pb), k offset ld_kk; no division per stage.
-  int64_t ld_s = 0, ld_i = pair_lo;
-  int32_t ld_kk = 0;
-  const float* ld_pa = nullptr;
-  const float* ld_pb = nullptr;
-  if (stages > 0) pair_bases<float>(p, in, ld_i, ld_pa, ld_pb);
-  auto advance = [&]() {
-    ++ld_s;
+  bool part[F_RING];          // the set holds a block's partial stage
+  auto load = [&](auto slot) {
+    constexpr int R = decltype(slot)::value;
+    const bool tail = ragged && ld_kk + F_BK > p.k;
+    part[R] = tail;
+    const char* const a = pa + (int64_t)ld_kk * p.lda * 4;
+    const char* const b = pb + (int64_t)ld_kk * 4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      ra[R][j] = gld<f32x4_a4>(a + (tail ? oa_t[j] : oa[j]));
+      rb[R][j] = gld<f32x4_a4>(b + (tail ? ob_t[j] : ob[j]));
+    }
+    if (++ld_s >= stages) return;   // stay on the last stage
     ld_kk += F_BK;
     if (ld_kk >= p.k) {
       ld_kk = 0;
       ++ld_i;
-      if constexpr (VEC) {   // stride kind
-        ld_pa += p.stride_a;
-        ld_pb += p.stride_b;
-      } else if (ld_s < stages) {
-        pair_bases<float>(p, in, ld_i, ld_pa, ld_pb);
+      if (p.kind == TPP_BR_STRIDE) {
+        pa += p.stride_a * 4;
+        pb += p.stride_b * 4;
+      } else {
+        if ((ld_i & 63) == 0) fill_list();
+        from_list();
       }
     }
-  };
-  auto load = [&](auto slot) {
-    constexpr int R = decltype(slot)::value;
-    if constexpr (VEC) {
-      // Exactly four 16-byte buffer loads per call, no branches, so the compiler can count the
-      // loads in flight: a vector outside the block (rows past the tile group, k past the end;
-      // whole vectors, since m and k are multiples of 4) or of a stage past the chunk's last gets
-      // an offset past the descriptor's range and reads as zero.
-      const bool live = ld_s < stages;
-      const __amdgpu_buffer_rsrc_t sa = f32_rsrc(ld_pa), sb = f32_rsrc(ld_pb);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int32_t ka = ld_kk + a_k[j];
-        const int32_t oa = live && a_ok[j][0] && ka < p.k
-                               ? (int32_t)((a_off[j][0] + (int64_t)ka * p.lda) * 4)
-                               : F_OUT_OF_RANGE;
-        ra[R][j] = __builtin_amdgcn_raw_buffer_load_b128(sa, oa, 0, 0);
-        const int32_t kb = ld_kk + b_k[j];
-        const int32_t ob =
-            live && b_ok[j] && kb < p.k ? (int32_t)((b_off[j] + kb) * 4) : F_OUT_OF_RANGE;
-        rb[R][j] = __builtin_amdgcn_raw_buffer_load_b128(sb, ob, 0, 0);
-      }
-    } else {
-      const float* const pa = ld_pa;
-      const float* const pb = ld_pb;
-      const int32_t kk = ld_kk;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int32_t ka = kk + a_k[j];
-        const int32_t kb = kk + b_k[j];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          ra[R][j][e] = (a_ok[j][e] && ka < p.k)
-                            ? gld<float>(pa + a_off[j][e] + (int64_t)ka * p.lda)
-                            : 0.0f;
-          rb[R][j][e] = (b_ok[j] && kb + e < p.k) ? gld<float>(pb + b_off[j] + kb + e) : 0.0f;
-        }
-      }
-    }
-    advance();
   };
   auto store = [&](int buf, auto slot) {
     constexpr int R = decltype(slot)::value;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      *reinterpret_cast<f32x4*>(&As[buf][a_k[j] * F_ROW + a_r[j]]) = ra[R][j];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Bs[buf][(b_k[j] + e) * F_ROW + b_c[j]] = rb[R][j][e];
+      const int q = t + F_NT * j;
+      f32x4 a = ra[R][j], b = rb[R][j];
+      if (ragged) {
+        a = shift_down(a, sr[j]);
+        if (part[R]) {
+          if (!ka_ok[j]) a = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+          b = shift_down(b, sk[j]);
+        }
+      }
+      *reinterpret_cast<f32x4*>(&As[buf][(q >> 4) * F_BM + (q & 15) * 4]) = a;
+      *reinterpret_cast<f32x4*>(&Bs[buf][(q >> 4) * F_BROW + (q & 15) * 4]) = b;
     }
   };
-  // Prologue: stages 0 .. F_RING - 1 in flight, stage 0 in LDS buffer 0, stage F_RING loading.
-  // (The vector path always issues its loads; past the last stage they read zeros.)
+
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  struct Frag {
+    float a[4];
+    f32x4 b;
+  };
+  const int half = lane >> 5;
+  const int k_at = kgrp * (F_BK / 2) + half * 4;
+  const int a_at = k_at * F_BM + wm * 32 + (lane & 31);
+  const int b_at = (wn * 32 + (lane & 31)) * F_BROW + k_at;
+  auto frag = [&](int buf, int g) {   // the 8 k of step g of the wave's half stage
+    Frag f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f.a[e] = As[buf][a_at + (8 * g + e) * F_BM];
+    f.b = *reinterpret_cast<const f32x4*>(&Bs[buf][b_at + 8 * g]);
+    return f;
+  };
+  auto mfmas = [&](const Frag& f) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[e], f.b[e], acc, 0, 0, 0);
+  };
+
   if (stages > 0) {
     load(IntC<0>());
-    if (VEC || 1 < stages) load(IntC<1>());
-    if (VEC || 2 < stages) load(IntC<2>());
-    if (VEC || 3 < stages) load(IntC<3>());
+    load(IntC<1>());
     store(0, IntC<0>());
-    if (VEC || F_RING < stages) load(IntC<0>());
+    load(IntC<0>());
     lds_barrier();
-  }
-  // Iteration s: MFMAs on LDS buffer s & 1 (stage s); stage s + 1 from its register set into the
-  // other buffer (free: every wave passed the barrier after stage s - 1's MFMAs); that set then
-  // takes stage s + 1 + F_RING.  One barrier per stage.  The slot index (s + 1) % F_RING and the
-  // buffer parity are compile-time constants of the unrolled steps.
-  int64_t s = 0;
-  auto step = [&](auto nslot) {
-    constexpr int NS = decltype(nslot)::value;   // (s + 1) % F_RING
-    const int buf = (int)(s & 1);
-#pragma unroll
-    for (int kq = 0; kq < F_BK / 2; ++kq) {
-      const int kr = kq * 2 + (lane >> 5);
-      const float a = As[buf][kr * F_ROW + wm * 32 + (lane & 31)];
-      const float b = Bs[buf][kr * F_ROW + wn * 32 + (lane & 31)];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+    // Stage s: MFMAs on LDS buffer s & 1; stage s + 1 goes from its register set into the other
+    // buffer (free: every wave passed the barrier after stage s - 1's MFMAs) and that set takes
+    // stage s + 1 + F_RING.
+    auto step = [&](auto nslot) {
+      constexpr int NS = decltype(nslot)::value;   // (s + 1) % F_RING
+      constexpr int BUF = NS ^ 1;                  // s & 1
+      Frag f0 = frag(BUF, 0);
+      Frag f1 = frag(BUF, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(f0);
+      f0 = frag(BUF, 2);
+      store(BUF ^ 1, IntC<NS>());
+      load(IntC<NS>());
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(f1);
+      f1 = frag(BUF, 3);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(f0);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(f1);
+      lds_barrier();   // LDS traffic only: the ring's global loads stay in flight
+    };
+    // whole turns of the ring without a branch between the steps (a way out of the loop after each
+    // step would again make the compiler wait for the newest loads), then the rest
+    for (int64_t turns = stages / F_RING; turns > 0; --turns) {
+      step(IntC<1>());
+      step(IntC<0>());
     }
-    if (s + 1 < stages) store(buf ^ 1, IntC<NS>());
-    if (VEC || s + 1 + F_RING < stages) load(IntC<NS>());
-    lds_barrier();   // LDS traffic only: the ring's global loads stay in flight
-    ++s;
-  };
-  while (s < stages) {
-    step(IntC<1>());
-    if (s >= stages) break;
-    step(IntC<2>());
-    if (s >= stages) break;
-    step(IntC<3>());
-    if (s >= stages) break;
-    step(IntC<0>());
+    if (stages % F_RING != 0) step(IntC<1>());
   }
-
-  if (split > 1) {
-    // This chunk's partial tile, the accumulators in register order: thread t's group q at float
-    // ((wave * 4 + q) * 64 + lane) * 4 of the chunk's 64 x 64 block, so each wave-wide 16-byte
-    // store covers 1 KB of consecutive bytes.
-    float* const w = p.ws + ((size_t)tile_bid * split + chunk) * (F_BM * F_BN) +
-                     ((wave * 4) * 64 + lane) * 4;
+  // The second group's sums join the first's (every wave has passed the last stage's barrier), as
+  // a 64 x 64 tile in LDS, column by column.
+  constexpr int TROW = F_BM + 4;
+  static_assert(sizeof(As) >= F_BN * TROW * sizeof(float), "the tile fits the A panels");
+  float* const tile = &As[0][0];
+  float* const mine = tile + (wn * 32 + (lane & 31)) * TROW + wm * 32 + half * 4;
+  if (kgrp == 1) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      gst<f32x4>(w + q * 256,
-                 (f32x4){acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]});
+      *reinterpret_cast<f32x4*>(mine + 8 * q) =
+          (f32x4){acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+  }
+  __syncthreads();
+  if (kgrp == 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 o = *reinterpret_cast<const f32x4*>(mine + 8 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[4 * q + e] += o[e];
+        o[e] = acc[4 * q + e];
+      }
+      if (w.split <= 1) *reinterpret_cast<f32x4*>(mine + 8 * q) = o;
+    }
+  }
+  if (w.split > 1) {
+    if (kgrp == 0) f32_finish_tile(p, w, wave, lane, acc);
     return;
   }
-  // Four consecutive rows per group: with m a multiple of 4 (the vector instance) they are valid
-  // together and lie in one instance, and the group is one 16-byte store when aligned.
-  const int32_t C = tc.col0 + wn * 32 + (lane & 31);
+  __syncthreads();
+  // 16 threads store a column's 64 rows: whole lines.  (Stored from the accumulators, 16 bytes per
+  // column and thread with the bias loaded group by group behind the stores, the epilogue took
+  // about 5 us.)
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int32_t R0 = tc.row0 + wm * 32 + q * 8 + (lane >> 5) * 4;
-    const float v[4] = {acc[q * 4 + 0], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
-    store_group<!VEC>(p, in, R0, C, v);
+  for (int j = 0; j < F_BN * 16 / F_NT; ++j) {
+    const int col = (t >> 4) + j * (F_NT / 16);
+    f32_store4(p, w, rows, w.tc.col0 + col,
+               *reinterpret_cast<const f32x4*>(tile + col * TROW + (t & 15) * 4));
   }
+}
+
+// m or k below 4: half a stage of element loads at a time, every row, column and k checked.
+template <>
+__global__ __launch_bounds__(NT) void brgemm_f32_kernel<false>(BrgemmParams p) {
+  constexpr int ROW = F_BM + 4, HK = F_BK / 2;
+  __shared__ __attribute__((aligned(16))) float As[HK * ROW];
+  __shared__ __attribute__((aligned(16))) float Bs[HK * ROW];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const F32Work w = f32_work(p);
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  // thread t: A row t % 64 and B column t % 64, k t / 64 + 4 e of each stage
+  const int rc = t & 63, k0 = t >> 6;
+  int64_t a_off = 0, b_off = 0;
+  const bool a_ok = row_in_a(p, w.tc.row0 + rc, a_off), b_ok = col_in_b(p, w.tc.col0 + rc, b_off);
+  for (int64_t h = 2 * w.s_lo; h < 2 * (w.s_lo + w.stages); ++h) {
+    const int64_t i = (h / 2) / w.ksteps;
+    const int32_t kk = (int32_t)(h / 2 - i * w.ksteps) * F_BK + (int32_t)(h & 1) * HK;
+    if (kk >= p.k) continue;   // uniform
+    const float *pa, *pb;
+    pair_bases<float>(p, w.in, i, pa, pb);
+    float a[8], b[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int32_t k = kk + k0 + 4 * e;
+      a[e] = a_ok && k < p.k ? gld<float>(pa + a_off + (int64_t)k * p.lda) : 0.0f;
+      b[e] = b_ok && k < p.k ? gld<float>(pb + b_off + k) : 0.0f;
+    }
+    __syncthreads();   // the stage before has been read
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      As[(k0 + 4 * e) * ROW + rc] = a[e];
+      Bs[(k0 + 4 * e) * ROW + rc] = b[e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kq = 0; kq < HK / 2; ++kq) {
+      const int kr = kq * 2 + (lane >> 5);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kr * ROW + wm * 32 + (lane & 31)],
+                                                 Bs[kr * ROW + wn * 32 + (lane & 31)], acc, 0, 0, 0);
+    }
+  }
+  f32_finish_tile(p, w, wave, lane, acc);
 }
 
 // Finishing step of a split fp32 launch: four workgroups per tile, thread f of a tile's 1024
@@ -853,7 +1095,7 @@ __global__ __launch_bounds__(NT) void brgemm_f32_split_finish(BrgemmParams p) {
   const int32_t C = tc.col0 + wn * 32 + (lane & 31);
   const int32_t R0 = tc.row0 + wm * 32 + q * 8 + (lane >> 5) * 4;
   const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-  if (p.m % 4 == 0)
+  if (p.vm % 4 == 0)
     store_group<false>(p, in, R0, C, v);
   else
     store_group<true>(p, in, R0, C, v);
@@ -1026,19 +1268,8 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
       hipLaunchKernelGGL((brgemm_bf16_kernel<64, 64, 2, 2, true>), grid, block, 0, stream, p);
       break;
     default: {
-      // 16-byte buffer loads when every k-column of A and every k-run of B splits into whole
-      // aligned vectors (stride kind: all pair bases follow from the bases and the steps) and every
-      // block lies within the descriptor's range of its pair base
-      const auto fits = [](int64_t last) { return last >= 0 && (last + 4) * 4 <= F_RANGE; };
-      const int64_t a_last = (p.fused ? (p.gm - 1) * p.a_step_m : 0) + p.m - 4 +
-                             (int64_t)(p.k - 1) * p.lda;
-      const int64_t b_last = (p.fused ? (p.gn - 1) * p.b_step_n : 0) +
-                             (int64_t)(p.n - 1) * p.ldb + p.k - 4;
-      const bool vec = p.kind == TPP_BR_STRIDE && p.aligned && p.m % 4 == 0 && p.k % 4 == 0 &&
-                       p.lda % 4 == 0 && p.ldb % 4 == 0 &&
-                       (!p.fused || (p.a_step_m % 4 == 0 && p.b_step_n % 4 == 0 &&
-                                     p.a_step_m >= 0 && p.b_step_n >= 0)) &&
-                       fits(a_last) && fits(b_last);
+      // windows of four rows and four k inside every block (plan_launch pads p.vm to match)
+      const bool vec = f32_vec(p);
       if (name_out) {
         *name_out = vec ? "brgemm_f32_kernel<true>" : "brgemm_f32_kernel<false>";
         if (p.split > 1) *name_out += " + brgemm_f32_split_finish";
@@ -1046,7 +1277,7 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
       }
       const dim3 g = p.split > 1 ? dim3((unsigned)(p.total_tiles * p.split)) : grid;
       if (vec)
-        hipLaunchKernelGGL(brgemm_f32_kernel<true>, g, block, 0, stream, p);
+        hipLaunchKernelGGL(brgemm_f32_kernel<true>, g, dim3(F_NT), 0, stream, p);
       else
         hipLaunchKernelGGL(brgemm_f32_kernel<false>, g, block, 0, stream, p);
       if (p.split > 1)
@@ -1056,6 +1287,11 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
     }
   }
   return name_out ? hipSuccess : hipGetLastError();
+}
+
+bool f32_vec(const BrgemmParams& p) {
+  const int64_t vm = (p.m + 3) / 4 * 4;
+  return p.m >= 4 && p.k >= 4 && vm * (p.fused ? p.gm : 1) < (1LL << 31) - 512;
 }
 
 int64_t f32_split_ws_floats(int32_t split, int64_t total_tiles) {

@@ -47,8 +47,8 @@ struct BrgemmParams {
   const int64_t* b_off;
   const int64_t* c_off;
   const int64_t* bias_off;
-  // Ragged instances of the 16-byte-load kernel (ragged = 1: m or k is no multiple of 8): the
-  // virtual rows of an instance, m padded to whole 8-row chunks (p.m otherwise); vrows counts them.
+  // Virtual rows of an instance, which vrows counts: m, padded to whole row chunks of 8 (ragged = 1,
+  // the bf16 16-byte-load kernel where m or k is no multiple of 8) or of 4 (the fp32 one).
   int32_t ragged, vm;
   // Tiling, filled by the launcher.
   int32_t vrows, vcols;      // virtual C extent of one tile group
@@ -77,7 +77,7 @@ enum KernelId : int32_t {
   K_BF16_128x128 = 1,   // 4 waves, 64x64 per wave, 16-byte loads (two workgroups per CU)
   K_BF16_64x64 = 2,     // 4 waves, 32x32 per wave, 16-byte loads
   K_BF16_GENERIC = 3,   // 64x64, element loads with full bounds checks (m or k below 8)
-  K_F32_GENERIC = 4,    // 64x64 fp32 MFMA, element loads with full bounds checks
+  K_F32_GENERIC = 4,    // 64x64 fp32 MFMA
   K_BF16_DL_256x256 = 5,  // direct global->LDS staging, 8 waves (k a multiple of 32)
   K_BF16_DL_128x128 = 6,  // direct global->LDS staging, 4 waves
   K_BF16_DL_64x64 = 7,    // direct global->LDS staging, 4 waves
@@ -90,6 +90,9 @@ enum KernelId : int32_t {
 
 const char* kernel_name(int32_t id);
 int kernel_tile_m(int32_t id);   // tile rows of kernel instance id
+constexpr int F32_STAGE_K = 64;   // k of one stage of the fp32 kernel
+// Whether the fp32 launch p takes the 16-byte-load kernel (m, k, fused, gm filled).
+bool f32_vec(const BrgemmParams& p);
 // fp32 workspace floats a split launch of the fp32 kernel needs (split x tiles x 64 x 64).
 int64_t f32_split_ws_floats(int32_t split, int64_t total_tiles);
 int kernel_tile_n(int32_t id);   // tile columns

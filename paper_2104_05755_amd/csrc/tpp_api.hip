@@ -258,19 +258,22 @@ tpp_status plan_launch(const tpp_brgemm_kernel_s* h, tpp::BrgemmParams& p, Launc
   const bool reg_staged = id == tpp::K_BF16_256x256 || id == tpp::K_BF16_128x128 ||
                           id == tpp::K_BF16_64x64;
   p.ragged = reg_staged && (p.m % 8 != 0 || p.k % 8 != 0);
-  p.vm = p.ragged ? (int32_t)tpp::padded_rows(p.m) : p.m;
+  p.vm = p.ragged ? (int32_t)tpp::padded_rows(p.m)
+         : id == tpp::K_F32_GENERIC && tpp::f32_vec(p) ? (p.m + 3) / 4 * 4 : p.m;
   p.vrows = p.fused ? (int32_t)(p.gm * p.vm) : p.vm;
   const int bm = tpp::kernel_tile_m(id), bn = tpp::kernel_tile_n(id);
-  if (id == tpp::K_F32_GENERIC && p.kind != TPP_BR_ADDRESS && p.count >= 2 &&
-      !(p.flags & tpp::EPI_AUX_MASK)) {
+  // pairs of every instance, where the host knows them (a list of lists is on the device)
+  const int64_t pairs = p.kind == TPP_BR_ADDRESS && p.begin ? 0 : p.count;
+  if (id == tpp::K_F32_GENERIC && !(p.flags & tpp::EPI_AUX_MASK)) {
     // A grid of few 64 x 64 tiles leaves most of the GPU idle while each workgroup walks the
-    // whole pair list: split the list into chunks reduced by separate workgroups (about 256 in
+    // whole stage list: split the list into chunks reduced by separate workgroups (about 256 in
     // all) and sum the chunks in a finishing kernel.
     const int64_t tiles = p.groups * ((p.vrows + 63) / 64) * ((p.vcols + 63) / 64);
-    if (tiles < 128) {
+    const int64_t stages = pairs * ((h->desc.k + tpp::F32_STAGE_K - 1) / tpp::F32_STAGE_K);
+    if (tiles < 128 && stages >= 4) {
       int64_t split = 256 / tiles;
       if (const char* env = std::getenv("TPP_SPLIT")) split = std::atoi(env);   // override
-      if (split > p.count) split = p.count;
+      if (split > stages) split = stages;
       if (split > 1) {
         lp.split = (int32_t)split;
         lp.ws_floats = tpp::f32_split_ws_floats(lp.split, tiles);
@@ -315,6 +318,8 @@ tpp_status launch(const tpp_brgemm_kernel_s* h, tpp::BrgemmParams& p, void* stre
                   const FixedWorkspace* fixed = nullptr) {
   LaunchPlan lp;
   if (tpp_status s = plan_launch(h, p, lp)) return s;
+  if (lp.split > 1 && !fixed && grows_under_capture(WORK_SPLIT, stream, lp.ws_floats))
+    lp.split = 1;
   p.split = lp.split;
   p.ws = nullptr;
   std::unique_lock<std::mutex> work_hold;   // held from a work-buffer lookup to the launch

@@ -1,4 +1,4 @@
-"""GPU parity, bit-exact: bf16 blocks whose m or k is no multiple of 8, on small-integer data
+"""GPU parity, bit-exact: bf16 blocks whose m or k is no multiple of 8 and fp32 blocks of any size, on small-integer data
 (every product and partial sum an integer below 2^24, so any summation order gives the same
 fp32 value and the same rounding).  The whole C buffer is compared, so a row window that passed its
 block, or a padded row stored, shows."""
@@ -22,17 +22,18 @@ SHAPES = [(7, 9, 13), (9, 7, 5), (8, 1, 9), (9, 3, 8), (15, 65, 63), (63, 5, 65)
           (71, 130, 127), (100, 33, 129), (129, 131, 77), (257, 260, 70)]
 
 
-def grid_case(m, n, k, count, kind, c_type, beta, flags, gm, gn, pad, seed):
+def grid_case(m, n, k, count, kind, c_type, beta, flags, gm, gn, pad, seed, ab_type="bf16"):
     """gm x gn instances over padded blocks, all operands small integers."""
     rng = np.random.default_rng(seed)
     lda, ldb, ldc = m + pad, k + pad, m + pad
     ab, bb, cb = lda * k, ldb * n, ldc * n
     ints = lambda size, r: rng.integers(-r, r + 1, size=size).astype(np.float32)
     c = ints(gm * gn * cb, 8)
-    arrays = dict(a=wk.bf16_bits(ints(gm * count * ab, 3)), b=wk.bf16_bits(ints(gn * count * bb, 3)),
+    conv = wk.bf16_bits if ab_type == "bf16" else lambda v: v
+    arrays = dict(a=conv(ints(gm * count * ab, 3)), b=conv(ints(gn * count * bb, 3)),
                   c=c if c_type == "f32" else wk.bf16_bits(c), bias=ints(gm * m, 8))
     assert count * k * 9 + 16 < 1 << 24
-    call = wk.Call(m, n, k, lda, ldb, ldc, "bf16", c_type, beta, kind, flags=set(flags), G=gm * gn,
+    call = wk.Call(m, n, k, lda, ldb, ldc, ab_type, c_type, beta, kind, flags=set(flags), G=gm * gn,
                    grid=dict(gm=gm, gn=gn, a_step_m=count * ab, b_step_n=count * bb, c_step_m=cb,
                              c_step_n=gm * cb, bias_step_m=m),
                    count=count, a="a", b="b", c="c", bias="bias" if "bias" in flags else None)
@@ -98,3 +99,56 @@ def test_ragged_aux_steps_match_elementwise():
     got2, _ = run_gpu(wl2)
     want = np.where(wk.bf16_values(z) > 0, v, 0).astype(np.uint16)
     assert_bits_equal(got2["c"][stored], want[stored], "relu_inv")
+
+
+# fp32: windows of 4 rows and 4 k, 64-k stages shared by two groups of waves, split stage lists
+F32_SHAPES = [(3, 9, 5), (4, 4, 4), (5, 1, 7), (7, 65, 63), (63, 5, 65), (65, 64, 71), (68, 130, 32),
+              (100, 33, 129), (130, 66, 200)]
+
+
+@pytest.mark.parametrize("split", [None, 1, 3])
+@pytest.mark.parametrize("m,n,k", F32_SHAPES)
+def test_fp32_grid_bit_exact(m, n, k, split, monkeypatch):
+    if split is not None:
+        monkeypatch.setenv("TPP_SPLIT", str(split))
+    for i, (kind, c_type, beta, flags, gm, gn, pad) in enumerate([
+            ("stride", "f32", 0.0, ("bias", "relu"), 3, 2, 0),
+            ("offset", "bf16", 1.0, ("bias",), 2, 3, 1),
+            ("stride", "f32", 1.0, (), 1, 1, 5)]):
+        wl = grid_case(m, n, k, 3, kind, c_type, beta, flags, gm, gn, pad, m * 100 + k + i, "f32")
+        print(f"fp32 {m}x{n}x{k} {kind} {c_type} split {split}", flush=True)
+        got, names = run_gpu(wl)
+        assert ("kernel<true>" in names[0]) == (m >= 4 and k >= 4), names
+        assert_bits_equal(got["c"], run_oracle(wl)[0], f"{names[0]} {m}x{n}x{k}")
+
+
+@pytest.mark.parametrize("count", [1, 5, 64, 65, 130])
+@pytest.mark.parametrize("kind", ["offset", "address"])
+def test_fp32_lists_past_64_pairs(kind, count):
+    # the entries of 64 pairs are held in lanes and refilled
+    wl = wk.small_case(np.random.default_rng(count), 36, 20, 24, count, kind, "f32", "f32", 1.0,
+                       {"bias"}, pad=1, integer=True)
+    print(f"fp32 {kind} of {count}", flush=True)
+    got, names = run_gpu(wl)
+    assert_bits_equal(got["c"], run_oracle(wl)[0], names[0])
+
+
+def test_fp32_split_call_under_capture():
+    """A split call needs a work buffer; on a stream that has none, under capture, it runs unsplit."""
+    from paper_2104_05755_amd import torch_io
+    wl = grid_case(64, 64, 64, 8, "stride", "f32", 0.0, (), 1, 1, 0, 3, "f32")
+    dev = torch_io.upload(wl)
+    dc = torch_io.prepare(wl.calls[0], dev)
+    assert "split_finish" in torch_io.describe(dc)
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    print("capture", flush=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        torch_io.launch(dc, s.cuda_stream)
+    ref = run_oracle(wl)[0]
+    for _ in range(3):
+        dev["c"].fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert_bits_equal(torch_io.to_host(dev["c"], wl.arrays["c"]), ref, "replay")
