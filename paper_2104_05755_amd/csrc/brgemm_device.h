@@ -196,6 +196,11 @@ __device__ __forceinline__ void epi_aux(const BrgemmParams& p, int64_t e0, float
   }
 }
 
+// a / d for 0 <= a < 2^31 (FastDiv).
+__device__ __forceinline__ int32_t fdiv(uint32_t a, const FastDiv& d) {
+  return (int32_t)(((uint64_t)a * d.mul) >> d.sh);
+}
+
 // XCD-aware tile order: workgroups are handed to the 8 XCDs round-robin, so consecutive block
 // ids land on different L2s.  Remapping gives each XCD a contiguous run of tiles (neighbouring
 // tiles share A rows or B columns and so share that XCD's L2).
@@ -212,21 +217,27 @@ struct TileCoord {
 
 __device__ __forceinline__ TileCoord decode_tile_at(const BrgemmParams& p, int bm, int bn,
                                                    int64_t bid) {
-  const int64_t t = xcd_tile(bid, p.total_tiles);
-  const int64_t per_group = (int64_t)p.tiles_m * p.tiles_n;
+  // tile ids are block ids: below 2^31
+  const int32_t t = (int32_t)xcd_tile(bid, p.total_tiles);
   TileCoord tc;
-  tc.g = p.groups == 1 ? 0 : t / per_group;
-  const int64_t tin = t - tc.g * per_group;
+  int32_t tin = t;
+  tc.g = 0;
+  if (p.groups != 1) {
+    const int32_t g = fdiv(t, p.div_group);
+    tc.g = g;
+    tin = t - g * (p.tiles_m * p.tiles_n);
+  }
   // Bands of up to 8 tile rows: consecutive tiles walk down a band, then move one tile column
   // right, so the 32 tiles an XCD runs at once cover about 8 rows x 4 columns and share both
   // their A rows and their B columns in that XCD's L2.
   const int32_t band = p.tiles_m < 8 ? p.tiles_m : 8;
-  const int64_t per_band = (int64_t)band * p.tiles_n;
-  const int32_t b0 = (int32_t)(tin / per_band) * band;
-  const int32_t bh = (p.tiles_m - b0) < band ? (p.tiles_m - b0) : band;
-  const int64_t tb = tin - (int64_t)b0 * p.tiles_n;
-  tc.row0 = (b0 + (int32_t)(tb % bh)) * bm;
-  tc.col0 = (int32_t)(tb / bh) * bn;
+  const int32_t b0 = fdiv(tin, p.div_band) * band;
+  const int32_t rows = p.tiles_m - b0;
+  const int32_t tb = tin - b0 * p.tiles_n;
+  const int32_t col = rows < band ? fdiv(tb, p.div_last) : fdiv(tb, p.div_rows);
+  const int32_t bh = rows < band ? rows : band;
+  tc.row0 = (b0 + tb - col * bh) * bm;
+  tc.col0 = col * bn;
   return tc;
 }
 
@@ -239,7 +250,7 @@ __device__ __forceinline__ TileCoord decode_tile(const BrgemmParams& p, int bm, 
 __device__ __forceinline__ bool row_in_a(const BrgemmParams& p, int32_t R, int64_t& off) {
   if (p.fused) {
     if (R >= p.vrows) return false;
-    const int32_t gi = R / p.m, r = R - gi * p.m;
+    const int32_t gi = fdiv(R, p.div_m), r = R - gi * p.vm;
     off = (int64_t)gi * p.a_step_m + r;
     return true;
   }
@@ -251,7 +262,7 @@ __device__ __forceinline__ bool row_in_a(const BrgemmParams& p, int32_t R, int64
 __device__ __forceinline__ bool row_in_at(const BrgemmParams& p, int32_t R, int64_t& off) {
   if (p.fused) {
     if (R >= p.vrows) return false;
-    const int32_t gi = R / p.m, r = R - gi * p.m;
+    const int32_t gi = fdiv(R, p.div_m), r = R - gi * p.vm;
     off = (int64_t)gi * p.a_step_m + (int64_t)r * p.lda;
     return true;
   }
@@ -263,7 +274,7 @@ __device__ __forceinline__ bool row_in_at(const BrgemmParams& p, int32_t R, int6
 __device__ __forceinline__ bool col_in_bt(const BrgemmParams& p, int32_t C, int64_t& off) {
   if (p.fused) {
     if (C >= p.vcols) return false;
-    const int32_t gi = C / p.n, c = C - gi * p.n;
+    const int32_t gi = fdiv(C, p.div_n), c = C - gi * p.n;
     off = (int64_t)gi * p.b_step_n + c;
     return true;
   }
@@ -275,7 +286,7 @@ __device__ __forceinline__ bool col_in_bt(const BrgemmParams& p, int32_t C, int6
 __device__ __forceinline__ bool col_in_b(const BrgemmParams& p, int32_t C, int64_t& off) {
   if (p.fused) {
     if (C >= p.vcols) return false;
-    const int32_t gi = C / p.n, c = C - gi * p.n;
+    const int32_t gi = fdiv(C, p.div_n), c = C - gi * p.n;
     off = (int64_t)gi * p.b_step_n + (int64_t)c * p.ldb;
     return true;
   }
@@ -294,7 +305,8 @@ __device__ __forceinline__ Instance instance_of(const BrgemmParams& p, int64_t g
   Instance in;
   in.a = in.b = in.c = in.bias = 0;
   if (!p.fused && p.grid_form) {
-    const int64_t gi_m = g % p.gm, gi_n = g / p.gm;
+    const int32_t gi_n = fdiv((uint32_t)g, p.div_gm);
+    const int64_t gi_m = g - gi_n * p.gm;
     in.a = gi_m * p.a_step_m;
     in.b = gi_n * p.b_step_n;
     in.c = gi_m * p.c_step_m + gi_n * p.c_step_n;
@@ -510,8 +522,7 @@ __device__ __forceinline__ void epilogue_via_lds(const BrgemmParams& p, const In
   int64_t row_off, bias_idx;
   int32_t nr = 8;                                    // valid rows of the lane's chunk
   if (p.fused) {
-    const int32_t im = RAGGED ? p.vm : p.m;
-    const int32_t gi = R / im, r = R - gi * im;
+    const int32_t gi = fdiv(R, p.div_m), r = R - gi * p.vm;
     row_ok = FULL || R < p.vrows;
     row_off = (int64_t)gi * p.c_step_m + r;
     bias_idx = (int64_t)gi * p.bias_step_m + r;
@@ -553,7 +564,7 @@ __device__ __forceinline__ void epilogue_via_lds(const BrgemmParams& p, const In
       int64_t col_off;
       bool col_ok;
       if (p.fused) {
-        const int32_t gi = C / p.n, c = C - gi * p.n;
+        const int32_t gi = fdiv(C, p.div_n), c = C - gi * p.n;
         col_ok = FULL || C < p.vcols;
         col_off = (int64_t)gi * p.c_step_n + (int64_t)c * p.ldc;
       } else {
@@ -639,8 +650,8 @@ __device__ __forceinline__ void load_bias4(const BrgemmParams& p, const Instance
   const int32_t R0 = row_base + 4 * half;
   int32_t gi = 0, r = R0;
   if (p.fused) {
-    gi = R0 / p.m;
-    r = R0 - gi * p.m;
+    gi = fdiv(R0, p.div_m);
+    r = R0 - gi * p.vm;
   }
   int64_t idx = p.fused ? (int64_t)gi * p.bias_step_m + r : in.bias + R0;
 #pragma unroll
@@ -710,7 +721,7 @@ __device__ __forceinline__ void epilogue_bf16_act(const BrgemmParams& p, const I
     bool row_ok;
     int64_t row_off;
     if (p.fused) {
-      const int32_t gi = R / p.m, r = R - gi * p.m;
+      const int32_t gi = fdiv(R, p.div_m), r = R - gi * p.vm;
       row_ok = FULL || R < p.vrows;
       row_off = (int64_t)gi * p.c_step_m + r;
     } else {
@@ -721,7 +732,7 @@ __device__ __forceinline__ void epilogue_bf16_act(const BrgemmParams& p, const I
     int32_t cin = C;
     int64_t col_off;
     if (p.fused) {
-      const int32_t gi = C / p.n;
+      const int32_t gi = fdiv(C, p.div_n);
       cin = C - gi * p.n;
       col_off = (int64_t)gi * p.c_step_n + (int64_t)cin * p.ldc;
     } else {
@@ -821,7 +832,7 @@ __device__ __forceinline__ void epilogue_bf16_act(const BrgemmParams& p, const I
     const int32_t C0 = tc.col0 + wn * WTN;
     auto row_offset = [&](int32_t R, bool& ok) -> int64_t {
       if (p.fused) {
-        const int32_t gi = R / p.m, r = R - gi * p.m;
+        const int32_t gi = fdiv(R, p.div_m), r = R - gi * p.vm;
         ok = FULL || R < p.vrows;
         return (int64_t)gi * p.c_step_m + r;
       }
@@ -830,7 +841,7 @@ __device__ __forceinline__ void epilogue_bf16_act(const BrgemmParams& p, const I
     };
     auto col_offset = [&](int32_t C) -> int64_t {
       if (p.fused) {
-        const int32_t gi = C / p.n;
+        const int32_t gi = fdiv(C, p.div_n);
         return (int64_t)gi * p.c_step_n + (int64_t)(C - gi * p.n) * p.ldc;
       }
       return (int64_t)C * p.ldc;

@@ -93,21 +93,23 @@ void brgemm_bf16_dl_kernel(BrgemmParams p) {
   // tile b % total_tiles (consecutive block ids still alternate over the XCDs, as the tile order
   // assumes) into a partial tile of the work buffer; a finishing kernel adds the chunks.
   const int64_t bid = blockIdx.x;
-  const int32_t chunk = p.split > 1 ? (int32_t)(bid / p.total_tiles) : 0;
+  const int32_t chunk = p.split > 1 ? fdiv((uint32_t)bid, p.div_tiles) : 0;
   const int64_t tile_bid = bid - (int64_t)chunk * p.total_tiles;
   const TileCoord tc = decode_tile_at(p, BM, BN, tile_bid);
   const Instance in = instance_of(p, tc.g);
   const int32_t ksteps = p.k / DL_BK;
   const int32_t all_stages = (int32_t)(in.npairs * ksteps);
-  const int32_t s_first = p.split > 1 ? (int32_t)((int64_t)all_stages * chunk / p.split) : 0;
-  const int32_t stages =
-      p.split > 1 ? (int32_t)((int64_t)all_stages * (chunk + 1) / p.split) - s_first : all_stages;
+  int32_t s_first = 0, stages = all_stages;
+  if (p.split > 1) {
+    s_first = chunk * p.split_base + min(chunk, p.split_rem);
+    stages = p.split_base + (chunk < p.split_rem ? 1 : 0);
+  }
 
   // Element offsets of the first instance block the tile touches in A and in B: every row / column
   // offset of the tile is at least this (the host takes this kernel only for non-negative steps
   // and a tile span below 2^31 bytes), so loads address the operands as base + 32-bit offset.
-  const int64_t base_a = p.fused ? (int64_t)(tc.row0 / p.m) * p.a_step_m : 0;
-  const int64_t base_b = p.fused ? (int64_t)(tc.col0 / p.n) * p.b_step_n : 0;
+  const int64_t base_a = p.fused ? (int64_t)fdiv(tc.row0, p.div_m) * p.a_step_m : 0;
+  const int64_t base_b = p.fused ? (int64_t)fdiv(tc.col0, p.div_n) * p.b_step_n : 0;
 
   // Per-lane load assignments.  A wave-load r covers bytes [q*1024, q*1024 + 1024) of the A
   // panel (q = wave * A_PER_W + r); lane j fills the 16-byte chunk at q*1024 + 16 j, i.e. k-row
@@ -177,7 +179,7 @@ void brgemm_bf16_dl_kernel(BrgemmParams p) {
   // Stages are issued in order; (iss_i, iss_kk) is the pair and k offset of the next one, so no
   // stage index is ever divided.  A stage's wave-loads can be spread over other work:
   // stage_begin(), issue_load(r) for r < LPS (A loads first, then B), stage_end().
-  int32_t iss_i = s_first / ksteps, iss_kk = (s_first - iss_i * ksteps) * DL_BK, iss_s = 0;
+  int32_t iss_i = p.split > 1 ? fdiv(s_first, p.div_ks) : 0, iss_kk = (s_first - iss_i * ksteps) * DL_BK, iss_s = 0;
   const char* ua = nullptr;
   const char* ub = nullptr;
   i32x4 ra, rb;

@@ -44,7 +44,7 @@ __device__ __forceinline__ void store_group(const BrgemmParams& p, const Instanc
   int64_t col_off;
   if (p.fused) {
     if (C >= p.vcols) return;
-    const int32_t gi = C / p.n, c = C - gi * p.n;
+    const int32_t gi = fdiv(C, p.div_n), c = C - gi * p.n;
     col_off = (int64_t)gi * p.c_step_n + (int64_t)c * p.ldc;
   } else {
     if (C >= p.n) return;
@@ -59,7 +59,7 @@ __device__ __forceinline__ void store_group(const BrgemmParams& p, const Instanc
     int32_t nr;
     if (p.fused) {
       if (R0 >= p.vrows) return;
-      const int32_t gi = R0 / p.vm, r = R0 - gi * p.vm;
+      const int32_t gi = fdiv(R0, p.div_m), r = R0 - gi * p.vm;
       row_off = (int64_t)gi * p.c_step_m + r;
       bias_idx = (int64_t)gi * p.bias_step_m + r;
       nr = p.m - r;
@@ -137,7 +137,7 @@ __device__ __forceinline__ void store_group(const BrgemmParams& p, const Instanc
       int64_t row_off, bias_idx;
       if (p.fused) {
         if (R >= p.vrows) continue;
-        const int32_t gi = R / p.m, r = R - gi * p.m;
+        const int32_t gi = fdiv(R, p.div_m), r = R - gi * p.vm;
         row_off = (int64_t)gi * p.c_step_m + r;
         bias_idx = (int64_t)gi * p.bias_step_m + r;
       } else {
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
     a_off[rep] = 0;
     if constexpr (RAGGED) {
       const int32_t R = tc.row0 + a_row[rep];
-      const int32_t gi = p.fused ? R / p.vm : 0, r = R - gi * p.vm;
+      const int32_t gi = p.fused ? fdiv(R, p.div_m) : 0, r = R - gi * p.vm;
       a_ok[rep] = q < A_SUB && R < p.vrows;
       if (a_ok[rep]) {
         const int32_t d = r + 8 > p.m ? r + 8 - p.m : 0;   // the window ends with the block
@@ -683,19 +683,25 @@ struct F32Work {
   TileCoord tc;
   Instance in;
   int64_t s_lo, stages;   // first stage and how many (stage = pair * ksteps + k-step)
+  int64_t i0;             // pair of the first stage
   int32_t ksteps;
 };
 __device__ __forceinline__ F32Work f32_work(const BrgemmParams& p) {
   F32Work w;
   w.split = p.split > 1 ? p.split : 1;
-  w.tile_bid = (int64_t)blockIdx.x / w.split;
+  w.tile_bid = p.split > 1 ? fdiv(blockIdx.x, p.div_split) : blockIdx.x;
   w.chunk = (int32_t)((int64_t)blockIdx.x - w.tile_bid * w.split);
   w.tc = decode_tile_at(p, F_BM, F_BN, w.tile_bid);
   w.in = instance_of(p, w.tc.g);
   w.ksteps = (p.k + F_BK - 1) / F_BK;
-  const int64_t all = w.in.npairs * w.ksteps;
-  w.s_lo = all * w.chunk / w.split;
-  w.stages = all * (w.chunk + 1) / w.split - w.s_lo;
+  w.s_lo = 0;
+  w.i0 = 0;
+  w.stages = w.in.npairs * w.ksteps;
+  if (p.split > 1) {
+    w.s_lo = (int64_t)w.chunk * p.split_base + min(w.chunk, p.split_rem);
+    w.stages = p.split_base + (w.chunk < p.split_rem ? 1 : 0);
+    w.i0 = fdiv((uint32_t)w.s_lo, p.div_ks);
+  }
   return w;
 }
 
@@ -736,7 +742,7 @@ struct F32Rows {
 __device__ __forceinline__ F32Rows f32_rows(const BrgemmParams& p, const F32Work& w, int chunk) {
   F32Rows o;
   const int32_t R = w.tc.row0 + chunk * 4;
-  const int32_t gi = p.fused ? R / p.vm : 0, r = R - gi * p.vm;
+  const int32_t gi = p.fused ? fdiv(R, p.div_m) : 0, r = R - gi * p.vm;
   o.off = (p.fused ? (int64_t)gi * p.c_step_m : 0) + r;
   o.nr = R >= p.vrows ? 0 : (p.m - r < 4 ? p.m - r : 4);
   const int64_t bi = p.fused ? (int64_t)gi * p.bias_step_m + r : w.in.bias + r;
@@ -750,7 +756,7 @@ __device__ __forceinline__ F32Rows f32_rows(const BrgemmParams& p, const F32Work
 __device__ __forceinline__ void f32_store4(const BrgemmParams& p, const F32Work& w,
                                            const F32Rows& rows, int32_t C, f32x4 x) {
   if (rows.nr == 0 || C >= (p.fused ? p.vcols : p.n)) return;
-  const int32_t gi = p.fused ? C / p.n : 0, c = C - gi * p.n;
+  const int32_t gi = p.fused ? fdiv(C, p.div_n) : 0, c = C - gi * p.n;
   const int64_t e0 = w.in.c + rows.off + (p.fused ? (int64_t)gi * p.c_step_n : 0) + c * p.ldc;
   float v[4] = {x[0], x[1], x[2], x[3]};
   if (rows.nr < 4) {
@@ -827,7 +833,7 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
     const int q = t + F_NT * j;
     const int ka = q >> 4, kb = (q & 15) * 4;
     const int32_t R = w.tc.row0 + (q & 15) * 4;
-    const int32_t gi = p.fused ? R / p.vm : 0;
+    const int32_t gi = p.fused ? fdiv(R, p.div_m) : 0;
     int32_t r = R - gi * p.vm;
     int64_t base = p.fused ? gi * p.a_step_m : 0;
     if (R >= p.vrows) {
@@ -850,8 +856,8 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
 
   // Stages are loaded strictly in order by a cursor: pair i (bases pa, pb), k offset kk.  Offset
   // and pointer lists: lane l holds the entries of pair 64 (i / 64) + l, taken with readlane.
-  int64_t ld_s = 0, ld_i = stages > 0 ? w.s_lo / w.ksteps : 0;
-  int32_t ld_kk = stages > 0 ? (int32_t)(w.s_lo - ld_i * w.ksteps) * F_BK : 0;
+  int64_t ld_s = 0, ld_i = w.i0;
+  int32_t ld_kk = (int32_t)(w.s_lo - ld_i * w.ksteps) * F_BK;
   const char* pa = nullptr;
   const char* pb = nullptr;
   uint64_t list_a = 0, list_b = 0;
@@ -1227,6 +1233,26 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
   p.tiles_m = (p.vrows + bm - 1) / bm;
   p.tiles_n = (p.vcols + bn - 1) / bn;
   p.total_tiles = p.groups * p.tiles_m * p.tiles_n;
+  {
+    const int32_t band = p.tiles_m < 8 ? p.tiles_m : 8;
+    const int32_t last = p.tiles_m % 8 ? p.tiles_m % 8 : 8;
+    const int32_t kstep = id == K_F32_GENERIC ? F_BK : kInfo[id].kstep > 1 ? kInfo[id].kstep : BK;
+    p.div_m = FastDiv(p.vm);
+    p.div_n = FastDiv(p.n);
+    p.div_gm = FastDiv(p.gm > 0 && p.gm < (1LL << 31) ? p.gm : 1);
+    p.div_group = FastDiv((int64_t)p.tiles_m * p.tiles_n);
+    p.div_band = FastDiv((int64_t)band * p.tiles_n);
+    p.div_tiles = FastDiv(p.total_tiles > 0 ? p.total_tiles : 1);
+    p.div_rows = FastDiv(band);
+    p.div_last = FastDiv(last);
+    p.div_split = FastDiv(p.split > 1 ? p.split : 1);
+    p.div_ks = FastDiv((p.k + kstep - 1) / kstep);
+    if (p.split > 1) {   // stride and offset kinds, and single lists: `count` pairs everywhere
+      const int64_t stages = p.count * ((p.k + kstep - 1) / kstep);
+      p.split_base = (int32_t)(stages / p.split);
+      p.split_rem = (int32_t)(stages % p.split);
+    }
+  }
   if (p.total_tiles <= 0) {
     if (name_out) *name_out = "";
     return hipSuccess;

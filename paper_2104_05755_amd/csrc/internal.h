@@ -13,6 +13,22 @@
 
 namespace tpp {
 
+// Division of values below 2^31 by a divisor known to the host: a / d = a * mul >> sh, with
+// mul = floor(2^sh / d) + 1 and sh = 31 + ceil(log2 d), so that mul * d - 2^sh <= 2^ceil(log2 d) and
+// the quotient is exact.  A multiply and a shift where a division by a run-time value is a chain of
+// about 25 dependent instructions: the tile, row and column decoding of a BRGEMM kernel has some
+// ten of them (see brgemm_device.h).
+struct FastDiv {
+  uint32_t mul = 1u << 31, sh = 31;   // division by 1
+  FastDiv() = default;
+  explicit FastDiv(int64_t d) {
+    int l = 0;
+    while ((int64_t(1) << l) < d) ++l;
+    sh = 31 + l;
+    mul = (uint32_t)((uint64_t(1) << sh) / (uint64_t)d + 1);
+  }
+};
+
 // Everything one batched BRGEMM launch needs, resolved on the host and passed by value.
 struct BrgemmParams {
   const void* a;
@@ -60,7 +76,12 @@ struct BrgemmParams {
   // workgroups into ws (split x total_tiles fp32 tiles), then summed in chunk order by a
   // finishing kernel that applies the epilogue.
   int32_t split;             // 1: no split
+  int32_t split_base, split_rem;   // chunk c has split_base stages, and one more if c < split_rem
   float* ws;
+  // Divisors of the decoding, filled by the launcher with the tiling: vm, n and gm; the tiles of a
+  // group, of a band of tile rows and of all groups, the tile rows of a whole and of the last band;
+  // split; the k-steps of a pair.
+  FastDiv div_m, div_n, div_gm, div_group, div_band, div_tiles, div_rows, div_last, div_split, div_ks;
   // Tensor of C's type and layout read or written by the back-propagation epilogue bits.
   void* aux;
 };
