@@ -167,8 +167,7 @@ struct TransformParams {
   int32_t kind, m, n;
   int64_t ld_in, ld_out;
   int32_t es, alpha;
-  int32_t vec;
-  int64_t tiles_m;
+  uint32_t tiles_n;   // tiles along n, filled by the launcher
   // Batch of G calls: call g reads in + g * in_stride and writes out + g * out_stride (elements).
   int64_t G;
   int64_t in_stride;

@@ -818,13 +818,8 @@ tpp_status transform_impl(int32_t kind, int32_t m, int32_t n, int64_t ld_in, int
   if (m == 0 || n == 0 || G == 0) return ok();
   if (!in || !out) return fail(TPP_ERR_INVALID_ARG, "NULL input or output");
   const int32_t es = dtype == TPP_DT_F32 ? 4 : 2;
-  // the 16-byte paths need every block of the batch aligned: the bases, the leading dimensions
-  // and (for G > 1) the block strides in whole 16-byte units
-  const bool vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0 &&
-                   (ld_in * es) % 16 == 0 && (ld_out * es) % 16 == 0 &&
-                   (G == 1 || ((in_stride * es) % 16 == 0 && (out_stride * es) % 16 == 0));
-  tpp::TransformParams p{in, out, kind, m, n, ld_in, ld_out, es, alpha, vec ? 1 : 0, 0,
-                         G, in_stride, out_stride};
+  tpp::TransformParams p{in, out, kind, m, n, ld_in, ld_out, es, alpha, 0, G, in_stride,
+                         out_stride};
   const hipError_t e = tpp::launch_transform(p, static_cast<hipStream_t>(stream));
   if (e == hipErrorInvalidConfiguration)
     return fail(TPP_ERR_UNSUPPORTED, "transform needs more than 2^31 - 1 workgroups");

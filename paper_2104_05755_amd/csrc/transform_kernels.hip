@@ -5,14 +5,15 @@
 // written once.  The paper builds its transposes from register shuffle networks (Sec. 3.3.1);
 // here a workgroup stages a 64 x 64 tile in LDS, reading it along the input's contiguous
 // direction and writing it along the output's, so both sides are coalesced.
-//   - Transpose: 16-byte loads and stores when the operands allow (aligned bases, leading
-//     dimensions of whole 16-byte units) and the tile is whole; the LDS tile keeps 16-byte
-//     chunks XOR-swizzled by column, so the column-wise gathers of the write phase hit distinct
-//     banks.  Ragged tiles and other operands move entry by entry.
+//   - Transpose: 16-byte loads and stores at any alignment; the LDS tile keeps 16-byte chunks
+//     XOR-swizzled by column, so the column-wise gathers of the write phase hit distinct banks.
+//     Only blocks with an edge below the tile's move entry by entry.
 //   - VNNI: no LDS: each thread writes one 16-byte chunk of an output group, gathering its
-//     alpha columns with one (16 / alpha)-byte load each.
+//     alpha columns with one (16 / alpha)-byte load each, at any alignment (bf16 4097 x 2049
+//     16.1 -> 6.6 us against aligned operands only).
 //   - VNNI to VNNI-transpose: the tiled kernel with both sides addressed in the VNNI layout,
-//     16-byte chunks on whole aligned tiles, entry by entry otherwise.
+//     16-byte chunks on whole tiles (at any alignment: bf16 4097 x 2049 20.1 -> 10.3 us against
+//     aligned operands only), entry by entry on partial ones.
 #include <hip/hip_runtime.h>
 
 #include "brgemm_device.h"
@@ -25,7 +26,7 @@ using dev::gld;
 using dev::gst;
 using dev::u32x4;
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
 
 constexpr int TT = 64;     // tile edge, entries
 constexpr int TPB = 256;   // threads per workgroup
@@ -59,6 +60,22 @@ __device__ __forceinline__ typename Entry<ES>::T entry_of(const uint32_t* words,
     return (uint16_t)(words[e >> 1] >> (16 * (e & 1)));
 }
 
+// 16 bytes at an entry's own alignment.
+template <int ES>
+__device__ __forceinline__ u32x4 load16(const void* src) {
+  if constexpr (ES == 4)
+    return gld<dev::u32x4_a4>(src);
+  else
+    return gld<dev::u32x4_a2>(src);
+}
+template <int ES>
+__device__ __forceinline__ void store16(void* dst, u32x4 v) {
+  if constexpr (ES == 4)
+    gst<dev::u32x4_a4>(dst, v);
+  else
+    gst<dev::u32x4_a2>(dst, v);
+}
+
 // Position of entry (c, r) of a staged tile ([c][r], 64 entries per c) with the 16-byte chunks
 // of each c XOR-swizzled by c / V: a chunk keeps its 16 bytes together, and V consecutive c of
 // one r fall in different chunks.
@@ -68,48 +85,97 @@ __device__ __forceinline__ int tile_pos(int c, int r) {
   return c * TT + (((r / V) ^ ((c / V) % CH)) * V) + r % V;
 }
 
-// Workgroup b of a batched launch works on call g = b / per (per workgroups per call), whose
-// blocks start g * in_stride and g * out_stride entries on; returns the workgroup's index within
-// its call.
+// Index b of a batched launch belongs to call g = b / per (per indices per call), whose blocks
+// start g * in_stride and g * out_stride entries on; returns the index within its call.
 template <typename T>
-__device__ __forceinline__ int64_t batch_of(const TransformParams& p, int64_t per, const T*& in,
-                                            T*& out) {
-  const int64_t bid = blockIdx.x;
-  const int64_t g = bid / per;
-  in = static_cast<const T*>(p.in) + g * p.in_stride;
-  out = static_cast<T*>(p.out) + g * p.out_stride;
-  return bid - g * per;
+__device__ __forceinline__ uint32_t batch_of(const TransformParams& p, uint32_t b, uint32_t per,
+                                             const T*& in, T*& out) {
+  const uint32_t g = b / per;
+  in = static_cast<const T*>(p.in) + (int64_t)g * p.in_stride;
+  out = static_cast<T*>(p.out) + (int64_t)g * p.out_stride;
+  return b - g * per;
 }
 
-// Transpose: the n x m output's entry (c, r) = in(r, c).  Tile (r0, c0) of a flattened grid
-// (tiles_m tiles along m, per tiles per call).
-template <int ES>
-__global__ __launch_bounds__(TPB) void transpose_kernel(TransformParams p, int64_t per) {
-  using T = typename Entry<ES>::T;
+// The workgroup's tile (r0, c0).  Tiles are numbered along the output's contiguous direction and
+// each XCD (workgroup b is on XCD b % 8) takes a contiguous run of them: where rows are no whole 128-byte lines, the two tiles
+// that share a line write it into the same L2, which then writes it back whole.  Transpose of
+// fp32 4097 x 2049: 15.2 us in launch order along the input, 13.2 with runs per XCD along the
+// input, 12.3 so; 4096 x 2048 (lines of one tile each): 11.1, 11.5, 10.9.
+template <typename T>
+__device__ __forceinline__ void tile_of(const TransformParams& p, uint32_t per, const T*& in,
+                                        T*& out, int32_t& r0, int32_t& c0) {
+  const uint32_t x = blockIdx.x % 8, run = gridDim.x / 8, rest = gridDim.x % 8;
+  const uint32_t b = x * run + min(x, rest) + blockIdx.x / 8;
+  const uint32_t t = batch_of<T>(p, b, per, in, out);
+  const uint32_t tm = t / p.tiles_n;
+  r0 = (int32_t)tm * TT;
+  c0 = (int32_t)(t - tm * p.tiles_n) * TT;
+}
+
+// Moves the 64 x 64 window at in / out, less the chunks that lie wholly in its first dc columns or
+// dr rows (ALL: none).
+template <int ES, bool ALL>
+__device__ __forceinline__ void move_window(const typename Entry<ES>::T* in,
+                                            typename Entry<ES>::T* out, int64_t ld_in,
+                                            int64_t ld_out, int dr, int dc,
+                                            typename Entry<ES>::T* lds) {
   constexpr int V = 16 / ES, CH = TT / V;
+  const int t = threadIdx.x;
+  // chunk q: column q / CH, rows (q % CH) * V .. + V - 1 of the window
+  constexpr int N = TT * CH / TPB;
+  u32x4 x[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int q = i * TPB + t, cc = q / CH, rv = (q % CH) * V;
+    if (ALL || (cc + V > dc && rv + V > dr)) x[i] = load16<ES>(in + (int64_t)cc * ld_in + rv);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int q = i * TPB + t, cc = q / CH, rv = (q % CH) * V;
+    if (ALL || (cc + V > dc && rv + V > dr))
+      *reinterpret_cast<u32x4*>(lds + tile_pos<ES>(cc, rv)) = x[i];
+  }
+  __syncthreads();
+  // chunk q: output column q / CH (an input row), entries (q % CH) * V .. + V - 1
+#pragma unroll
+  for (int q = t; q < TT * CH; q += TPB) {
+    const int rr = q / CH, cv = (q % CH) * V;
+    if (ALL || (rr >= dr && cv + V > dc)) {
+      typename Entry<ES>::T v[V];
+#pragma unroll
+      for (int j = 0; j < V; ++j) v[j] = lds[tile_pos<ES>(cv + j, rr)];
+      store16<ES>(out + (int64_t)rr * ld_out + cv, pack16<ES>(v));
+    }
+  }
+}
+
+// Transpose: the n x m output's entry (c, r) = in(r, c), per tiles per call.  Memory-bound.  From
+// 64 x 64 up every tile is a window of 64 x 64 entries inside the block, moved in 16-byte chunks
+// at any alignment: the window of a last, partial tile starts further back, and the chunks that
+// lie wholly in the tiles before it are left to them (the rest of a chunk is written twice, with
+// the same entries).  Smaller blocks move entry by entry.  Against entry by entry wherever bases
+// or leading dimensions are no whole 16-byte units or a tile is partial: fp32 4097 x 2049
+// 19.7 -> 11.9 us (5.6 TB/s), bf16 4097 x 4095 31.5 -> 12.7, 512 calls of fp32 65 x 65
+// 13.6 -> 6.1, of 64 x 64 (aligned) 4.25 -> 3.9.
+template <int ES>
+__global__ __launch_bounds__(TPB) void transpose_kernel(TransformParams p, uint32_t per) {
+  using T = typename Entry<ES>::T;
   __shared__ __attribute__((aligned(16))) T lds[TT * TT];
   const int t = threadIdx.x;
   const T* in;
   T* out;
-  const int64_t bid = batch_of<T>(p, per, in, out);
-  const int32_t r0 = (int32_t)(bid % p.tiles_m) * TT, c0 = (int32_t)(bid / p.tiles_m) * TT;
-  const bool whole = r0 + TT <= p.m && c0 + TT <= p.n;
-  if (whole && p.vec) {
-    // chunk q: input column c0 + q / CH, rows r0 + (q % CH) * V .. + V - 1
-    for (int q = t; q < TT * CH; q += TPB) {
-      const int cc = q / CH, rv = (q % CH) * V;
-      const u32x4 v = gld<u32x4>(in + (int64_t)(c0 + cc) * p.ld_in + r0 + rv);
-      *reinterpret_cast<u32x4*>(lds + tile_pos<ES>(cc, rv)) = v;
-    }
-    __syncthreads();
-    // chunk q: output column r0 + q / CH (an input row), entries c0 + (q % CH) * V .. + V - 1
-    for (int q = t; q < TT * CH; q += TPB) {
-      const int rr = q / CH, cv = (q % CH) * V;
-      T v[V];
-#pragma unroll
-      for (int j = 0; j < V; ++j) v[j] = lds[tile_pos<ES>(cv + j, rr)];
-      gst<u32x4>(out + (int64_t)(r0 + rr) * p.ld_out + c0 + cv, pack16<ES>(v));
-    }
+  int32_t r0, c0;
+  tile_of<T>(p, per, in, out, r0, c0);
+  if (p.m >= TT && p.n >= TT) {
+    // the tile's window, and the entries of it that an earlier tile moves
+    const int32_t rw = min(r0, p.m - TT), cw = min(c0, p.n - TT);
+    const int dr = r0 - rw, dc = c0 - cw;
+    in += (int64_t)cw * p.ld_in + rw;
+    out += (int64_t)rw * p.ld_out + cw;
+    if (dr == 0 && dc == 0)
+      move_window<ES, true>(in, out, p.ld_in, p.ld_out, 0, 0, lds);
+    else
+      move_window<ES, false>(in, out, p.ld_in, p.ld_out, dr, dc, lds);
   } else {
     for (int q = t; q < TT * TT; q += TPB) {
       const int cc = q / TT, rr = q % TT;
@@ -128,24 +194,24 @@ __global__ __launch_bounds__(TPB) void transpose_kernel(TransformParams p, int64
 // VNNI to VNNI-transpose: logical tile rows [r0, r0 + 64), columns [c0, c0 + 64) (both multiples
 // of alpha, so groups never straddle tiles), staged as lds[c][r].  Reads walk the input's
 // contiguous order (c % alpha fastest, then r), writes the output's (r % alpha fastest, then c).
-// Whole tiles with aligned operands move 16-byte chunks on both sides: an input chunk is
+// Whole tiles move 16-byte chunks on both sides: an input chunk is
 // V / alpha rows of one group's alpha columns, an output chunk V / alpha columns of one output
 // group's alpha rows.  Output rows from m up to the next multiple of alpha are the zero
 // completion of the last group (never in a whole tile).
 template <int ES, int ALPHA>
-__global__ __launch_bounds__(TPB) void vnni_t_kernel(TransformParams p, int64_t per) {
+__global__ __launch_bounds__(TPB) void vnni_t_kernel(TransformParams p, uint32_t per) {
   using T = typename Entry<ES>::T;
   constexpr int V = 16 / ES, CPG = TT * ALPHA / V;   // 16-byte chunks per group of a tile
   __shared__ T lds[TT][TT + 1];
   const int t = threadIdx.x;
   const T* in;
   T* out;
-  const int64_t bid = batch_of<T>(p, per, in, out);
-  const int32_t r0 = (int32_t)(bid % p.tiles_m) * TT, c0 = (int32_t)(bid / p.tiles_m) * TT;
-  if (r0 + TT <= p.m && c0 + TT <= p.n && p.vec) {
+  int32_t r0, c0;
+  tile_of<T>(p, per, in, out, r0, c0);
+  if (r0 + TT <= p.m && c0 + TT <= p.n) {
     for (int q = t; q < TT * TT / V; q += TPB) {
       const int gi = q / CPG, j0 = (q % CPG) * V, rr0 = j0 / ALPHA;
-      const u32x4 w4 = gld<u32x4>(in + (int64_t)(c0 / ALPHA + gi) * p.ld_in +
+      const u32x4 w4 = load16<ES>(in + (int64_t)(c0 / ALPHA + gi) * p.ld_in +
                                   (int64_t)(r0 + rr0) * ALPHA);
       const uint32_t w[4] = {w4[0], w4[1], w4[2], w4[3]};
 #pragma unroll
@@ -157,8 +223,8 @@ __global__ __launch_bounds__(TPB) void vnni_t_kernel(TransformParams p, int64_t 
       T v[V];
 #pragma unroll
       for (int e = 0; e < V; ++e) v[e] = lds[cc0 + e / ALPHA][gi * ALPHA + e % ALPHA];
-      gst<u32x4>(out + (int64_t)(r0 / ALPHA + gi) * p.ld_out + (int64_t)(c0 + cc0) * ALPHA,
-                 pack16<ES>(v));
+      store16<ES>(out + (int64_t)(r0 / ALPHA + gi) * p.ld_out + (int64_t)(c0 + cc0) * ALPHA,
+                  pack16<ES>(v));
     }
     return;
   }
@@ -179,17 +245,17 @@ __global__ __launch_bounds__(TPB) void vnni_t_kernel(TransformParams p, int64_t 
   }
 }
 
-// A (16 / ALPHA)-byte load of the vector path, as 32-bit words.
-template <int BYTES>
+// A (16 / ALPHA)-byte load at an entry's own alignment, as 32-bit words.
+template <int ES, int BYTES>
 __device__ __forceinline__ void load_words(const void* src, uint32_t* w) {
   if constexpr (BYTES == 16) {
-    const u32x4 x = gld<u32x4>(src);
+    const u32x4 x = load16<ES>(src);
     w[0] = x[0], w[1] = x[1], w[2] = x[2], w[3] = x[3];
   } else if constexpr (BYTES == 8) {
-    const u32x2 x = gld<u32x2>(src);
+    const dev::u32x2_a2 x = gld<dev::u32x2_a2>(src);
     w[0] = x[0], w[1] = x[1];
   } else {
-    w[0] = gld<uint32_t>(src);
+    w[0] = gld<u32_a2>(src);
   }
 }
 
@@ -198,29 +264,29 @@ __device__ __forceinline__ void load_words(const void* src, uint32_t* w) {
 // (j0 + V) / ALPHA - 1 of the group's ALPHA columns.  Columns past n are the zero completion.
 template <int ES, int ALPHA>
 __global__ __launch_bounds__(TPB) void vnni_kernel(TransformParams p, int64_t cpg, int64_t total,
-                                                   int64_t per) {
+                                                   uint32_t per) {
   using T = typename Entry<ES>::T;
   constexpr int V = 16 / ES, ROWS = V / ALPHA;
   const T* in;
   T* out;
-  const int64_t q = batch_of<T>(p, per, in, out) * TPB + threadIdx.x;
+  const int64_t q = (int64_t)batch_of<T>(p, blockIdx.x, per, in, out) * TPB + threadIdx.x;
   if (q >= total) return;
   const int64_t g = q / cpg;
   const int64_t j0 = (q - g * cpg) * V;
   const int64_t extent = (int64_t)p.m * ALPHA;
   T* o = out + g * p.ld_out + j0;
-  if (p.vec && j0 + V <= extent) {
+  if (j0 + V <= extent) {
     const int64_t r0 = j0 / ALPHA;
     T v[V];
 #pragma unroll
     for (int a = 0; a < ALPHA; ++a) {
       const int64_t c = g * ALPHA + a;
       uint32_t w[(ROWS * ES + 3) / 4] = {};
-      if (c < p.n) load_words<ROWS * ES>(in + c * p.ld_in + r0, w);
+      if (c < p.n) load_words<ES, ROWS * ES>(in + c * p.ld_in + r0, w);
 #pragma unroll
       for (int e = 0; e < ROWS; ++e) v[e * ALPHA + a] = entry_of<ES>(w, e);
     }
-    gst<u32x4>(o, pack16<ES>(v));
+    store16<ES>(o, pack16<ES>(v));
   } else {
     for (int e = 0; e < V && j0 + e < extent; ++e) {
       const int64_t j = j0 + e, r = j / ALPHA, c = g * ALPHA + j % ALPHA;
@@ -236,12 +302,12 @@ template <int ES>
 hipError_t launch_es(TransformParams& p, hipStream_t stream) {
   const int64_t tiles_n = (p.n + TT - 1) / TT;
   const int64_t G = p.G;
+  p.tiles_n = (uint32_t)tiles_n;
   if (p.kind == 0) {
-    p.tiles_m = (p.m + TT - 1) / TT;
-    const int64_t tiles = p.tiles_m * tiles_n;
+    const int64_t tiles = (p.m + TT - 1) / TT * tiles_n;
     if (!grid_fits(tiles, G)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(transpose_kernel<ES>, dim3((uint32_t)(tiles * G)), dim3(TPB), 0, stream, p,
-                       tiles);
+                       (uint32_t)tiles);
   } else if (p.kind == 1) {
     constexpr int V = 16 / ES;
     const int64_t cpg = ((int64_t)p.m * p.alpha + V - 1) / V;
@@ -250,20 +316,19 @@ hipError_t launch_es(TransformParams& p, hipStream_t stream) {
     if (!grid_fits(blocks, G)) return hipErrorInvalidConfiguration;
     const dim3 grid((uint32_t)(blocks * G));
     switch (p.alpha) {
-      case 1: hipLaunchKernelGGL((vnni_kernel<ES, 1>), grid, dim3(TPB), 0, stream, p, cpg, total, blocks); break;
-      case 2: hipLaunchKernelGGL((vnni_kernel<ES, 2>), grid, dim3(TPB), 0, stream, p, cpg, total, blocks); break;
-      default: hipLaunchKernelGGL((vnni_kernel<ES, 4>), grid, dim3(TPB), 0, stream, p, cpg, total, blocks); break;
+      case 1: hipLaunchKernelGGL((vnni_kernel<ES, 1>), grid, dim3(TPB), 0, stream, p, cpg, total, (uint32_t)blocks); break;
+      case 2: hipLaunchKernelGGL((vnni_kernel<ES, 2>), grid, dim3(TPB), 0, stream, p, cpg, total, (uint32_t)blocks); break;
+      default: hipLaunchKernelGGL((vnni_kernel<ES, 4>), grid, dim3(TPB), 0, stream, p, cpg, total, (uint32_t)blocks); break;
     }
   } else {
     const int64_t m_pad = ((int64_t)p.m + p.alpha - 1) / p.alpha * p.alpha;
-    p.tiles_m = (m_pad + TT - 1) / TT;
-    const int64_t tiles = p.tiles_m * tiles_n;
+    const int64_t tiles = (m_pad + TT - 1) / TT * tiles_n;
     if (!grid_fits(tiles, G)) return hipErrorInvalidConfiguration;
     const dim3 grid((uint32_t)(tiles * G));
     switch (p.alpha) {
-      case 1: hipLaunchKernelGGL((vnni_t_kernel<ES, 1>), grid, dim3(TPB), 0, stream, p, tiles); break;
-      case 2: hipLaunchKernelGGL((vnni_t_kernel<ES, 2>), grid, dim3(TPB), 0, stream, p, tiles); break;
-      default: hipLaunchKernelGGL((vnni_t_kernel<ES, 4>), grid, dim3(TPB), 0, stream, p, tiles); break;
+      case 1: hipLaunchKernelGGL((vnni_t_kernel<ES, 1>), grid, dim3(TPB), 0, stream, p, (uint32_t)tiles); break;
+      case 2: hipLaunchKernelGGL((vnni_t_kernel<ES, 2>), grid, dim3(TPB), 0, stream, p, (uint32_t)tiles); break;
+      default: hipLaunchKernelGGL((vnni_t_kernel<ES, 4>), grid, dim3(TPB), 0, stream, p, (uint32_t)tiles); break;
     }
   }
   return hipGetLastError();
