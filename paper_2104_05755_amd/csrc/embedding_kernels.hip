@@ -1,15 +1,22 @@
 // embedding_kernels.hip -- the sparse embedding gather-reduce of Alg. 5 for gfx950.
 //
-// One wavefront per bag.  A table row is split into 16-byte chunks (4 fp32 or 8 bf16 entries);
-// lpr lanes cover one row's chunks (all of them when the row has at most 64 chunks) and the
-// wavefront's 64 / lpr row slots take every slot-th listed index, so one load instruction reads
-// that many rows.  Each slot keeps U rows in flight (their index loads, then their row loads,
-// then the additions), which plays the part of Alg. 5's unrolled accumulators and next-row
-// prefetch.  The slots meet through cross-lane shuffles in slot order, and the accumulation
-// order depends only on the bag's list, so results do not vary between runs.  The sum is fp32
-// in registers and each output row is stored once.  Rows whose chunks are not 16-byte aligned
-// take an entry-per-lane kernel.  Indices outside [0, M) add nothing (the table is never read
-// outside its rows).
+// One wavefront per bag.  A table row is split into 16-byte chunks (4 fp32 or 8 bf16 entries, at
+// any alignment; a row that is no multiple of them ends with the 16-byte window that ends with it,
+// whose first entries the chunk before computes too, to the same bits); lpr lanes cover one row's
+// chunks (all of them when the row has at most 64 chunks) and the wavefront's 64 / lpr row slots
+// take every slot-th listed index, so one load instruction reads that many rows.  Each slot keeps U
+// rows in flight, which plays the part of Alg. 5's unrolled accumulators and next-row prefetch.
+// The indices come 64 to a load, a lane each, and reach their slots through shuffles.  The slots
+// meet through cross-lane shuffles, halving their number each time, and the accumulation order
+// depends only on the bag's list, so results do not vary between runs.  The sum is fp32 in
+// registers and each output row is stored once.  Rows shorter than a chunk take an entry-per-lane
+// kernel.  Indices outside [0, M) add nothing (the table is never read outside its rows).
+//
+// Bound by HBM on rows of 512 bytes, by the latency of the chain index - row - fold on short ones.
+// 16384 bags of 1 to 64 rows, 1M-row tables larger than the last-level cache: 128 fp32 52.2 us with
+// an index load in front of every U rows, 47.5 with one per 64; with the next U indices loaded
+// behind the rows 58.4.  100 bf16 (not whole chunks) 156 entry by entry, 29.4 in chunks; 16 bf16
+// (32 slots, folded one after the other before) 46.5 and 13.7; 13 fp32 72.6 and 15.8.
 #include <hip/hip_runtime.h>
 
 #include "brgemm_device.h"
@@ -38,56 +45,40 @@ __device__ __forceinline__ void widen16(u32x4 w, float (&x)[V]) {
   }
 }
 
-// N consecutive output entries at o (rounded to bf16 or stored as fp32), 16-byte stores when
-// aligned.
+// N consecutive output entries at o, at any alignment (rounded to bf16 or stored as fp32).
 template <bool OUT_BF16, int N>
 __device__ __forceinline__ void store_row_part(void* o, const float (&v)[N]) {
-  if constexpr (OUT_BF16) {
-    uint16_t* q = static_cast<uint16_t*>(o);
-    if constexpr (N == 8) {
-      if ((reinterpret_cast<uintptr_t>(q) & 15) == 0) {
-        gst<u32x4>(q, (u32x4){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                              pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])});
-        return;
-      }
-    }
-    if constexpr (N == 4) {
-      if ((reinterpret_cast<uintptr_t>(q) & 7) == 0) {
-        gst<u32x2>(q, (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])});
-        return;
-      }
-    }
+  if constexpr (OUT_BF16 && N == 8)
+    gst<u32x4_a2>(o, (u32x4){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
+                             pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])});
+  else if constexpr (OUT_BF16 && N == 4)
+    gst<u32x2_a2>(o, (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])});
+  else if constexpr (OUT_BF16)
+    gst<uint16_t>(o, f32_to_bf16_bits(v[0]));
+  else if constexpr (N == 1)
+    gst<float>(o, v[0]);
+  else
 #pragma unroll
-    for (int e = 0; e < N; ++e) gst<uint16_t>(q + e, f32_to_bf16_bits(v[e]));
-  } else {
-    float* q = static_cast<float*>(o);
-    if constexpr (N % 4 == 0) {
-      if ((reinterpret_cast<uintptr_t>(q) & 15) == 0) {
-#pragma unroll
-        for (int g = 0; g < N / 4; ++g)
-          gst<f32x4>(q + 4 * g, (f32x4){v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]});
-        return;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < N; ++e) gst<float>(q + e, v[e]);
-  }
+    for (int g = 0; g < N / 4; ++g)
+      gst<f32x4_a4>(static_cast<float*>(o) + 4 * g,
+                    (f32x4){v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]});
 }
 
-// 16-byte chunk path: E a multiple of V, the table and its row stride 16-byte aligned.
+// 16-byte chunk path: E >= V, any stride and alignment.
 // lpr lanes per row (chunks c0 + lane % lpr of a column group), rpw = 64 / lpr row slots.
 template <bool W_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(ET) void embedding_vec_kernel(EmbeddingParams p, int32_t lpr,
-                                                           int32_t rpw) {
+                                                           int32_t rpw, int32_t half) {
   constexpr int V = W_BF16 ? 8 : 4;
   constexpr int ES = W_BF16 ? 2 : 4;
   const int lane = threadIdx.x & 63;
   const int64_t b = (int64_t)blockIdx.x * (ET / 64) + (threadIdx.x >> 6);
   if (b >= p.n_bags) return;   // b is the same for the whole wavefront
   const int64_t j0 = p.begin[b], j1 = p.begin[b + 1];
-  const int32_t cpr = p.E / V;
+  const int32_t cpr = (p.E - 1) / V + 1;
   const int r = lane / lpr, cl = lane - (lane / lpr) * lpr;
   const bool slot_ok = r < rpw;
+  const int32_t nb = 64 - 64 % rpw;   // indices per block: whole rounds of the slots
   const char* wb = static_cast<const char*>(p.W);
   for (int32_t c0 = 0; c0 < cpr; c0 += lpr) {
     const int32_t c = c0 + cl;
@@ -95,44 +86,48 @@ __global__ __launch_bounds__(ET) void embedding_vec_kernel(EmbeddingParams p, in
     float acc[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = 0.0f;
-    for (int64_t j = j0 + r; j < j1; j += (int64_t)rpw * U) {
-      int64_t row[U];
+    // the first entry of the chunk; the last chunk is the window that ends with the row
+    const int32_t e0 = c < p.E / V ? c * V : p.E - V;
+    for (int64_t jb = j0; jb < j1; jb += nb) {
+      // lane l holds index jb + l; every slot takes its own from there
+      const int32_t left = j1 - jb < nb ? (int32_t)(j1 - jb) : nb;
+      const int64_t mine = lane < left ? gld<int64_t>(p.idx + jb + lane) : -1;
+      for (int32_t t = 0; t < left; t += rpw * U) {
+        u32x4 x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t jj = j + (int64_t)u * rpw;
-        row[u] = jj < j1 ? gld<int64_t>(p.idx + jj) : -1;
-      }
-      u32x4 x[U];
+        for (int u = 0; u < U; ++u) {
+          const int32_t at = t + u * rpw + r;
+          const int64_t row = __shfl(mine, at & 63, 64);
+          const bool take = ok && at < left && row >= 0 && row < p.M;
+          x[u] = take ? (u32x4)gld<u32x4_a2>(wb + (row * p.ldw + e0) * ES)
+                      : (u32x4){0u, 0u, 0u, 0u};
+        }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool take = ok && row[u] >= 0 && row[u] < p.M;
-        x[u] = take ? gld<u32x4>(wb + (row[u] * p.ldw + (int64_t)c * V) * ES)
-                    : (u32x4){0u, 0u, 0u, 0u};
-      }
+        for (int u = 0; u < U; ++u) {
+          float v[V];
+          widen16<W_BF16, V>(x[u], v);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        float v[V];
-        widen16<W_BF16, V>(x[u], v);
-#pragma unroll
-        for (int e = 0; e < V; ++e) acc[e] += v[e];
+          for (int e = 0; e < V; ++e) acc[e] += v[e];
+        }
       }
     }
-    // slot 0 adds slots 1, 2, ... in order
-    for (int s = 1; s < rpw; ++s) {
+    // slot s adds slot s + h, for h = the half (rounded up to a power of two) of the slots left
+    for (int h = half; h > 0; h >>= 1) {
+      const bool adds = r < h && r + h < rpw;
 #pragma unroll
       for (int e = 0; e < V; ++e) {
-        const float t = __shfl(acc[e], cl + s * lpr, 64);
-        if (r == 0) acc[e] += t;
+        const float t = __shfl(acc[e], lane + h * lpr, 64);
+        if (adds) acc[e] += t;
       }
     }
     if (r == 0 && c < cpr) {
-      char* ob = static_cast<char*>(p.out) + (b * p.ldo + (int64_t)c * V) * (OUT_BF16 ? 2 : 4);
+      char* ob = static_cast<char*>(p.out) + (b * p.ldo + e0) * (OUT_BF16 ? 2 : 4);
       store_row_part<OUT_BF16, V>(ob, acc);
     }
   }
 }
 
-// Entry-per-lane path for any E, stride and alignment.
+// Entry-per-lane path for rows shorter than a chunk.
 template <bool W_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(ET) void embedding_elem_kernel(EmbeddingParams p) {
   const int lane = threadIdx.x & 63;
@@ -157,14 +152,13 @@ __global__ __launch_bounds__(ET) void embedding_elem_kernel(EmbeddingParams p) {
 template <bool W_BF16, bool OUT_BF16>
 void launch_typed(const EmbeddingParams& p, dim3 grid, hipStream_t stream) {
   constexpr int V = W_BF16 ? 8 : 4;
-  const int es = W_BF16 ? 2 : 4;
-  const bool vec = p.E % V == 0 && (reinterpret_cast<uintptr_t>(p.W) & 15) == 0 &&
-                   (p.ldw * es) % 16 == 0;
-  if (vec) {
-    const int32_t cpr = p.E / V;
-    const int32_t lpr = cpr < 64 ? cpr : 64;
+  if (p.E >= V) {
+    const int32_t cpr = (p.E - 1) / V + 1;
+    const int32_t lpr = cpr < 64 ? cpr : 64, rpw = 64 / lpr;
+    int32_t half = 0;   // largest power of two below the number of row slots
+    for (int32_t h = 1; h < rpw; h *= 2) half = h;
     hipLaunchKernelGGL((embedding_vec_kernel<W_BF16, OUT_BF16>), grid, dim3(ET), 0, stream, p,
-                       lpr, 64 / lpr);
+                       lpr, rpw, half);
   } else {
     hipLaunchKernelGGL((embedding_elem_kernel<W_BF16, OUT_BF16>), grid, dim3(ET), 0, stream, p);
   }

@@ -1,7 +1,8 @@
 """GPU parity of the sparse embedding gather-reduce (Alg. 5), through the C ABI, against the CPU
 oracle: bit-exact on small-integer tables (every fp32 partial sum exact), relative Frobenius
 error <= 1e-5 for fp32 tables and outputs and <= 5e-3 once bf16 is involved, on both load paths
-(16-byte chunks with 1, 2, 4 or more rows per wavefront load, and entry per lane), empty and
+(16-byte chunks with 1, 2, 4 or more rows per wavefront load at any alignment, and entry per
+lane), empty and
 ragged bags, padded strides, skipped out-of-range indices, and the full-size lookup workload on
 sampled bags."""
 from __future__ import annotations
@@ -65,8 +66,8 @@ CASES = [  # rows, dim, bags, pooling, w_type, out_type, pad
     (300, 512, 9, (1, 20), "bf16", "f32", 0),     # 64 chunks: one slot
     (200, 1024, 5, (1, 12), "f32", "bf16", 0),    # 256 chunks: four column groups
     (400, 128, 33, (0, 30), "bf16", "bf16", 8),   # padded strides, still 16-byte aligned
-    (400, 13, 17, (0, 25), "f32", "f32", 0),      # entry-per-lane path
-    (400, 64, 17, (0, 25), "bf16", "bf16", 3),    # misaligned stride: entry-per-lane path
+    (400, 13, 17, (0, 25), "f32", "f32", 0),      # four chunks, the last one overlapping
+    (400, 64, 17, (0, 25), "bf16", "bf16", 3),    # misaligned stride
     (1, 8, 6, (0, 5), "f32", "f32", 0),           # a one-row table
 ]
 
@@ -91,6 +92,47 @@ def test_embedding_matches_oracle(case, integer):
     if pad:   # the output rows' gaps are untouched
         assert np.array_equal(got.reshape(bags, st.ldo)[:, dim:].view(np.uint8),
                               wl.arrays["out"].reshape(bags, st.ldo)[:, dim:].view(np.uint8))
+
+
+FORMS = [  # rows, dim, bags, pooling, w_type, out_type, pad, first entry of the table
+    (300, 100, 33, (0, 40), "bf16", "bf16", 0, 0),   # 13 chunks, the last one overlapping; four slots
+    (300, 9, 33, (0, 140), "bf16", "f32", 0, 1),     # two chunks overlapping by seven; 32 slots, two trips
+    (300, 8, 21, (0, 300), "bf16", "bf16", 0, 1),    # one chunk, 64 slots
+    (300, 4, 21, (0, 300), "f32", "bf16", 1, 1),     # the shortest fp32 row of the chunk path
+    (300, 7, 21, (0, 40), "bf16", "f32", 0, 0),      # the longest bf16 row of the entry path
+    (300, 3, 21, (0, 40), "f32", "f32", 0, 0),       # the longest fp32 row of the entry path
+    (300, 22, 21, (0, 90), "bf16", "bf16", 3, 1),    # three chunks: 21 slots, not a power of two
+    (200, 257, 15, (0, 20), "f32", "f32", 0, 3),     # 65 chunks: two column groups
+]
+
+
+@pytest.mark.parametrize("case", FORMS, ids=lambda c: "-".join(map(str, c)).replace(" ", ""))
+def test_embedding_any_row_length_and_alignment(case):
+    """Bit-exact on small integers: every row length around a chunk, every slot count's fold, tables
+    and outputs that begin at any entry; nothing beside the rows of the output is written."""
+    from paper_2104_05755_amd import (TPP_DT_BF16, TPP_DT_F32, tpp_embedding_bag)
+    rows, dim, bags, pool, wt, ot, pad, off = case
+    say(f"embedding {case}")
+    wl = small(rows + dim + bags, rows, dim, bags, pool, wt, ot, pad, integer=True)
+    st = wl.steps[0]
+    ref = run_ref(wl).reshape(bags, st.ldo)[:, :dim]
+    code = {"f32": TPP_DT_F32, "bf16": TPP_DT_BF16}
+    size = lambda t: 4 if t == "f32" else 2
+    raw = wl.arrays["w"].view(np.uint8)
+    w = torch.empty(raw.size + off * size(wt), dtype=torch.uint8, device="cuda")
+    w[off * size(wt):] = torch.from_numpy(raw.copy()).cuda()
+    out = torch.full(((bags * st.ldo + 2 * off) * size(ot),), 0xA5, dtype=torch.uint8, device="cuda")
+    begin = torch.from_numpy(wl.arrays[st.begin].copy()).cuda()
+    idx = torch.from_numpy(wl.arrays[st.idx].copy()).cuda()
+    tpp_embedding_bag(rows, dim, code[wt], w.data_ptr() + off * size(wt), st.ldw, bags, begin, idx,
+                      code[ot], out.data_ptr() + off * size(ot), st.ldo)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    edge = off * size(ot)
+    body = got[edge:got.size - edge].reshape(bags, st.ldo * size(ot))
+    assert np.array_equal(body[:, :dim * size(ot)], np.ascontiguousarray(ref).view(np.uint8))
+    rest = np.concatenate([got[:edge], got[got.size - edge:], body[:, dim * size(ot):].ravel()])
+    assert (rest == 0xA5).all()
 
 
 def test_out_of_range_indices_are_skipped():
