@@ -119,9 +119,12 @@ tpp_status tpp_brgemm_dispatch(const tpp_brgemm_desc* desc, tpp_brgemm_handle* o
  *   stride:  A_i = a + i * stride_a, B_i = b + i * stride_b
  *   offset:  A_i = a + offs_a[i],    B_i = b + offs_b[i]      (device int64 arrays, elements)
  *   address: A_i = ptrs_a[i],        B_i = ptrs_b[i]          (device arrays of device pointers)
- * An fp32 call whose output is only a few 64 x 64 tiles splits the pair list over several
+ * An fp32 call whose output is only a few 64 x 64 tiles splits its reduction over several
  * workgroups; their partial sums go to a device work buffer the library keeps per GPU and per
  * stream (as tpp_reduce) and are added in a fixed order, so results do not vary between runs.
+ * Under stream capture they go to a buffer of that capture's own, which the library never frees or
+ * uses for anything else, so a graph may be replayed on any stream, beside and after any other call
+ * (4 GiB per GPU for all captures of a process; a call that would pass them runs unsplit).
  * Errors: INVALID_ARG for a NULL handle, count < 0, a NULL pointer the call needs, or a handle
  * with an AUX bit (those run through tpp_brgemm_execute_batched_aux); NO_MEMORY if that work
  * buffer cannot be allocated. */
@@ -248,7 +251,8 @@ tpp_status tpp_brgemm_execute_batched_noalloc(
  *   (both may be set: one pass, two outputs).  fold: SUM (from 0), MUL (from 1), MIN, MAX.
  *   Outputs are device fp32 arrays.  Arithmetic is fp32; the summation order is unspecified.
  * Partial results go to a device work buffer the library keeps per GPU and per stream (allocated
- * on first use, kept until the process ends; growing it synchronises the device).  Exactly one of
+ * on first use, kept until the process ends; growing it synchronises the device), under stream
+ * capture to a buffer of the capture's own (see the BRGEMM calls above).  Exactly one of
  * BY_COLS / BY_ROWS, and at least one of X / X2, must be set.  Errors: INVALID_ARG for m, n <= 0,
  * ld < m, bad flags, NULL pointers; NO_MEMORY if the work buffer cannot be allocated. */
 typedef enum { TPP_RED_SUM = 0, TPP_RED_MUL = 1, TPP_RED_MIN = 2, TPP_RED_MAX = 3 } tpp_reduce_op;

@@ -211,19 +211,58 @@ tpp_status work_buffer(int purpose, void* stream, int64_t floats, float** out,
   return TPP_OK;
 }
 
-// Whether work_buffer would have to allocate while `stream` is being captured into a graph, where
-// the runtime refuses to: the caller then takes the form of its launch that needs no work space.
-bool grows_under_capture(int purpose, void* stream, int64_t floats) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  {
-    std::lock_guard<std::mutex> lock(g_work_mu);
-    const auto it = g_work.find(std::make_tuple(dev, stream, purpose));
-    if (it != g_work.end() && it->second.floats >= floats) return false;
-  }
+// Work space of calls captured into graphs.  A graph keeps the address it was captured with for as
+// long as it is replayed, on whatever stream and beside whatever eager calls, so a captured call
+// never takes the stream's work buffer (which another call may grow, and so free): each stream of
+// each capture has a buffer of its own, in use by nothing else and never freed.  Calls of one stream
+// in one capture are ordered in the graph and share it.  The captures of one GPU take at most
+// CAPTURE_FLOATS in all; past that (or without memory) a captured call takes the form of its launch
+// that needs no work space.
+constexpr int64_t CAPTURE_FLOATS = int64_t(1) << 30;   // 4 GiB of 288
+struct CaptureBuffer {
+  unsigned long long id = 0;   // the capture that the buffer belongs to
+  float* ptr = nullptr;
+  int64_t floats = 0;
+};
+std::map<std::pair<int, void*>, CaptureBuffer> g_capture;   // of each stream's latest capture
+std::map<int, int64_t> g_capture_floats;                    // taken per device
+
+// Whether `stream` is being captured, and the capture's id.
+bool capturing(void* stream, unsigned long long* id) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(static_cast<hipStream_t>(stream), &st) == hipSuccess &&
-         st == hipStreamCaptureStatusActive;
+  if (hipStreamGetCaptureInfo(static_cast<hipStream_t>(stream), &st, id) != hipSuccess) {
+    (void)hipGetLastError();   // the null stream while another is captured: not this call's error
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
+}
+
+// The buffer of capture `id` on `stream`, or null where there is none to be had.
+float* capture_buffer(void* stream, unsigned long long id, int64_t floats) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  std::lock_guard<std::mutex> lock(g_work_mu);
+  CaptureBuffer& cb = g_capture[std::make_pair(dev, stream)];
+  if (cb.id == id && cb.floats >= floats) return cb.ptr;
+  // a capture that needs more again doubles, so that its outgrown buffers add up to less than one
+  const int64_t twice = 2 * cb.floats;
+  const int64_t size = cb.id == id && twice > floats ? twice : floats;
+  int64_t& taken = g_capture_floats[dev];
+  if (size > CAPTURE_FLOATS - taken) return nullptr;
+  void* ptr = nullptr;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // allocation is no stream operation
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+  const hipError_t e = hipMalloc(&ptr, (size_t)size * sizeof(float));
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  taken += size;
+  cb.id = id;
+  cb.ptr = static_cast<float*>(ptr);
+  cb.floats = size;
+  return cb.ptr;
 }
 
 // What one launch runs: the kernel instance, the split of its stage (or pair) list and the
@@ -312,18 +351,22 @@ struct FixedWorkspace {
 };
 
 // Plan and launch.  fixed == nullptr: a split's work space comes from the per-stream work buffer
-// (allocated or grown here); otherwise only from *fixed, and a plan that needs more is refused
-// without launching anything.
+// (allocated or grown here) or, under capture, from the capture's own; otherwise only from *fixed,
+// and a plan that needs more is refused without launching anything.
 tpp_status launch(const tpp_brgemm_kernel_s* h, tpp::BrgemmParams& p, void* stream,
                   const FixedWorkspace* fixed = nullptr) {
   LaunchPlan lp;
   if (tpp_status s = plan_launch(h, p, lp)) return s;
-  if (lp.split > 1 && !fixed && grows_under_capture(WORK_SPLIT, stream, lp.ws_floats))
-    lp.split = 1;
-  p.split = lp.split;
   p.ws = nullptr;
+  unsigned long long capture = 0;
+  const bool captured = lp.split > 1 && !fixed && capturing(stream, &capture);
+  if (captured) {
+    p.ws = capture_buffer(stream, capture, lp.ws_floats);
+    if (!p.ws) lp.split = 1;
+  }
+  p.split = lp.split;
   std::unique_lock<std::mutex> work_hold;   // held from a work-buffer lookup to the launch
-  if (lp.split > 1) {
+  if (lp.split > 1 && !captured) {
     if (fixed) {
       if (lp.ws_floats > fixed->floats || !fixed->ptr)
         return fail(TPP_ERR_UNSUPPORTED,
@@ -777,14 +820,19 @@ tpp_status reduce_impl(int32_t m, int32_t n, int64_t ld, int32_t in_type, const 
   tpp::ReduceParams p{in, m, n, ld, in_type == TPP_DT_BF16, op, flags, out_x, out_x2,
                       G, in_stride, out_stride, 0};
   int64_t need = tpp::reduce_work_floats(p);
-  if (need > 0 && grows_under_capture(WORK_REDUCE, stream, need)) {
-    p.whole = 1;
-    need = tpp::reduce_work_floats(p);
+  float* work = nullptr;
+  unsigned long long capture = 0;
+  const bool captured = need > 0 && capturing(stream, &capture);
+  if (captured) {
+    work = capture_buffer(stream, capture, need);
+    if (!work) {
+      p.whole = 1;
+      need = tpp::reduce_work_floats(p);
+    }
   }
   if (need < 0) return fail(TPP_ERR_UNSUPPORTED, "reduce needs more than 2^31 - 1 workgroups");
-  float* work = nullptr;
   std::unique_lock<std::mutex> work_hold;   // held from the work-buffer lookup to the launch
-  if (need > 0) {
+  if (need > 0 && !captured) {
     const tpp_status st = work_buffer(WORK_REDUCE, stream, need, &work, work_hold);
     if (st != TPP_OK) return st;
   }

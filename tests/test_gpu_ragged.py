@@ -134,7 +134,7 @@ def test_fp32_lists_past_64_pairs(kind, count):
 
 
 def test_fp32_split_call_under_capture():
-    """A split call needs a work buffer; on a stream that has none, under capture, it runs unsplit."""
+    """A split call captured on a stream that has no work buffer yet."""
     from paper_2104_05755_amd import torch_io
     wl = grid_case(64, 64, 64, 8, "stride", "f32", 0.0, (), 1, 1, 0, 3, "f32")
     dev = torch_io.upload(wl)

@@ -1,7 +1,6 @@
 """GPU Reduce TPP, exact on integer data: every group width of the by-rows kernel (8 to 64 lanes per
 column), row tails and bases at any element, the by-columns window of the last rows and its
-shared-slot fold, both combine widths, and a call whose work buffer would have to grow under graph
-capture.  Values are integers of at most 8 in magnitude and sums stay below 2^24, so fp32 sums are
+shared-slot fold, both combine widths, and a call captured on a stream that has no work buffer.  Values are integers of at most 8 in magnitude and sums stay below 2^24, so fp32 sums are
 exact in any order and the reference is numpy's integer sum."""
 from __future__ import annotations
 
@@ -75,9 +74,8 @@ def test_batched_blocks_at_any_alignment():
 
 @pytest.mark.parametrize("by,m,n", [("cols", 64, 40000), ("rows", 60000, 5)])
 def test_capture_without_a_work_buffer(by, m, n):
-    """A shape that folds partial results needs a work buffer; on a stream that has none, under
-    capture, the call runs with one partial per output instead of allocating.  Replays see the
-    inputs of their time."""
+    """A shape that folds partial results, captured on a stream that has no work buffer.  Replays
+    see the inputs of their time."""
     import paper_2104_05755_amd as tpp
     s = torch.cuda.Stream()
     x = torch.zeros(m * n, dtype=torch.bfloat16, device="cuda")
