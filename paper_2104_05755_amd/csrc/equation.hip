@@ -485,7 +485,7 @@ __device__ __forceinline__ bool eq_walk(const EqArgs& p, int lane, int wave, EqW
   const int32_t chunk = grp * p.w + (lane - k.sub * p.w);
   k.mine = k.sub < p.q && chunk * 8 < p.m;
   const int32_t r0 = k.mine ? chunk * 8 : 0;
-  k.first = r0 + 8 > p.m ? r0 + 8 - p.m : 0;
+  k.first = p.m - r0 < 8 ? 8 - (p.m - r0) : 0;   // r0 + 8 may pass 2^31 - 1
   k.r = r0 - k.first;
   return true;
 }
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(EQ_T) void equation_vec_kernel(EqArgs p) {
        gidx += (int64_t)gridDim.x * EQ_T) {
     const int32_t c = (int32_t)(gidx / chunks);
     const int32_t r0 = (int32_t)(gidx - (int64_t)c * chunks) * EPT;
-    const int32_t first = r0 + EPT > p.m ? r0 + EPT - p.m : 0;
+    const int32_t first = p.m - r0 < EPT ? EPT - (p.m - r0) : 0;   // r0 + EPT may pass 2^31 - 1
     const int32_t r = r0 - first;
     float t0[EPT], t1[EPT], t2[EPT], t3[EPT], t4[EPT], t5[EPT], t6[EPT], t7[EPT];
 #define TPP_EQ_TMP_CASE(j, o) \
@@ -869,12 +869,12 @@ hipError_t launch_equation(const EqProgram& prog, hipStream_t stream) {
       ch.q = 64 / ch.w;
       // Columns per wavefront: enough steps to reuse its column leaves and its column values, while
       // about 16 wavefronts per CU (4096) still share the work; at most the 64 columns of its file.
-      const int64_t steps = (int64_t)ch.ng * ((use->n + ch.q - 1) / ch.q);
+      const int64_t steps = ch.ng * (((int64_t)use->n + ch.q - 1) / ch.q);
       int64_t per = steps / 4096;
       if (per < 1) per = 1;
       if (per > 64 / ch.q) per = 64 / ch.q;
       ch.cw = (int32_t)per * ch.q;
-      ch.tiles = (use->n + ch.cw - 1) / ch.cw;
+      ch.tiles = ((int64_t)use->n + ch.cw - 1) / ch.cw;
       const dim3 grid((unsigned)((ch.tiles * ch.ng + EQ_T / 64 - 1) / (EQ_T / 64)));
       const unsigned lds = (unsigned)(ch.uslots * 64 * 4 * (EQ_T / 64));
 #define TPP_EQ_CHAIN(B, N) \

@@ -127,3 +127,47 @@ def test_few_contiguous_rows(m, n):
     print(f"few rows {m}x{n}", flush=True)
     g, r, _, _ = one(nodes, len(nodes) - 1, m, n, specs, seed=m, integer=True)
     assert np.array_equal(g, r)
+
+
+TOP = 2 ** 31 - 1
+
+
+def _top_case(m, n, nodes, root, leaves, want):
+    """out = want(r, c) over an m x n bf16 output with 64 guard entries behind it."""
+    import paper_2104_05755_amd as tpp
+    total = m * n
+    out = torch.full((total + 64,), -1.0, dtype=torch.bfloat16, device="cuda")
+    print(f"equation {m} x {n}", flush=True)
+    tpp.tpp_equation_execute(nodes, root, m, n, [(x, ld, tpp.TPP_DT_BF16, bc) for x, ld, bc in leaves],
+                             out, m, tpp.TPP_DT_BF16, tpp.current_stream())
+    torch.cuda.synchronize()
+    assert bool((out[total:] == -1).all()), "stored past the output"
+    chunk = 1 << 26
+    # all of an output of one column or row, the two ends of a larger one
+    starts = range(0, total, chunk) if total <= TOP else (0, total - chunk)
+    for s in starts:
+        e = torch.arange(s, min(s + chunk, total), dtype=torch.int64, device="cuda")
+        assert bool((out[s:s + e.numel()].float() == want(e % m, e // m)).all()), s
+
+
+def test_extents_at_the_top_of_int32():
+    """Rows and columns within a chunk of 2^31: the last window and the host's tile counts do not wrap.
+    One contiguous row (run as one column by the chain kernel), one column of a tree that is no
+    chain, and 8 x (2^31 - 1) over column tiles."""
+    def pattern(n):
+        x = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+        for s in range(0, n, 1 << 26):
+            e = torch.arange(s, min(s + (1 << 26), n), dtype=torch.int64, device="cuda")
+            x[s:s + e.numel()] = ((e % 61) - 30).to(torch.bfloat16)
+        return x
+    at = lambda e: ((e % 61) - 30).float()
+    x = pattern(TOP)
+    two = torch.full((1,), 2.0, dtype=torch.bfloat16, device="cuda")
+    scaled = [("leaf", 0), ("leaf", 1), ("mul", 0, 1)]
+    _top_case(1, TOP, scaled, 2, [(x, 1, "none"), (two, 1, "scalar")], lambda r, c: 2 * at(c))
+    larger = [("leaf", 0), ("leaf", 1), ("max", 0, 1)]
+    _top_case(TOP - 2, 1, larger, 2, [(x, TOP - 2, "none"), (two, 1, "scalar")],
+              lambda r, c: at(r).clamp(min=2))
+    col = torch.arange(8, dtype=torch.float32, device="cuda").to(torch.bfloat16)
+    added = [("leaf", 0), ("leaf", 1), ("add", 0, 1)]
+    _top_case(8, TOP, added, 2, [(col, 1, "col"), (x, 1, "row")], lambda r, c: r.float() + at(c))
