@@ -133,11 +133,11 @@ __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t
   if (wid >= (int64_t)p.n * nseg) return;
   const int32_t c = (int32_t)(wid % p.n), s = (int32_t)(wid / p.n);
   const int32_t r_lo = s * seg_rows;
-  const int32_t r_hi = min(p.m, r_lo + seg_rows);
+  const int32_t rows = min(p.m - r_lo, seg_rows);   // r_lo + seg_rows may pass 2^31 - 1
   const int64_t col = (int64_t)c * p.ld;
   const bool want_x = (p.flags & TPP_RED_X) != 0, want_x2 = (p.flags & TPP_RED_X2) != 0;
   float ax = fold_identity<OP>(), ax2 = fold_identity<OP>();
-  const int32_t nv = (r_hi - r_lo) / V;   // full V-chunks
+  const int32_t nv = rows / V;   // full V-chunks
   for (int32_t j = lane; j < nv; j += 64) {
     float x[V];
     loadv<BF16, V>(p.in, col + r_lo + (int64_t)j * V, x);
@@ -147,8 +147,8 @@ __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t
       if (X2) ax2 = fold<OP>(ax2, x[e] * x[e]);
     }
   }
-  for (int32_t r = r_lo + nv * V + lane; r < r_hi; r += 64) {
-    const float x = load1<BF16>(p.in, col + r);
+  if (lane < rows - nv * V) {
+    const float x = load1<BF16>(p.in, col + r_lo + nv * V + lane);
     ax = fold<OP>(ax, x);
     if (X2) ax2 = fold<OP>(ax2, x * x);
   }
@@ -260,18 +260,19 @@ __global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t
   const int64_t lb = batch_of<BF16>(p, per, work, 2LL * nseg * p.m);
   const int32_t rb = (int32_t)(lb % nrb), s = (int32_t)(lb / nrb);
   const int32_t r0 = rb * TR * V + tr * V;
-  const int32_t c_lo = s * col_seg, c_hi = min(p.n, c_lo + col_seg);
+  // unsigned: the sums below pass 2^31 - 1 where n is near it
+  const uint32_t c_lo = (uint32_t)s * col_seg, c_hi = min((uint32_t)p.n, c_lo + col_seg);
   float ax[V], ax2[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) ax[e] = ax2[e] = fold_identity<OP>();
   // the last rows: the vector that ends with the column, of which the first `skip` rows belong to
   // the thread before
   const bool vec = p.m >= V && r0 < p.m;
-  const int32_t skip = vec && r0 + V > p.m ? r0 + V - p.m : 0;
-  const auto load_vec = [&](int32_t c, float (&x)[V]) {
+  const int32_t skip = vec && p.m - r0 < V ? V - (p.m - r0) : 0;
+  const auto load_vec = [&](uint32_t c, float (&x)[V]) {
     loadv<BF16, V>(p.in, (int64_t)c * p.ld + r0 - skip, x);
   };
-  const auto load_rows = [&](int32_t c, float (&x)[V]) {   // fewer than V rows in all
+  const auto load_rows = [&](uint32_t c, float (&x)[V]) {   // fewer than V rows in all
 #pragma unroll
     for (int e = 0; e < V; ++e)
       x[e] = r0 + e < p.m ? load1<BF16>(p.in, (int64_t)c * p.ld + r0 + e) : 0.0f;
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t
   for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int e = 0; e < V; ++e) bx[u][e] = bx2[u][e] = fold_identity<OP>();
-  int32_t c = c_lo + tc;
+  uint32_t c = c_lo + tc;
   auto trip = [&](auto count, auto&& load) {
     constexpr int U = decltype(count)::value;
     for (; c + (U - 1) * TC < c_hi; c += U * TC) {
@@ -453,8 +454,9 @@ Plan make_plan(const ReduceParams& p) {
     if (nseg > 256) nseg = 256;
     if (p.whole) nseg = 1;
     const int64_t per = (p.m + nseg - 1) / nseg;
-    pl.seg = (int32_t)(((per + rows_per_pass - 1) / rows_per_pass) * rows_per_pass);
-    pl.nseg = (int32_t)((p.m + pl.seg - 1) / pl.seg);
+    pl.seg = nseg == 1 ? p.m   // whole passes past m may not fit 32 bits
+                       : (int32_t)(((per + rows_per_pass - 1) / rows_per_pass) * rows_per_pass);
+    pl.nseg = (int32_t)(((int64_t)p.m + pl.seg - 1) / pl.seg);
     pl.blocks = ((int64_t)p.n * pl.nseg + (RT / 64) - 1) / (RT / 64);
     // whole columns: the fewest lanes (8 to 64) whose one pass covers a column, and with plenty
     // of columns 2 or 4 rounds of them per wavefront, still >= 4096 wavefronts
@@ -470,7 +472,7 @@ Plan make_plan(const ReduceParams& p) {
   } else {
     // Up to 64 row vectors per workgroup (at least four column lanes): a tall input gets more
     // row blocks rather than more column ranges, which keeps the partials per output few.
-    const int64_t vecs = (p.m + pl.v - 1) / pl.v;
+    const int64_t vecs = ((int64_t)p.m + pl.v - 1) / pl.v;
     int32_t tr = 1;
     while (tr < vecs && tr < RT / 4) tr <<= 1;
     // A tall input with enough rows for 512 row blocks of at least 8 row vectors takes fewer
@@ -489,8 +491,8 @@ Plan make_plan(const ReduceParams& p) {
     nseg = nseg < 1 ? 1 : (nseg > max_seg ? max_seg : nseg);
     if (nseg > 512) nseg = 512;
     if (p.whole) nseg = 1;
-    pl.seg = (int32_t)((p.n + nseg - 1) / nseg);
-    pl.nseg = (int32_t)((p.n + pl.seg - 1) / pl.seg);
+    pl.seg = (int32_t)(((int64_t)p.n + nseg - 1) / nseg);
+    pl.nseg = (int32_t)(((int64_t)p.n + pl.seg - 1) / pl.seg);
     pl.blocks = (int64_t)pl.nrb * pl.nseg;
   }
   return pl;
@@ -548,7 +550,7 @@ int64_t reduce_work_floats(const ReduceParams& p) {
   const Plan pl = make_plan(p);
   const int32_t n_out = pl.by_cols ? p.m : p.n;
   // every pass of the launch (first pass, combine) must fit 2^31 - 1 workgroups
-  const int64_t per = pl.blocks > (n_out + 3) / 4 ? pl.blocks : (n_out + 3) / 4;
+  const int64_t per = pl.blocks > ((int64_t)n_out + 3) / 4 ? pl.blocks : ((int64_t)n_out + 3) / 4;
   if (per > 0x7fffffff / (p.G > 0 ? p.G : 1)) return -1;
   if (pl.nseg <= 1) return 0;
   return 2LL * pl.nseg * n_out * p.G;

@@ -93,3 +93,44 @@ def test_capture_without_a_work_buffer(by, m, n):
         a = v.reshape(n, m)
         assert np.array_equal(ox.cpu().numpy(), a.sum(axis=0 if by == "cols" else 1))
         assert np.array_equal(ox2.cpu().numpy(), (a * a).sum(axis=0 if by == "cols" else 1))
+
+
+@pytest.mark.parametrize("by,m,n", [("rows", 2 ** 31 - 1, 1), ("cols", 1, 2 ** 31 - 1),
+                                    ("cols", 3, 2 ** 31 - 1), ("cols", 2 ** 31 - 1, 1)])
+@pytest.mark.parametrize("captured", [False, True])
+def test_extents_at_the_top_of_int32(by, m, n, captured):
+    """Row segments, column ranges and windows whose ends pass 2^31 - 1.  x(e) = (e mod 61) - 30: any
+    run sums to less than 2^24 in magnitude in whatever order, and every residue comes up in the
+    strided part of each thread."""
+    import paper_2104_05755_amd as tpp
+    total = m * n
+    print(f"reduce by {by} {m} x {n} captured {captured}", flush=True)
+    x = torch.empty(total, dtype=torch.bfloat16, device="cuda")
+    for s in range(0, total, 1 << 27):
+        e = torch.arange(s, min(s + (1 << 27), total), dtype=torch.int64, device="cuda")
+        x[s:s + e.numel()] = ((e % 61) - 30).to(torch.bfloat16)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    if captured:
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            ox, _ = call(x, m, n, m, tpp.TPP_RED_SUM, by, flags="x", stream=stream.cuda_stream)
+            mx, _ = call(x, m, n, m, tpp.TPP_RED_MAX, by, flags="x", stream=stream.cuda_stream)
+        g.replay()
+    else:
+        with torch.cuda.stream(stream):
+            ox, _ = call(x, m, n, m, tpp.TPP_RED_SUM, by, flags="x")
+            mx, _ = call(x, m, n, m, tpp.TPP_RED_MAX, by, flags="x")
+    torch.cuda.synchronize()
+    if (m if by == "cols" else n) <= 3:   # few outputs, each over every m-th (or every) element
+        step = m if by == "cols" else 1
+        for o in range(m if by == "cols" else n):
+            count = (total - o + step - 1) // step
+            # whole periods of 61 sum to zero (61 is prime: any step walks all residues)
+            rest = sum((o + step * i) % 61 - 30 for i in range(count - count % 61, count))
+            assert ox[o].item() == rest and mx[o].item() == 30
+    else:                                 # one column: a copy
+        for s in range(0, total, 1 << 27):
+            e = torch.arange(s, min(s + (1 << 27), total), dtype=torch.int64, device="cuda")
+            want = ((e % 61) - 30).float()
+            assert torch.equal(ox[s:s + e.numel()], want) and torch.equal(mx[s:s + e.numel()], want)
