@@ -530,17 +530,18 @@ void launch_op(const ReduceParams& p, const Plan& pl, float* work, hipStream_t s
   }
   if (pl.nseg > 1) {
     const int32_t n_out = pl.by_cols ? p.m : p.n;
-    // 16 outputs per workgroup read whole 64-byte runs; few outputs take more threads each
-    const bool few = n_out < 512;
-    const int64_t per = few ? (n_out + 3) / 4 : (n_out + 15) / 16;
-    if (few)
-      hipLaunchKernelGGL((reduce_combine_kernel<OP, 4>), dim3((unsigned)(per * p.G)), dim3(RT), 0,
-                         stream, work, n_out, pl.nseg, p.flags, p.out_x, p.out_x2, per,
-                         p.out_stride);
-    else
-      hipLaunchKernelGGL((reduce_combine_kernel<OP, 16>), dim3((unsigned)(per * p.G)), dim3(RT), 0,
-                         stream, work, n_out, pl.nseg, p.flags, p.out_x, p.out_x2, per,
-                         p.out_stride);
+    // 16 outputs per workgroup read whole 64-byte runs; few outputs take more threads each, and
+    // outputs whose workgroups would pass a grid's 2^32 threads (2^28 in all) fewer
+    const int64_t per16 = ((int64_t)n_out + 15) / 16;
+    const int ow = n_out < 512 ? 4 : per16 * p.G * RT < (1LL << 32) ? 16 : 64;
+    const int64_t per = ((int64_t)n_out + ow - 1) / ow;
+#define TPP_RED_COMBINE(OW)                                                                     \
+  hipLaunchKernelGGL((reduce_combine_kernel<OP, OW>), dim3((unsigned)(per * p.G)), dim3(RT), 0, \
+                     stream, work, n_out, pl.nseg, p.flags, p.out_x, p.out_x2, per, p.out_stride)
+    if (ow == 4) TPP_RED_COMBINE(4);
+    else if (ow == 16) TPP_RED_COMBINE(16);
+    else TPP_RED_COMBINE(64);
+#undef TPP_RED_COMBINE
   }
 }
 
