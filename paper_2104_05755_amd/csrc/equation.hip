@@ -548,6 +548,10 @@ __global__ __launch_bounds__(EQ_T) void equation_chain_kernel(EqArgs p) {
                  k.cn);
   file[(p.uslots - 2) * 64 + lane] = 1.0f;
   file[(p.uslots - 1) * 64 + lane] = -0.0f;
+  // the columns below are read by other lanes of the wavefront than wrote them
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
   for (int32_t cs = 0; cs < k.cn; cs += p.q) {   // uniform; ci = cs + sub
     const bool ok_next = k.mine && ci + p.q < k.cn;
