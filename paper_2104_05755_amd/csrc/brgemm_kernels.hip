@@ -24,6 +24,7 @@
 
 #include <cstdio>
 #include <string>
+#include <type_traits>
 
 #include "brgemm_device.h"
 #include "internal.h"
@@ -444,7 +445,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
   const TileCoord tc = decode_tile(p, BM, BN);
   const Instance in = instance_of(p, tc.g);
   const int32_t ksteps = (p.k + BK - 1) / BK;
-  const int32_t stages = (int32_t)(in.npairs * ksteps);
+  // The host bounds the stages of stride and offset kind by 2^31; a pointer list may be longer.
+  using StageCount = std::conditional_t<KIND == TPP_BR_ADDRESS, int64_t, int32_t>;
+  const StageCount stages = (StageCount)(in.npairs * ksteps);
 
   // Staging assignments, fixed for the whole reduction.  Out-of-range rows / columns keep
   // offset 0 (an in-range address) and a false flag.
@@ -494,9 +497,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
   Staged st0;
   Staged st1;
 
-  auto load_stage = [&](int32_t s, Staged& r) {
-    const int32_t i = s / ksteps;
-    const int32_t kk = (s - i * ksteps) * BK;
+  // Stages are loaded in order; pointer lists keep the pair and k offset of the next one.
+  int64_t next_i = 0;
+  int32_t next_kk = 0;
+  auto load_stage = [&](StageCount s, Staged& r) {
+    int64_t i;
+    int32_t kk;
+    if constexpr (KIND == TPP_BR_ADDRESS) {
+      i = next_i;
+      kk = next_kk;
+      next_kk += BK;
+      if (next_kk >= p.k) {
+        next_kk = 0;
+        ++next_i;
+      }
+    } else {
+      i = s / ksteps;
+      kk = (s - (int32_t)i * ksteps) * BK;
+    }
     const uint16_t* pa;
     const uint16_t* pb;
     pair_bases_k<KIND, uint16_t>(p, in, i, pa, pb);
@@ -597,7 +615,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
     store_a(0, st0);
     store_b(0, st0);
     __syncthreads();
-    int32_t s = 0;
+    StageCount s = 0;
     // One stage; PAR = s & 1 is a compile-time constant so the register sets are never indexed
     // at run time.
     auto step = [&](auto par) {

@@ -429,3 +429,22 @@ def test_noalloc_refuses_before_device_work(tpp, monkeypatch):
                                                None, None, None, None, None, 0)
     assert e.value.status == tpp.TPP_ERR_UNSUPPORTED
     assert "scratch" in tpp.tpp_last_error_message()
+
+
+def test_pointer_lists_past_2_pow_31_stages_run_whole(tpp, monkeypatch, capfd):
+    """The chunks of a split fp32 launch count stages in 32 bits: a list of 2^31 stages runs whole,
+    one of 2^31 - 1 is split.  Where there is no GPU a split ends at the work buffer and a whole call
+    at the launch, whose choice TPP_LOG prints."""
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are stand-ins: never launched on a GPU")
+    fake = ctypes.create_string_buffer(64)
+    at = ctypes.addressof(fake)
+    h = tpp.tpp_brgemm_dispatch(tpp.make_desc(64, 64, 64, 64, 64, 64, "f32", "f32", 0.0, "address",
+                                              0, 0, []))
+    monkeypatch.setenv("TPP_LOG", "1")
+    for count, whole in ((2 ** 31 - 1, False), (2 ** 31, True)):
+        with pytest.raises(tpp.TppError) as e:
+            tpp.tpp_brgemm_execute_address(h, at, at, at, None, count)
+        assert e.value.status == tpp.TPP_ERR_HIP
+        assert ("split=1 ->" in capfd.readouterr().err) == whole
