@@ -1334,8 +1334,10 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
 }
 
 bool f32_vec(const BrgemmParams& p) {
-  const int64_t vm = (p.m + 3) / 4 * 4;
-  return p.m >= 4 && p.k >= 4 && vm * (p.fused ? p.gm : 1) < (1LL << 31) - 512;
+  // padded rows that still count in 32 bits, and 512 threads per tile that HIP accepts as a grid
+  const int64_t rows = ((int64_t)p.m + 3) / 4 * 4 * (p.fused ? p.gm : 1);
+  const int64_t tiles = p.groups * ((rows + F_BM - 1) / F_BM) * (((int64_t)p.vcols + F_BN - 1) / F_BN);
+  return p.m >= 4 && p.k >= 4 && rows < (1LL << 31) - 512 && tiles * F_NT < (1LL << 32);
 }
 
 int64_t f32_split_ws_floats(int32_t split, int64_t total_tiles) {

@@ -112,7 +112,7 @@ enum KernelId : int32_t {
 const char* kernel_name(int32_t id);
 int kernel_tile_m(int32_t id);   // tile rows of kernel instance id
 constexpr int F32_STAGE_K = 64;   // k of one stage of the fp32 kernel
-// Whether the fp32 launch p takes the 16-byte-load kernel (m, k, fused, gm filled).
+// Whether the fp32 launch p takes the 16-byte-load kernel (m, k, fused, gm, groups, vcols filled).
 bool f32_vec(const BrgemmParams& p);
 // fp32 workspace floats a split launch of the fp32 kernel needs (split x tiles x 64 x 64).
 int64_t f32_split_ws_floats(int32_t split, int64_t total_tiles);

@@ -298,7 +298,7 @@ tpp_status plan_launch(const tpp_brgemm_kernel_s* h, tpp::BrgemmParams& p, Launc
                           id == tpp::K_BF16_64x64;
   p.ragged = reg_staged && (p.m % 8 != 0 || p.k % 8 != 0);
   p.vm = p.ragged ? (int32_t)tpp::padded_rows(p.m)
-         : id == tpp::K_F32_GENERIC && tpp::f32_vec(p) ? (p.m + 3) / 4 * 4 : p.m;
+         : id == tpp::K_F32_GENERIC && tpp::f32_vec(p) ? (int32_t)(((int64_t)p.m + 3) / 4 * 4) : p.m;
   p.vrows = p.fused ? (int32_t)(p.gm * p.vm) : p.vm;
   const int bm = tpp::kernel_tile_m(id), bn = tpp::kernel_tile_n(id);
   // pairs of every instance, where the host knows them (a list of lists is on the device)

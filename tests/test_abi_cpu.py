@@ -448,3 +448,15 @@ def test_pointer_lists_past_2_pow_31_stages_run_whole(tpp, monkeypatch, capfd):
             tpp.tpp_brgemm_execute_address(h, at, at, at, None, count)
         assert e.value.status == tpp.TPP_ERR_HIP
         assert ("split=1 ->" in capfd.readouterr().err) == whole
+
+
+@pytest.mark.parametrize("m,G,vec", [(8, 2 ** 23 - 1, True), (8, 2 ** 23, False), (8, 2 ** 24 - 1, False),
+                                     (2 ** 31 - 1, 1, False), (2 ** 29 - 64, 1, True)])
+def test_fp32_launches_at_the_limits_of_a_grid(tpp, m, G, vec):
+    """The fp32 16-byte-load kernel has 512 threads per tile and padded rows: launches whose threads
+    would pass a grid's 2^32, or whose rows 2^31, take the element kernel."""
+    h = tpp.tpp_brgemm_dispatch(tpp.make_desc(m, 8, 8, m, 8, m, "f32", "f32", 0.0, "stride", 0, 0, []))
+    fake = 4096
+    name = tpp.tpp_brgemm_describe_launch(h, None, G, fake, fake, fake, None, fake, fake, fake, None, 1,
+                                          None, None, None, None, None)
+    assert ("brgemm_f32_kernel<true>" in name) == vec, name

@@ -152,3 +152,26 @@ def test_fp32_split_call_under_capture():
         g.replay()
         torch.cuda.synchronize()
         assert_bits_equal(torch_io.to_host(dev["c"], wl.arrays["c"]), ref, "replay")
+
+
+def test_fp32_instances_past_2_pow_23():
+    """More instances than 512 threads each fit a grid (the element kernel takes them)."""
+    import paper_2104_05755_amd as tpp
+    G, e, blocks = 2 ** 23 + 5, 16, 61
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    a, b = (torch.randint(-4, 5, (blocks, e), generator=g, device="cuda").float() for _ in range(2))
+    c = torch.full((G * e,), float("nan"), device="cuda")
+    i = torch.arange(G, dtype=torch.int64, device="cuda")
+    h = tpp.tpp_brgemm_dispatch(tpp.make_desc(4, 4, 4, 4, 4, 4, "f32", "f32", 0.0, "stride", 0, 0, []))
+    a_off, b_off, c_off = i % blocks * e, i % (blocks - 1) * e, i * e
+    print(f"fp32 4x4x4 x {G}", flush=True)
+    tpp.tpp_brgemm_execute_batched(h, None, G, a_off, b_off, c_off, None, a, b, c, None, 1, None, None,
+                                   None, None, None, tpp.current_stream())
+    torch.cuda.synchronize()
+    # blocks are column-major: a[k][row], b[col][k], c[col][row]; elementwise products, exact
+    at, bt = a.view(blocks, 1, 4, 4), b.view(blocks, 4, 4, 1)
+    for s in range(0, G, 1 << 20):
+        j = i[s:s + (1 << 20)]
+        want = (at[j % blocks] * bt[j % (blocks - 1)]).sum(dim=2)
+        assert torch.equal(c[s * e:(s + j.numel()) * e].view(-1, 4, 4), want)
