@@ -227,11 +227,13 @@ struct CaptureBuffer {
 std::map<std::pair<int, void*>, CaptureBuffer> g_capture;   // of each stream's latest capture
 std::map<int, int64_t> g_capture_floats;                    // taken per device
 
-// Whether `stream` is being captured, and the capture's id.
+// Whether `stream` is being captured, and the capture's id.  The null stream never is, and is not
+// asked: the answer would be an error while another stream is captured.
 bool capturing(void* stream, unsigned long long* id) {
+  if (!stream) return false;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamGetCaptureInfo(static_cast<hipStream_t>(stream), &st, id) != hipSuccess) {
-    (void)hipGetLastError();   // the null stream while another is captured: not this call's error
+    (void)hipGetLastError();
     return false;
   }
   return st == hipStreamCaptureStatusActive;
