@@ -700,10 +700,12 @@ struct F32Work {
   int32_t split, chunk;
   TileCoord tc;
   Instance in;
-  int64_t s_lo, stages;   // first stage and how many (stage = pair * ksteps + k-step)
-  int64_t i0;             // pair of the first stage
+  int64_t s_lo, steps;    // first step and how many (step = pair * ksteps + k-step)
+  int64_t i0;             // pair of the first step
   int32_t ksteps;
 };
+// PER steps of the list make a stage, of 64 k in all.
+template <int PER>
 __device__ __forceinline__ F32Work f32_work(const BrgemmParams& p) {
   F32Work w;
   w.split = p.split > 1 ? p.split : 1;
@@ -711,13 +713,14 @@ __device__ __forceinline__ F32Work f32_work(const BrgemmParams& p) {
   w.chunk = (int32_t)((int64_t)blockIdx.x - w.tile_bid * w.split);
   w.tc = decode_tile_at(p, F_BM, F_BN, w.tile_bid);
   w.in = instance_of(p, w.tc.g);
-  w.ksteps = (p.k + F_BK - 1) / F_BK;
+  w.ksteps = (p.k + F_BK / PER - 1) / (F_BK / PER);
   w.s_lo = 0;
   w.i0 = 0;
-  w.stages = w.in.npairs * w.ksteps;
-  if (p.split > 1) {
-    w.s_lo = (int64_t)w.chunk * p.split_base + min(w.chunk, p.split_rem);
-    w.stages = p.split_base + (w.chunk < p.split_rem ? 1 : 0);
+  w.steps = w.in.npairs * w.ksteps;
+  if (p.split > 1) {   // whole stages per chunk, of which the very last may lack a step
+    w.s_lo = PER * ((int64_t)w.chunk * p.split_base + min(w.chunk, p.split_rem));
+    const int64_t n = PER * ((int64_t)p.split_base + (w.chunk < p.split_rem ? 1 : 0));
+    w.steps = PER == 1 || w.steps - w.s_lo > n ? n : w.steps - w.s_lo;
     w.i0 = fdiv((uint32_t)w.s_lo, p.div_ks);
   }
   return w;
@@ -823,33 +826,38 @@ __device__ __forceinline__ void f32_store4(const BrgemmParams& p, const F32Work&
   }
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(NT) void brgemm_f32_kernel(BrgemmParams p);
-
-template <>
-__global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams p) {
+// PAIRED: a stage is two steps of 32 k, one for each group of waves, from one pair's blocks or from
+// two pairs'; else one step of 64 k, half of it for each.
+// LISTS: offset and pointer lists too, else stride kind alone (without the lists' code, of which every
+// load of the unrolled loop has a copy).
+template <bool PAIRED, bool LISTS>
+__device__ __forceinline__ void f32_vec_body(const BrgemmParams& p) {
+  constexpr int PER = PAIRED ? 2 : 1, STEP = F_BK / PER;
+  constexpr int BQ = STEP / 4;   // 4-k vectors of a column of B in a step
   __shared__ __attribute__((aligned(16))) float As[2][F_BK * F_BM];     // [k][row]
   __shared__ __attribute__((aligned(16))) float Bs[2][F_BN * F_BROW];   // [column][k]
   const int t = threadIdx.x, lane = t & 63;
   const int wave = (t >> 6) & 3, kgrp = t >> 8;   // wave of its group; the group's half of a stage
   const int wm = wave & 1, wn = wave >> 1;
-  const F32Work w = f32_work(p);
-  const int64_t stages = w.stages;
+  const F32Work w = f32_work<PER>(p);
+  const int64_t stages = (w.steps + PER - 1) / PER;
   const F32Rows rows = f32_rows(p, w, t & 15);
 
-  // Thread t moves A vectors q = t + 512 j (j < 2): k-column q / 16, rows 4 (q % 16) .. +3; and B
-  // vectors q = t + 512 j: column q / 16, k 4 (q % 16) .. +3.  Byte offsets from a stage's bases, in
-  // whole stages and in a block's last, partial one (_t).  Rows and columns outside C read the
-  // first ones: only outputs that are not stored see them.
-  const bool ragged = p.k % F_BK != 0 || p.vm != p.m;   // uniform
-  const int32_t ktail = p.k - (w.ksteps - 1) * F_BK;     // k of the last k-step
+  // Thread t moves two vectors of A and two of B per stage: those of a 64-k step with q = t + 512 j
+  // (j < 2), or that of step j with q = t.  A: k-column q / 16 of the step, rows 4 (q % 16) .. +3;
+  // B: column q / BQ, k 4 (q % BQ) .. +3.  Byte offsets from a step's bases, in whole steps and in a
+  // block's last, partial one (_t).  Rows and columns outside C read the first ones: only outputs
+  // that are not stored see them.
+  const bool ragged_rows = p.vm != p.m, ragged_k = p.k % 4 != 0;
+  const bool ragged = p.k % STEP != 0 || ragged_rows;
+  const int32_t ktail = p.k - (w.ksteps - 1) * STEP;     // k of the last k-step
   int64_t oa[2], ob[2], oa_t[2], ob_t[2];
-  int32_t sr[2], sk[2];       // shifts: rows of A, k of B in the partial stage
-  bool ka_ok[2];              // A's k-column exists in the partial stage
+  int32_t sr[2], sk[2];       // shifts: rows of A, k of B in the partial step
+  bool ka_ok[2];              // A's k-column exists in the partial step
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int q = t + F_NT * j;
-    const int ka = q >> 4, kb = (q & 15) * 4;
+    const int q = PAIRED ? t : t + F_NT * j;
+    const int ka = q >> 4, kb = (q % BQ) * 4;
     const int32_t R = w.tc.row0 + (q & 15) * 4;
     const int32_t gi = p.fused ? fdiv(R, p.div_m) : 0;
     int32_t r = R - gi * p.vm;
@@ -864,7 +872,7 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
     oa[j] = (base + (int64_t)ka * p.lda) * 4;
     oa_t[j] = (base + (int64_t)(ka_ok[j] ? ka : 0) * p.lda) * 4;
     int64_t col = 0;
-    if (!col_in_b(p, w.tc.col0 + (q >> 4), col)) col = 0;
+    if (!col_in_b(p, w.tc.col0 + q / BQ, col)) col = 0;
     // the window of 4 k ends with the block (k >= 4, so it may begin in the k-step before)
     const int32_t kw = kb + 4 > ktail ? ktail - 4 : kb;
     sk[j] = kb - kw;
@@ -872,12 +880,15 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
     ob_t[j] = (col + kw) * 4;
   }
 
-  // Stages are loaded strictly in order by a cursor: pair i (bases pa, pb), k offset kk.  Offset
+  // Steps are loaded strictly in order by a cursor: pair i (bases pa, pb), k offset kk.  Offset
   // and pointer lists: lane l holds the entries of pair 64 (i / 64) + l, taken with readlane.
   int64_t ld_s = 0, ld_i = w.i0;
-  int32_t ld_kk = (int32_t)(w.s_lo - ld_i * w.ksteps) * F_BK;
+  int32_t ld_kk = (int32_t)(w.s_lo - ld_i * w.ksteps) * STEP;
   const char* pa = nullptr;
   const char* pb = nullptr;
+  // read here: a first read between two steps' loads would hold the second step's back by its latency
+  int64_t step_a = p.stride_a * 4, step_b = p.stride_b * 4;
+  if (PAIRED) asm volatile("" : "+s"(step_a), "+s"(step_b));
   uint64_t list_a = 0, list_b = 0;
   const auto uni = [](uint64_t v, int src) {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), src) << 32) |
@@ -897,52 +908,65 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
     pa = reinterpret_cast<const char*>(uni(list_a, (int)(ld_i & 63)));
     pb = reinterpret_cast<const char*>(uni(list_b, (int)(ld_i & 63)));
   };
-  if (stages > 0) {
+  if (!LISTS) {
+    pa = static_cast<const char*>(p.a) + w.in.a * 4 + ld_i * step_a;
+    pb = static_cast<const char*>(p.b) + w.in.b * 4 + ld_i * step_b;
+  } else if (stages > 0) {
     fill_list();
     from_list();
   }
   f32x4 ra[F_RING][2], rb[F_RING][2];
-  bool part[F_RING];          // the set holds a block's partial stage
-  auto load = [&](auto slot) {
-    constexpr int R = decltype(slot)::value;
-    const bool tail = ragged && ld_kk + F_BK > p.k;
-    part[R] = tail;
+  bool part[F_RING][PER];     // the step is a block's partial one
+  bool lone[F_RING];          // PAIRED: the second step is past the list
+  auto load_step = [&](auto slot, auto which) {
+    constexpr int R = decltype(slot)::value, J = decltype(which)::value;
+    const bool tail = ragged && ld_kk + STEP > p.k;
+    part[R][J] = tail;
     const char* const a = pa + (int64_t)ld_kk * p.lda * 4;
     const char* const b = pb + (int64_t)ld_kk * 4;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = PAIRED ? J : 0; j < (PAIRED ? J + 1 : 2); ++j) {
       ra[R][j] = gld<f32x4_a4>(a + (tail ? oa_t[j] : oa[j]));
       rb[R][j] = gld<f32x4_a4>(b + (tail ? ob_t[j] : ob[j]));
     }
-    if (++ld_s >= stages) return;   // stay on the last stage
-    ld_kk += F_BK;
+    if (++ld_s >= w.steps) return;   // stay on the last step
+    ld_kk += STEP;
     if (ld_kk >= p.k) {
       ld_kk = 0;
       ++ld_i;
-      if (p.kind == TPP_BR_STRIDE) {
-        pa += p.stride_a * 4;
-        pb += p.stride_b * 4;
+      if (!LISTS || p.kind == TPP_BR_STRIDE) {
+        pa += step_a;
+        pb += step_b;
       } else {
         if ((ld_i & 63) == 0) fill_list();
         from_list();
       }
     }
   };
+  auto load = [&](auto slot) {
+    lone[decltype(slot)::value] = ld_s + 1 >= w.steps;
+    load_step(slot, IntC<0>());
+    if constexpr (PAIRED) load_step(slot, IntC<1>());
+  };
   auto store = [&](int buf, auto slot) {
     constexpr int R = decltype(slot)::value;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int q = t + F_NT * j;
+      const int q = PAIRED ? t : t + F_NT * j;
+      const int k0 = PAIRED ? STEP * j : 0;   // the step's place in the stage
       f32x4 a = ra[R][j], b = rb[R][j];
-      if (ragged) {
-        a = shift_down(a, sr[j]);
-        if (part[R]) {
-          if (!ka_ok[j]) a = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
-          b = shift_down(b, sk[j]);
+      const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (ragged) {   // uniform, as the next three conditions but ka_ok and sk
+        if (ragged_rows) a = shift_down(a, sr[j]);
+        if (part[R][PAIRED ? j : 0]) {
+          if (!ka_ok[j]) a = zero;
+          if (ragged_k) b = shift_down(b, sk[j]);
+          else if (sk[j] != 0) b = zero;   // whole windows: 4 k and more past the end
         }
       }
-      *reinterpret_cast<f32x4*>(&As[buf][(q >> 4) * F_BM + (q & 15) * 4]) = a;
-      *reinterpret_cast<f32x4*>(&Bs[buf][(q >> 4) * F_BROW + (q & 15) * 4]) = b;
+      if (PAIRED && j == 1 && lone[R]) a = b = zero;
+      *reinterpret_cast<f32x4*>(&As[buf][(k0 + (q >> 4)) * F_BM + (q & 15) * 4]) = a;
+      *reinterpret_cast<f32x4*>(&Bs[buf][q / BQ * F_BROW + k0 + (q % BQ) * 4]) = b;
     }
   };
 
@@ -970,6 +994,8 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[e], f.b[e], acc, 0, 0, 0);
   };
 
+  // groups of 8 k that a step has: fewer than four in blocks of at most 24 k
+  const int32_t eights = p.k < STEP ? (p.k + 7) / 8 : 4;
   if (stages > 0) {
     load(IntC<0>());
     load(IntC<1>());
@@ -991,11 +1017,13 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
       load(IntC<NS>());
       __builtin_amdgcn_sched_barrier(0);
       mfmas(f1);
-      f1 = frag(BUF, 3);
-      __builtin_amdgcn_sched_barrier(0);
-      mfmas(f0);
-      __builtin_amdgcn_sched_barrier(0);
-      mfmas(f1);
+      if (!PAIRED || eights > 2) {   // uniform
+        f1 = frag(BUF, 3);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!PAIRED || eights > 3) mfmas(f1);
+      }
       lds_barrier();   // LDS traffic only: the ring's global loads stay in flight
     };
     // whole turns of the ring without a branch between the steps (a way out of the loop after each
@@ -1047,6 +1075,30 @@ __global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams 
   }
 }
 
+template <bool VEC>
+__global__ __launch_bounds__(NT) void brgemm_f32_kernel(BrgemmParams p);
+
+template <>
+__global__ __launch_bounds__(F_NT, 4) void brgemm_f32_kernel<true>(BrgemmParams p) {
+  f32_vec_body<false, true>(p);
+}
+
+// Blocks of an odd number of 32-k steps (k of at most 32 above all, the inner blocks of blocked
+// layouts), where stages of 64 k of one pair would spend half of a pair's last stage on zeros.  64 x
+// 64 blocks on 512 tiles: 32 pairs of k = 32 91.3 us in 64-k stages, 46.2 here; 128 pairs of k = 8
+// 340 and 124; pointer lists of 16 pairs of k = 32 51.0 and 30.8.  Blocks of 64 k lose 1.4 % by it (a
+// second cursor step per stage; 45.3 and 45.9 us for a 2048 x 1024 x 1024 layer), so an even number
+// of steps keeps 64-k stages.  Stride kind has an instance without the code of the lists: one stage on
+// each of 8 workgroups takes 5.9 us with it and 7.7 without.  VEC as for brgemm_f32_kernel (true).
+template <bool VEC>
+__global__ __launch_bounds__(F_NT, 4) void brgemm_f32_paired_kernel(BrgemmParams p) {
+  f32_vec_body<true, true>(p);
+}
+template <bool VEC>
+__global__ __launch_bounds__(F_NT, 4) void brgemm_f32_paired_stride_kernel(BrgemmParams p) {
+  f32_vec_body<true, false>(p);
+}
+
 // m or k below 4: half a stage of element loads at a time, every row, column and k checked.
 template <>
 __global__ __launch_bounds__(NT) void brgemm_f32_kernel<false>(BrgemmParams p) {
@@ -1055,7 +1107,7 @@ __global__ __launch_bounds__(NT) void brgemm_f32_kernel<false>(BrgemmParams p) {
   __shared__ __attribute__((aligned(16))) float Bs[HK * ROW];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave & 1, wn = wave >> 1;
-  const F32Work w = f32_work(p);
+  const F32Work w = f32_work<1>(p);
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
@@ -1063,7 +1115,7 @@ __global__ __launch_bounds__(NT) void brgemm_f32_kernel<false>(BrgemmParams p) {
   const int rc = t & 63, k0 = t >> 6;
   int64_t a_off = 0, b_off = 0;
   const bool a_ok = row_in_a(p, w.tc.row0 + rc, a_off), b_ok = col_in_b(p, w.tc.col0 + rc, b_off);
-  for (int64_t h = 2 * w.s_lo; h < 2 * (w.s_lo + w.stages); ++h) {
+  for (int64_t h = 2 * w.s_lo; h < 2 * (w.s_lo + w.steps); ++h) {
     const int64_t i = (h / 2) / w.ksteps;
     const int32_t kk = (int32_t)(h / 2 - i * w.ksteps) * F_BK + (int32_t)(h & 1) * HK;
     if (kk >= p.k) continue;   // uniform
@@ -1254,7 +1306,8 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
   {
     const int32_t band = p.tiles_m < 8 ? p.tiles_m : 8;
     const int32_t last = p.tiles_m % 8 ? p.tiles_m % 8 : 8;
-    const int32_t kstep = id == K_F32_GENERIC ? F_BK : kInfo[id].kstep > 1 ? kInfo[id].kstep : BK;
+    const int32_t kstep = id == K_F32_GENERIC ? (f32_paired(p) ? F_BK / 2 : F_BK)
+                          : kInfo[id].kstep > 1 ? kInfo[id].kstep : BK;
     p.div_m = FastDiv(p.vm);
     p.div_n = FastDiv(p.n);
     p.div_gm = FastDiv(p.gm > 0 && p.gm < (1LL << 31) ? p.gm : 1);
@@ -1266,7 +1319,8 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
     p.div_split = FastDiv(p.split > 1 ? p.split : 1);
     p.div_ks = FastDiv((p.k + kstep - 1) / kstep);
     if (p.split > 1) {   // stride and offset kinds, and single lists: `count` pairs everywhere
-      const int64_t stages = p.count * ((p.k + kstep - 1) / kstep);
+      const int64_t stages = id == K_F32_GENERIC ? f32_stages(p, p.count)
+                                                 : p.count * ((p.k + kstep - 1) / kstep);
       p.split_base = (int32_t)(stages / p.split);
       p.split_rem = (int32_t)(stages % p.split);
     }
@@ -1313,14 +1367,21 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
       break;
     default: {
       // windows of four rows and four k inside every block (plan_launch pads p.vm to match)
-      const bool vec = f32_vec(p);
+      const bool vec = f32_vec(p), paired = f32_paired(p);
       if (name_out) {
-        *name_out = vec ? "brgemm_f32_kernel<true>" : "brgemm_f32_kernel<false>";
+        *name_out = paired ? (p.kind == TPP_BR_STRIDE ? "brgemm_f32_paired_stride_kernel<true>"
+                                                      : "brgemm_f32_paired_kernel<true>")
+                    : vec  ? "brgemm_f32_kernel<true>"
+                           : "brgemm_f32_kernel<false>";
         if (p.split > 1) *name_out += " + brgemm_f32_split_finish";
         return hipSuccess;
       }
       const dim3 g = p.split > 1 ? dim3((unsigned)(p.total_tiles * p.split)) : grid;
-      if (vec)
+      if (paired && p.kind == TPP_BR_STRIDE)
+        hipLaunchKernelGGL(brgemm_f32_paired_stride_kernel<true>, g, dim3(F_NT), 0, stream, p);
+      else if (paired)
+        hipLaunchKernelGGL(brgemm_f32_paired_kernel<true>, g, dim3(F_NT), 0, stream, p);
+      else if (vec)
         hipLaunchKernelGGL(brgemm_f32_kernel<true>, g, dim3(F_NT), 0, stream, p);
       else
         hipLaunchKernelGGL(brgemm_f32_kernel<false>, g, block, 0, stream, p);
@@ -1338,6 +1399,13 @@ bool f32_vec(const BrgemmParams& p) {
   const int64_t rows = ((int64_t)p.m + 3) / 4 * 4 * (p.fused ? p.gm : 1);
   const int64_t tiles = p.groups * ((rows + F_BM - 1) / F_BM) * (((int64_t)p.vcols + F_BN - 1) / F_BN);
   return p.m >= 4 && p.k >= 4 && rows < (1LL << 31) - 512 && tiles * F_NT < (1LL << 32);
+}
+
+bool f32_paired(const BrgemmParams& p) { return f32_vec(p) && (p.k + 31) / 32 % 2 != 0; }
+
+int64_t f32_stages(const BrgemmParams& p, int64_t pairs) {
+  return f32_paired(p) ? (pairs * ((p.k + 31) / 32) + 1) / 2
+                       : pairs * (((int64_t)p.k + F_BK - 1) / F_BK);
 }
 
 int64_t f32_split_ws_floats(int32_t split, int64_t total_tiles) {

@@ -111,9 +111,13 @@ enum KernelId : int32_t {
 
 const char* kernel_name(int32_t id);
 int kernel_tile_m(int32_t id);   // tile rows of kernel instance id
-constexpr int F32_STAGE_K = 64;   // k of one stage of the fp32 kernel
+constexpr int F32_STAGE_K = 64;   // k of one stage of the fp32 kernels
 // Whether the fp32 launch p takes the 16-byte-load kernel (m, k, fused, gm, groups, vcols filled).
 bool f32_vec(const BrgemmParams& p);
+// Whether it takes the instance whose stages are two 32-k steps of the pair list, of one pair or of
+// two, and the stages of `pairs` pairs.
+bool f32_paired(const BrgemmParams& p);
+int64_t f32_stages(const BrgemmParams& p, int64_t pairs);
 // fp32 workspace floats a split launch of the fp32 kernel needs (split x tiles x 64 x 64).
 int64_t f32_split_ws_floats(int32_t split, int64_t total_tiles);
 int kernel_tile_n(int32_t id);   // tile columns

@@ -310,9 +310,9 @@ tpp_status plan_launch(const tpp_brgemm_kernel_s* h, tpp::BrgemmParams& p, Launc
     // whole stage list: split the list into chunks reduced by separate workgroups (about 256 in
     // all) and sum the chunks in a finishing kernel.
     const int64_t tiles = p.groups * ((p.vrows + 63) / 64) * ((p.vcols + 63) / 64);
-    const int64_t stages = pairs * ((h->desc.k + tpp::F32_STAGE_K - 1) / tpp::F32_STAGE_K);
-    // (a split's chunks are counted in 32 bits; a longer pointer list runs whole)
-    if (tiles < 128 && stages >= 4 && stages < (1LL << 31)) {
+    const int64_t stages = tpp::f32_stages(p, pairs);
+    // (a split's chunks and steps are counted in 32 bits; a longer pointer list runs whole)
+    if (tiles < 128 && stages >= 4 && stages < (1LL << 30)) {
       int64_t split = 256 / tiles;
       if (const char* env = std::getenv("TPP_SPLIT")) split = std::atoi(env);   // override
       if (split > stages) split = stages;

@@ -122,6 +122,24 @@ def test_fp32_grid_bit_exact(m, n, k, split, monkeypatch):
         assert_bits_equal(got["c"], run_oracle(wl)[0], f"{names[0]} {m}x{n}x{k}")
 
 
+@pytest.mark.parametrize("k", [4, 8, 9, 16, 17, 24, 31, 32, 36, 64, 65, 96, 100])
+@pytest.mark.parametrize("kind", ["stride", "offset", "address"])
+def test_fp32_steps_of_two_pairs_in_a_stage(kind, k):
+    """An odd number of 32-k steps per block: a stage may hold the last step of one pair and the first
+    of the next, and the last stage a single step; one to four groups of 8 k per step."""
+    for count in (1, 2, 3, 8, 67):
+        for split in (None, "3"):
+            wl = wk.small_case(np.random.default_rng(k + count), 68, 70, k, count, kind, "f32", "f32", 0.0,
+                               {"bias"}, pad=1 if count == 3 else 0, integer=True)
+            print(f"fp32 {kind} k {k} count {count} split {split}", flush=True)
+            with pytest.MonkeyPatch.context() as mp:
+                if split:
+                    mp.setenv("TPP_SPLIT", split)
+                got, names = run_gpu(wl)
+            assert ("paired" in names[0]) == ((k + 31) // 32 % 2 == 1), names
+            assert_bits_equal(got["c"], run_oracle(wl)[0], f"{names[0]} {kind} {k} x {count}")
+
+
 @pytest.mark.parametrize("count", [1, 5, 64, 65, 130])
 @pytest.mark.parametrize("kind", ["offset", "address"])
 def test_fp32_lists_past_64_pairs(kind, count):
