@@ -63,6 +63,21 @@ def test_ragged_grid_bit_exact(m, n, k, kid, monkeypatch):
         assert_bits_equal(got["c"], run_oracle(wl)[0], f"{names[0]} {m}x{n}x{k}")
 
 
+@pytest.mark.parametrize("kid", [None, 0, 1, 2])
+@pytest.mark.parametrize("k", [8, 24, 40, 56, 72, 120, 136, 9, 31, 73])
+def test_partial_stages_of_k_bit_exact(k, kid, monkeypatch):
+    """Every block ends with a partial stage (most have no other): the operands are masked on their way
+    to LDS, one or two stages after their loads."""
+    if kid is not None:
+        monkeypatch.setenv("TPP_FORCE_KERNEL", str(kid))
+    for m, count in ((64, 1), (72, 2), (60, 5)):
+        wl = grid_case(m, 70, k, count, "stride", "f32", 0.0, (), 2, 2, 0, k + m)
+        print(f"partial stages {m}x70x{k} count {count} kernel {kid}", flush=True)
+        got, names = run_gpu(wl)
+        assert "vec_kernel" in names[0], names
+        assert_bits_equal(got["c"], run_oracle(wl)[0], names[0])
+
+
 @pytest.mark.parametrize("m,n,k", [(17, 33, 65), (64, 40, 24), (100, 9, 136)])
 def test_pointer_lists_at_any_alignment(m, n, k):
     wl = wk.small_case(np.random.default_rng(m), m, n, k, 5, "address", "bf16", "f32", 0.0, set(),
