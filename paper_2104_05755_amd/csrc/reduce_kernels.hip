@@ -248,14 +248,16 @@ __global__ __launch_bounds__(RT) void reduce_rows_group_kernel(ReduceParams p, i
 // [rb*TR*V, (rb+1)*TR*V).  Thread t: row vector tr = t % TR, column lane tc = t / TR.
 // HBM-bound for tall inputs (262144 rows of 128 bf16 columns, 67 MB: 19.9 us a call before, 14.9 =
 // 4.5 TB/s with eight loads in flight per thread and no branch between them).
-template <int OP, bool BF16, int V, bool X2>
-__global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t TR,
+// U: columns per trip, by how many a column lane has (2, 4 or 8: the registers of eight cost a call of
+// one column per lane, 2^20 x 1 bf16, 10.0 us in place of 5.6).  BT: threads of the workgroup.
+template <int OP, bool BF16, int V, bool X2, int U, int BT>
+__global__ __launch_bounds__(BT) void reduce_cols_kernel(ReduceParams p, int32_t TR,
                                                          int32_t col_seg, int32_t nseg,
                                                          int32_t nrb, float* work, int64_t per) {
-  __shared__ float sx[RT * V];
-  __shared__ float sx2[X2 ? RT * V : 1];
+  __shared__ __attribute__((aligned(16))) float sx[BT * V];
+  __shared__ __attribute__((aligned(16))) float sx2[X2 ? BT * V : 4];
   const int t = threadIdx.x;
-  const int TC = RT / TR;
+  const int TC = BT / TR;
   const int tr = t % TR, tc = t / TR;
   const int64_t lb = batch_of<BF16>(p, per, work, 2LL * nseg * p.m);
   const int32_t rb = (int32_t)(lb % nrb), s = (int32_t)(lb / nrb);
@@ -280,45 +282,66 @@ __global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t
   // Up to eight columns per trip, all loads issued before any is folded, into four accumulator
   // sets (combined in a fixed order below): a workgroup's usual eight columns per lane then cost
   // one memory latency.
-  float bx[4][V], bx2[4][V];
+  constexpr int SETS = U < 4 ? U : 4;
+  float bx[SETS][V], bx2[SETS][V];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < SETS; ++u)
 #pragma unroll
     for (int e = 0; e < V; ++e) bx[u][e] = bx2[u][e] = fold_identity<OP>();
   uint32_t c = c_lo + tc;
   auto trip = [&](auto count, auto&& load) {
-    constexpr int U = decltype(count)::value;
-    for (; c + (U - 1) * TC < c_hi; c += U * TC) {
-      float x[U][V];
+    constexpr int N = decltype(count)::value;
+    for (; c + (N - 1) * TC < c_hi; c += N * TC) {
+      float x[N][V];
 #pragma unroll
-      for (int u = 0; u < U; ++u) load(c + u * TC, x[u]);
+      for (int u = 0; u < N; ++u) load(c + u * TC, x[u]);
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int u = 0; u < N; ++u)
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-          bx[u & 3][e] = fold<OP>(bx[u & 3][e], x[u][e]);
-          if (X2) bx2[u & 3][e] = fold<OP>(bx2[u & 3][e], x[u][e] * x[u][e]);
+          bx[u % SETS][e] = fold<OP>(bx[u % SETS][e], x[u][e]);
+          if (X2) bx2[u % SETS][e] = fold<OP>(bx2[u % SETS][e], x[u][e] * x[u][e]);
         }
     }
   };
   if (vec) {
-    trip(Count<8>(), load_vec);
-    trip(Count<4>(), load_vec);
+    if constexpr (U >= 8) trip(Count<8>(), load_vec);
+    trip(Count<(U < 4 ? U : 4)>(), load_vec);
     trip(Count<1>(), load_vec);
   } else if (r0 < p.m) {
-    trip(Count<4>(), load_rows);
+    trip(Count<(U < 4 ? U : 4)>(), load_rows);
     trip(Count<1>(), load_rows);
   }
 #pragma unroll
   for (int e = 0; e < V; ++e) {
-    ax[e] = fold<OP>(fold<OP>(bx[0][e], bx[1][e]), fold<OP>(bx[2][e], bx[3][e]));
-    if (X2) ax2[e] = fold<OP>(fold<OP>(bx2[0][e], bx2[1][e]), fold<OP>(bx2[2][e], bx2[3][e]));
+    if constexpr (SETS == 2) {
+      ax[e] = fold<OP>(bx[0][e], bx[1][e]);
+      if (X2) ax2[e] = fold<OP>(bx2[0][e], bx2[1][e]);
+    } else {
+      ax[e] = fold<OP>(fold<OP>(bx[0][e], bx[1][e]), fold<OP>(bx[2][e], bx[3][e]));
+      if (X2) ax2[e] = fold<OP>(fold<OP>(bx2[0][e], bx2[1][e]), fold<OP>(bx2[2][e], bx2[3][e]));
+    }
   }
+  // column lanes that had a column: a batch of 17 x 9 blocks has 9 of 64
+  const int lanes = c_hi - c_lo < (uint32_t)TC ? (int)(c_hi - c_lo) : TC;
+  if (tc < lanes) {
+    const int at = tc * TR * V + tr * V;
+    if (skip == 0) {   // 16 bytes at a time: single floats, V apart, meet in V-way bank conflicts
 #pragma unroll
-  for (int e = 0; e < V; ++e) {
-    if (e < skip) continue;
-    sx[tc * TR * V + tr * V + e - skip] = ax[e];
-    if (X2) sx2[tc * TR * V + tr * V + e - skip] = ax2[e];
+      for (int e = 0; e < V; e += 4) {
+        *reinterpret_cast<float4*>(sx + at + e) = make_float4(ax[e], ax[e + 1], ax[e + 2], ax[e + 3]);
+        if (X2)
+          *reinterpret_cast<float4*>(sx2 + at + e) =
+              make_float4(ax2[e], ax2[e + 1], ax2[e + 2], ax2[e + 3]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        if (e < skip) continue;
+        sx[at + e - skip] = ax[e];
+        if (X2) sx2[at + e - skip] = ax2[e];
+      }
+    }
   }
   __syncthreads();
   const bool want_x = (p.flags & TPP_RED_X) != 0, want_x2 = (p.flags & TPP_RED_X2) != 0;
@@ -334,15 +357,15 @@ __global__ __launch_bounds__(RT) void reduce_cols_kernel(ReduceParams p, int32_t
       if (X2) work[(int64_t)nseg * p.m + (int64_t)s * p.m + r] = fx2;
     }
   };
-  // Fold the TC column lanes of each row slot.  With fewer slots than threads, RT / slots threads
-  // share a slot (TR * V is a power of two), each taking every RT / slots-th column lane, and meet
-  // in LDS once more: V reads per thread and RT / slots more, where one thread per slot read all TC
+  // Fold the TC column lanes of each row slot.  With fewer slots than threads, BT / slots threads
+  // share a slot (TR * V is a power of two), each taking every BT / slots-th column lane, and meet
+  // in LDS once more: V reads per thread and BT / slots more, where one thread per slot read all TC
   // in turn (32 for 64 rows of bf16: a third of that kernel's time).
-  const int parts = slots < RT ? RT / slots : 1;
-  for (int i = t; i < slots * parts; i += RT) {
+  const int parts = slots < BT ? BT / slots : 1;
+  for (int i = t; i < slots * parts; i += BT) {
     const int slot = i % slots, part = i / slots;
-    float fx = sx[part * slots + slot], fx2 = X2 ? sx2[part * slots + slot] : 0.0f;
-    for (int l = part + parts; l < TC; l += parts) {
+    float fx = fold_identity<OP>(), fx2 = fold_identity<OP>();
+    for (int l = part; l < lanes; l += parts) {
       fx = fold<OP>(fx, sx[l * slots + slot]);
       if (X2) fx2 = fold<OP>(fx2, sx2[l * slots + slot]);
     }
@@ -386,47 +409,44 @@ __device__ __forceinline__ int64_t combine_batch(int64_t per, int32_t n_out, int
   return bid - g * per;
 }
 
+// Workgroups of blockIdx.y = 1 take the x2 part of a call that wants both (one after the other in one
+// workgroup, the two chains of loads made 511 x 9000 bf16 by columns 10.2 us in place of 8.9).
 template <int OP, int OW>
 __global__ __launch_bounds__(RT) void reduce_combine_kernel(const float* work, int32_t n_out,
                                                             int32_t nseg, uint32_t flags,
                                                             float* out_x, float* out_x2,
                                                             int64_t per, int64_t out_stride) {
   constexpr int SL = RT / OW;   // lanes over the partials
-  __shared__ float sx[2][SL][OW];
+  __shared__ float sx[SL][OW];
   const int ol = threadIdx.x % OW, sl = threadIdx.x / OW;
   const int64_t lb = combine_batch(per, n_out, nseg, out_stride, work, out_x, out_x2);
   const int64_t o = lb * OW + ol;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    if (!(flags & (half ? TPP_RED_X2 : TPP_RED_X))) continue;
-    const float* const w = work + (half ? (int64_t)nseg * n_out : 0) + o;
-    float f = fold_identity<OP>();
-    if (o < n_out) {
-      int32_t s = sl;
-      for (; s + 7 * SL < nseg; s += 8 * SL) {   // eight partials in flight
-        float a[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = w[(int64_t)(s + u * SL) * n_out];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) f = fold<OP>(f, a[u]);
-      }
+  const bool second = !(flags & TPP_RED_X) || blockIdx.y != 0;
+  const float* const w = work + (second ? (int64_t)nseg * n_out : 0) + o;
+  float f = fold_identity<OP>();
+  if (o < n_out) {
+    int32_t s = sl;
+    for (; s + 7 * SL < nseg; s += 8 * SL) {   // eight partials in flight
       float a[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        a[u] = s + u * SL < nseg ? w[(int64_t)(s + u * SL) * n_out] : fold_identity<OP>();
+      for (int u = 0; u < 8; ++u) a[u] = w[(int64_t)(s + u * SL) * n_out];
 #pragma unroll
       for (int u = 0; u < 8; ++u) f = fold<OP>(f, a[u]);
     }
-    sx[half][sl][ol] = f;
-  }
-  __syncthreads();
-  if (threadIdx.x >= 2 * OW) return;
-  const int half = threadIdx.x / OW;
-  if (o >= n_out || !(flags & (half ? TPP_RED_X2 : TPP_RED_X))) return;
-  float f = sx[half][0][ol];
+    float a[8];
 #pragma unroll
-  for (int l = 1; l < SL; ++l) f = fold<OP>(f, sx[half][l][ol]);
-  (half ? out_x2 : out_x)[o] = f;
+    for (int u = 0; u < 8; ++u)
+      a[u] = s + u * SL < nseg ? w[(int64_t)(s + u * SL) * n_out] : fold_identity<OP>();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f = fold<OP>(f, a[u]);
+  }
+  sx[sl][ol] = f;
+  __syncthreads();
+  if (threadIdx.x >= OW || o >= n_out) return;
+  f = sx[0][ol];
+#pragma unroll
+  for (int l = 1; l < SL; ++l) f = fold<OP>(f, sx[l][ol]);
+  (second ? out_x2 : out_x)[o] = f;
 }
 
 struct Plan {
@@ -435,6 +455,8 @@ struct Plan {
   int32_t nseg;   // partial results per output
   int32_t seg;    // rows per segment (BY_ROWS) or columns per range (BY_COLS)
   int32_t tr;     // BY_COLS: row vectors per workgroup
+  int32_t u;      // BY_COLS: columns per trip
+  int32_t bt;     // BY_COLS: threads per workgroup
   int32_t nrb;    // BY_COLS: row blocks
   int64_t blocks; // first-pass workgroups
   int32_t cg;     // BY_ROWS with one segment: rounds of columns per wavefront (0: segments)
@@ -470,8 +492,6 @@ Plan make_plan(const ReduceParams& p) {
       pl.blocks = (waves + (RT / 64) - 1) / (RT / 64);
     }
   } else {
-    // Up to 64 row vectors per workgroup (at least four column lanes): a tall input gets more
-    // row blocks rather than more column ranges, which keeps the partials per output few.
     const int64_t vecs = ((int64_t)p.m + pl.v - 1) / pl.v;
     int32_t tr = 1;
     while (tr < vecs && tr < RT / 4) tr <<= 1;
@@ -479,11 +499,25 @@ Plan make_plan(const ReduceParams& p) {
     // row vectors per workgroup (down to 8, up to 2048 row blocks) instead of column ranges:
     // every workgroup then folds whole columns, no combine pass runs, and the many short
     // workgroups keep more loads in flight per CU.
-    if (vecs >= 512LL * 8)
+    if (vecs >= 512LL * 8) {
       while (tr > 8 && (vecs + tr - 1) / tr < 2048) tr >>= 1;
+    } else {
+      // Fewer row vectors as well where whole columns then fit one pass of at most 8 per lane (4096
+      // x 64 fp32: 7.2 us in two column ranges, 4.2 in one), and, of an input of many ranges, where
+      // the last row block would leave more than a fifth of the lanes idle (257 x 20000 fp32, 65 row
+      // vectors: 13.4 us on blocks of 64, 8.8 on 16).
+      while (tr > 16 && p.n > 8 * (RT / tr) && p.n <= 8 * (RT / 16)) tr >>= 1;
+      while (tr > 8 && p.n > 8 * (RT / tr) && (vecs + tr - 1) / tr * tr * 4 > vecs * 5) tr >>= 1;
+    }
+    // more of them where the columns are fewer than half the column lanes (100000 x 10 bf16: 8.4
+    // us with 32 column lanes, 4.2 with 16)
+    while (tr < RT && tr < vecs && RT / tr >= 2 * (int64_t)p.n) tr <<= 1;
+    // blocks whose columns fit two per lane of one wavefront take one wavefront each (5000 calls of
+    // 17 x 9 bf16: 21.7 us in workgroups of four, 5.1 so)
+    pl.bt = tr <= 16 && p.n <= 2 * (64 / tr) ? 64 : RT;
     pl.tr = tr;
     pl.nrb = (int32_t)((p.m + (int64_t)tr * pl.v - 1) / ((int64_t)tr * pl.v));
-    const int32_t tc = RT / tr;
+    const int32_t tc = pl.bt / tr;
     // otherwise aim for ~1024 workgroups (four per CU), each walking at least 8 columns per
     // column lane, and at most 512 partial results per output for the combine pass
     int64_t nseg = pl.nrb >= 512 ? 1 : (1024 + pl.nrb - 1) / pl.nrb;
@@ -494,6 +528,7 @@ Plan make_plan(const ReduceParams& p) {
     pl.seg = (int32_t)(((int64_t)p.n + nseg - 1) / nseg);
     pl.nseg = (int32_t)(((int64_t)p.n + pl.seg - 1) / pl.seg);
     pl.blocks = (int64_t)pl.nrb * pl.nseg;
+    pl.u = pl.seg >= 8 * tc ? 8 : pl.seg >= 4 * tc ? 4 : 2;
   }
   return pl;
 }
@@ -513,9 +548,14 @@ void launch_first(const ReduceParams& p, const Plan& pl, float* work, hipStream_
   else if (!pl.by_cols)
     hipLaunchKernelGGL((reduce_rows_kernel<OP, BF16, V, X2>), grid, dim3(RT), 0, stream, p, pl.seg,
                        pl.nseg, w, pl.blocks);
-  else
-    hipLaunchKernelGGL((reduce_cols_kernel<OP, BF16, V, X2>), grid, dim3(RT), 0, stream, p, pl.tr,
-                       pl.seg, pl.nseg, pl.nrb, w, pl.blocks);
+#define TPP_RED_COLS(U, BT)                                                                      \
+  hipLaunchKernelGGL((reduce_cols_kernel<OP, BF16, V, X2, U, BT>), grid, dim3(BT), 0, stream, p, \
+                     pl.tr, pl.seg, pl.nseg, pl.nrb, w, pl.blocks)
+  else if (pl.bt == 64) TPP_RED_COLS(2, 64);
+  else if (pl.u == 8) TPP_RED_COLS(8, RT);
+  else if (pl.u == 4) TPP_RED_COLS(4, RT);
+  else TPP_RED_COLS(2, RT);
+#undef TPP_RED_COLS
 }
 
 template <int OP>
@@ -530,13 +570,15 @@ void launch_op(const ReduceParams& p, const Plan& pl, float* work, hipStream_t s
   }
   if (pl.nseg > 1) {
     const int32_t n_out = pl.by_cols ? p.m : p.n;
-    // 16 outputs per workgroup read whole 64-byte runs; few outputs take more threads each, and
-    // outputs whose workgroups would pass a grid's 2^32 threads (2^28 in all) fewer
+    // 16 outputs per workgroup read whole 64-byte runs; few outputs of many partials (the statistics
+    // of a convolution) take more threads each, and outputs whose workgroups would pass a grid's
+    // 2^32 threads (2^28 in all) fewer
     const int64_t per16 = ((int64_t)n_out + 15) / 16;
-    const int ow = n_out < 512 ? 4 : per16 * p.G * RT < (1LL << 32) ? 16 : 64;
+    const unsigned parts = (p.flags & TPP_RED_X) && x2 ? 2 : 1;
+    const int ow = n_out <= 128 && pl.nseg > 32 ? 4 : per16 * p.G * RT < (1LL << 32) ? 16 : 64;
     const int64_t per = ((int64_t)n_out + ow - 1) / ow;
 #define TPP_RED_COMBINE(OW)                                                                     \
-  hipLaunchKernelGGL((reduce_combine_kernel<OP, OW>), dim3((unsigned)(per * p.G)), dim3(RT), 0, \
+  hipLaunchKernelGGL((reduce_combine_kernel<OP, OW>), dim3((unsigned)(per * p.G), parts), dim3(RT), 0, \
                      stream, work, n_out, pl.nseg, p.flags, p.out_x, p.out_x2, per, p.out_stride)
     if (ow == 4) TPP_RED_COMBINE(4);
     else if (ow == 16) TPP_RED_COMBINE(16);

@@ -67,6 +67,16 @@ def test_cols_windows_and_combine_widths(m, dtype):
         check(m, n, n % 3, m % 2, dtype, "cols")
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("m,n,G", [(17, 9, 40), (3, 32, 7), (16, 8, 5), (65, 8, 3), (100000, 10, 1), (9000, 1, 1),
+                                   (2100, 3, 2), (4096, 64, 1), (1030, 130, 1), (257, 3000, 1), (300, 2001, 2)])
+def test_cols_plans(m, n, G, dtype):
+    # one wavefront per small block, more row vectors than 64 for few columns, one pass in place of
+    # two ranges, row blocks of 16 and 8 vectors for an uneven number of rows
+    check(m, n, 0, 0, dtype, "cols", G=G)
+    check(m, n, 1, 1, dtype, "cols", G=G)
+
+
 def test_batched_blocks_at_any_alignment():
     check(61, 67, 2, 1, torch.bfloat16, "cols", G=9)
     check(61, 67, 2, 1, torch.float32, "rows", G=9)
