@@ -135,6 +135,34 @@ def test_embedding_any_row_length_and_alignment(case):
     assert (rest == 0xA5).all()
 
 
+@pytest.mark.parametrize("w_type", ["f32", "bf16"])
+@pytest.mark.parametrize("E", [4, 5, 8, 9, 16, 17, 31, 33, 63, 64, 65])
+def test_embedding_forms_by_row_and_list_length(E, w_type):
+    """Rows of one or two chunks, of at most 64 entries and longer, under lists of every length around
+    the four rows that a slot keeps in flight, whole rounds of the slots and the 64 indices of a block,
+    in one call; integers, so sums are exact."""
+    from paper_2104_05755_amd import TPP_DT_BF16, TPP_DT_F32, current_stream, tpp_embedding_bag
+    rng = np.random.default_rng(E)
+    M = 50
+    lens = [0, 1, 2, 3, 4, 5, 7, 8, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 600]
+    begin = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    idx = rng.integers(-1, M + 1, begin[-1])          # some outside the table
+    W = rng.integers(-8, 9, (M, E)).astype(np.float32)
+    want = np.zeros((len(lens), E), np.float32)
+    for b in range(len(lens)):
+        j = idx[begin[b]:begin[b + 1]]
+        want[b] = W[j[(j >= 0) & (j < M)]].sum(axis=0)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    Wd = dev(W).to(torch.float32 if w_type == "f32" else torch.bfloat16)
+    out = torch.full((len(lens) + 1, E), float("nan"), device="cuda")
+    print(f"embedding rows of {E} {w_type}", flush=True)
+    tpp_embedding_bag(M, E, TPP_DT_F32 if w_type == "f32" else TPP_DT_BF16, Wd, E, len(lens), dev(begin),
+                      dev(idx), TPP_DT_F32, out, E, current_stream())
+    torch.cuda.synchronize()
+    assert np.array_equal(out[:-1].cpu().numpy(), want)
+    assert bool(out[-1].isnan().all())
+
+
 def test_out_of_range_indices_are_skipped():
     wl = small(61, 300, 128, 25, (1, 30), "f32", "f32", integer=True)
     idx = wl.arrays["idx"]
