@@ -176,6 +176,11 @@ struct TransformParams {
   int64_t G;
   int64_t in_stride;
   int64_t out_stride;
+  // Filled by the launcher as well: tiles along m, the workgroups of a call and tiles_n and tiles_m as
+  // divisors, workgroups per XCD and XCDs that have one more (run 0: tiles in launch order).
+  uint32_t tiles_m;
+  FastDiv div_per, div_n, div_m;
+  uint32_t run, rest;
 };
 hipError_t launch_transform(TransformParams& p, hipStream_t stream);
 

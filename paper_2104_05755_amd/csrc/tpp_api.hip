@@ -870,7 +870,7 @@ tpp_status transform_impl(int32_t kind, int32_t m, int32_t n, int64_t ld_in, int
   if (!in || !out) return fail(TPP_ERR_INVALID_ARG, "NULL input or output");
   const int32_t es = dtype == TPP_DT_F32 ? 4 : 2;
   tpp::TransformParams p{in, out, kind, m, n, ld_in, ld_out, es, alpha, 0, G, in_stride,
-                         out_stride};
+                         out_stride, 0, {}, {}, {}, 0, 0};
   const hipError_t e = tpp::launch_transform(p, static_cast<hipStream_t>(stream));
   if (e == hipErrorInvalidConfiguration)
     return fail(TPP_ERR_UNSUPPORTED, "transform needs more than 2^31 - 1 workgroups");

@@ -90,24 +90,31 @@ __device__ __forceinline__ int tile_pos(int c, int r) {
 template <typename T>
 __device__ __forceinline__ uint32_t batch_of(const TransformParams& p, uint32_t b, uint32_t per,
                                              const T*& in, T*& out) {
-  const uint32_t g = b / per;
+  const uint32_t g = (uint32_t)dev::fdiv(b, p.div_per);   // grids are below 2^31
   in = static_cast<const T*>(p.in) + (int64_t)g * p.in_stride;
   out = static_cast<T*>(p.out) + (int64_t)g * p.out_stride;
   return b - g * per;
 }
 
-// The workgroup's tile (r0, c0).  Tiles are numbered along the output's contiguous direction and
-// each XCD (workgroup b is on XCD b % 8) takes a contiguous run of them: where rows are no whole 128-byte lines, the two tiles
-// that share a line write it into the same L2, which then writes it back whole.  Transpose of
-// fp32 4097 x 2049: 15.2 us in launch order along the input, 13.2 with runs per XCD along the
-// input, 12.3 so; 4096 x 2048 (lines of one tile each): 11.1, 11.5, 10.9.
+// The workgroup's tile (r0, c0).  In runs, tiles are numbered along the output's contiguous direction
+// and each XCD (workgroup b is on XCD b % 8) takes a contiguous run of them: where rows are no whole
+// 128-byte lines, the two tiles that share a line write it into the same L2, which then writes it back
+// whole.  Transpose of fp32 4097 x 2049: 15.4 us in launch order along the input, 13.2 with runs per XCD
+// along the input, 11.7 so.  Else in launch order along the input (tiles_in_runs).
 template <typename T>
 __device__ __forceinline__ void tile_of(const TransformParams& p, uint32_t per, const T*& in,
                                         T*& out, int32_t& r0, int32_t& c0) {
-  const uint32_t x = blockIdx.x % 8, run = gridDim.x / 8, rest = gridDim.x % 8;
-  const uint32_t b = x * run + min(x, rest) + blockIdx.x / 8;
+  if (p.run == 0) {
+    const uint32_t t = batch_of<T>(p, blockIdx.x, per, in, out);
+    const uint32_t tn = (uint32_t)dev::fdiv(t, p.div_m);
+    r0 = (int32_t)(t - tn * p.tiles_m) * TT;
+    c0 = (int32_t)tn * TT;
+    return;
+  }
+  const uint32_t x = blockIdx.x % 8;
+  const uint32_t b = x * p.run + min(x, p.rest) + blockIdx.x / 8;
   const uint32_t t = batch_of<T>(p, b, per, in, out);
-  const uint32_t tm = t / p.tiles_n;
+  const uint32_t tm = (uint32_t)dev::fdiv(t, p.div_n);
   r0 = (int32_t)tm * TT;
   c0 = (int32_t)(t - tm * p.tiles_n) * TT;
 }
@@ -298,14 +305,39 @@ __global__ __launch_bounds__(TPB) void vnni_kernel(TransformParams p, int64_t cp
 // A launch of per workgroups for each of the G calls: at most 2^31 - 1 workgroups in all.
 inline bool grid_fits(int64_t per, int64_t G) { return per <= 0x7fffffff / (G > 0 ? G : 1); }
 
+// Whether the tiles go in runs per XCD (see tile_of): always where two tiles share a 128-byte line, and
+// otherwise for the sizes that gain by it.  Below the L2s' 32 MiB (in and out) and in blocks one tile wide
+// launch order is faster: fp32 1024 x 1024 4.0 us and 4.9 in runs, 65536 x 64 VNNI to VNNI-transpose
+// (alpha 2) 5.7 and 6.7.  So it is well past the last-level cache's 256 MiB, where eight distant runs of columns a power of two apart
+// meet in the same memory channels: fp32 8192 x 8192 VNNI to VNNI-transpose 112 us (alpha 4), 129 in runs.
+// In between: fp32 4096 x 4096 23.5 and 20.1, bf16 8192 x 8192 44.1 and 38.8.
+inline bool tiles_in_runs(const TransformParams& p, int64_t es) {
+  const auto whole = [&](const void* q, int64_t ld, int64_t stride) {
+    return (reinterpret_cast<uintptr_t>(q) | (uintptr_t)(ld * es) | (uintptr_t)(stride * es)) % 128 == 0;
+  };
+  if (!whole(p.in, p.ld_in, p.in_stride) || !whole(p.out, p.ld_out, p.out_stride)) return true;
+  const int64_t bytes = 2 * es * p.m * p.n * p.G;
+  return p.m > TT && p.n > TT && bytes >= (32 << 20) && bytes <= (384 << 20);
+}
+
 template <int ES>
 hipError_t launch_es(TransformParams& p, hipStream_t stream) {
   const int64_t tiles_n = (p.n + TT - 1) / TT;
   const int64_t G = p.G;
-  p.tiles_n = (uint32_t)tiles_n;
+  const auto plan = [&](int64_t tiles_m, int64_t per) {   // per * G fits a grid
+    p.tiles_n = (uint32_t)tiles_n;
+    p.tiles_m = (uint32_t)tiles_m;
+    p.div_per = FastDiv(per);
+    p.div_n = FastDiv(tiles_n);
+    p.div_m = FastDiv(tiles_m);
+    const bool runs = tiles_in_runs(p, ES);
+    p.run = runs ? (uint32_t)(per * G / 8) : 0;
+    p.rest = (uint32_t)(per * G % 8);
+  };
   if (p.kind == 0) {
     const int64_t tiles = (p.m + TT - 1) / TT * tiles_n;
     if (!grid_fits(tiles, G)) return hipErrorInvalidConfiguration;
+    plan(tiles / tiles_n, tiles);
     hipLaunchKernelGGL(transpose_kernel<ES>, dim3((uint32_t)(tiles * G)), dim3(TPB), 0, stream, p,
                        (uint32_t)tiles);
   } else if (p.kind == 1) {
@@ -314,6 +346,7 @@ hipError_t launch_es(TransformParams& p, hipStream_t stream) {
     const int64_t total = cpg * ((p.n + p.alpha - 1) / p.alpha);
     const int64_t blocks = (total + TPB - 1) / TPB;
     if (!grid_fits(blocks, G)) return hipErrorInvalidConfiguration;
+    plan(1, blocks);
     const dim3 grid((uint32_t)(blocks * G));
     switch (p.alpha) {
       case 1: hipLaunchKernelGGL((vnni_kernel<ES, 1>), grid, dim3(TPB), 0, stream, p, cpg, total, (uint32_t)blocks); break;
@@ -324,6 +357,7 @@ hipError_t launch_es(TransformParams& p, hipStream_t stream) {
     const int64_t m_pad = ((int64_t)p.m + p.alpha - 1) / p.alpha * p.alpha;
     const int64_t tiles = (m_pad + TT - 1) / TT * tiles_n;
     if (!grid_fits(tiles, G)) return hipErrorInvalidConfiguration;
+    plan(tiles / tiles_n, tiles);
     const dim3 grid((uint32_t)(tiles * G));
     switch (p.alpha) {
       case 1: hipLaunchKernelGGL((vnni_t_kernel<ES, 1>), grid, dim3(TPB), 0, stream, p, (uint32_t)tiles); break;

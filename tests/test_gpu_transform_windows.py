@@ -51,3 +51,27 @@ def test_any_alignment_matches_the_oracle(dtype, kind, alpha, m, n, G, pad, shif
     got = od.cpu().numpy().view(nt)
     assert (got[:shift] == 0xBEEF).all()
     assert (got[shift:] == want).all()
+
+
+# whole 128-byte lines: launch order below 32 MiB, in one-tile strips and past 384 MiB, runs per XCD
+# in between; a line shared by tiles: runs at any size
+@pytest.mark.parametrize("m,n,G,pad", [(1024, 2048, 1, 0), (2048, 2048, 1, 0), (4096, 2176, 1, 0),
+                                       (64, 131072, 1, 0), (131072, 64, 1, 0), (10240, 5184, 1, 0),
+                                       (1024, 1088, 9, 0), (2048, 2048, 1, 1), (10240, 5184, 1, 1)])
+def test_orders_of_tiles(m, n, G, pad):
+    import paper_2104_05755_amd as tpp
+    print(f"transpose {G} x {m} x {n} pad {pad}", flush=True)
+    x = torch.arange(G * n * (m + pad), dtype=torch.int32, device="cuda")
+    y = torch.full((G, m, n), -1, dtype=torch.int32, device="cuda")
+    tpp.tpp_transform_batched(tpp.TPP_TR_TRANSPOSE, m, n, m + pad, n, tpp.TPP_DT_F32, 1, x,
+                              n * (m + pad), y, m * n, G, tpp.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(y, x.view(G, n, m + pad)[:, :, :m].transpose(1, 2))
+    # alpha 2: groups of two columns in, groups of two rows out
+    if pad == 0:
+        y.fill_(-1)
+        tpp.tpp_transform_batched(tpp.TPP_TR_VNNI_TO_VNNI_T, m, n, 2 * m, 2 * n, tpp.TPP_DT_F32, 2, x,
+                                  n * m, y, m * n, G, tpp.current_stream())
+        torch.cuda.synchronize()
+        a = x.view(G, n // 2, m // 2, 2, 2)                  # [g][c/2][r/2][r%2][c%2]
+        assert torch.equal(y.view(G, m // 2, n // 2, 2, 2), a.permute(0, 2, 1, 4, 3))
