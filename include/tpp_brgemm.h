@@ -191,8 +191,8 @@ tpp_status tpp_brgemm_execute_batched_aux(tpp_brgemm_handle h, const tpp_grid_st
 void tpp_brgemm_release(tpp_brgemm_handle h);
 
 /* Human-readable description of a handle's descriptor (types, m / n / k, batch kind, whether
- * the 16-byte load path is open to it).  The kernel instance is chosen per launch, from the grid
- * as well: tpp_brgemm_describe_launch names it.  Writes at most len bytes including the
+ * it keeps every 8-element chunk of its bf16 blocks aligned: "vec", else "generic").  The kernel
+ * instance is chosen per launch, from the grid as well: tpp_brgemm_describe_launch names it.  Writes at most len bytes including the
  * terminating NUL.  Host-only. */
 tpp_status tpp_brgemm_describe(tpp_brgemm_handle h, char* buf, size_t len);
 

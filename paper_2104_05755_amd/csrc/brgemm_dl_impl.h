@@ -235,7 +235,7 @@ void brgemm_bf16_dl_kernel(BrgemmParams p) {
       buffer_load_lds16(is_a ? ra : rb, is_a ? la[r] : lb[r - A_PER_W], dst);
     } else {
       // a pair block off 16-byte alignment (offset or pointer lists): the same chunk through
-      // registers, element by element
+      // registers, one 16-byte load at any element address
       const char* src = is_a ? ua + la[r] : ub + lb[r - A_PER_W];
       *reinterpret_cast<u32x4*>(dst + lane * 16) =
           ld16_unaligned(reinterpret_cast<const uint16_t*>(src));

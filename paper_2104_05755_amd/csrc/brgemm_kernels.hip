@@ -168,23 +168,6 @@ __device__ __forceinline__ void store_group(const BrgemmParams& p, const Instanc
 // ---------------------------------------------------------------------------------------------
 // bf16 kernel family
 // ---------------------------------------------------------------------------------------------
-// 16 bytes = 8 bf16 of one column, zero when `ok` is false; element loads if the address is not
-// 16-byte aligned.
-__device__ __forceinline__ uint4 load8(const uint16_t* ptr, bool ok, bool aligned) {
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (ok) {
-    if (aligned) {
-      v = *reinterpret_cast<const uint4*>(ptr);
-    } else {
-      v.x = (uint32_t)ptr[0] | ((uint32_t)ptr[1] << 16);
-      v.y = (uint32_t)ptr[2] | ((uint32_t)ptr[3] << 16);
-      v.z = (uint32_t)ptr[4] | ((uint32_t)ptr[5] << 16);
-      v.w = (uint32_t)ptr[6] | ((uint32_t)ptr[7] << 16);
-    }
-  }
-  return v;
-}
-
 __device__ __forceinline__ uint32_t word(const uint4& v, int d) {
   return d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w;
 }
@@ -205,7 +188,8 @@ __device__ __forceinline__ void store_a_transposed(uint16_t* dst_row0, const uin
   }
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GENERIC>
+// Blocks narrower than one 8-element chunk in m or k: element loads, every row, column and k checked.
+template <int BM, int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(NT) void brgemm_bf16_kernel(BrgemmParams p) {
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -228,8 +212,8 @@ __global__ __launch_bounds__(NT) void brgemm_bf16_kernel(BrgemmParams p) {
   const int64_t stages = in.npairs * ksteps;
 
   // Staging assignments, fixed for the whole reduction.
-  int64_t a_off[A_REP][GENERIC ? 8 : 1];
-  bool a_ok[A_REP][GENERIC ? 8 : 1];
+  int64_t a_off[A_REP][8];
+  bool a_ok[A_REP][8];
   int a_kc[A_REP], a_row[A_REP];
 #pragma unroll
   for (int rep = 0; rep < A_REP; ++rep) {
@@ -237,7 +221,7 @@ __global__ __launch_bounds__(NT) void brgemm_bf16_kernel(BrgemmParams p) {
     a_kc[rep] = q % KCH;
     a_row[rep] = (q / KCH) * 8;
 #pragma unroll
-    for (int e = 0; e < (GENERIC ? 8 : 1); ++e) {
+    for (int e = 0; e < 8; ++e) {
       a_off[rep][e] = 0;
       a_ok[rep][e] = (q < A_SUB) && row_in_a(p, tc.row0 + a_row[rep] + e, a_off[rep][e]);
     }
@@ -263,44 +247,33 @@ __global__ __launch_bounds__(NT) void brgemm_bf16_kernel(BrgemmParams p) {
     const uint16_t* pa;
     const uint16_t* pb;
     pair_bases<uint16_t>(p, in, i, pa, pb);
-    const bool aligned =
-        !GENERIC && ((reinterpret_cast<uintptr_t>(pa) | reinterpret_cast<uintptr_t>(pb)) & 15) == 0;
 #pragma unroll
     for (int rep = 0; rep < A_REP; ++rep) {
       const int32_t k0 = kk + a_kc[rep] * 8;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        if (!GENERIC) {
-          const bool ok = a_ok[rep][0] && k0 < p.k;
-          a_reg[rep][j] = load8(pa + a_off[rep][0] + (int64_t)(k0 + j) * p.lda, ok, aligned);
-        } else {
-          // element loads: each of the 8 rows and the k index checked on its own
-          uint32_t h[8];
+        // each of the 8 rows and the k index checked on its own
+        uint32_t h[8];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const bool ok = a_ok[rep][e] && (k0 + j) < p.k;
-            h[e] = ok ? pa[a_off[rep][e] + (int64_t)(k0 + j) * p.lda] : 0u;
-          }
-          a_reg[rep][j] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16),
-                                     h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+        for (int e = 0; e < 8; ++e) {
+          const bool ok = a_ok[rep][e] && (k0 + j) < p.k;
+          h[e] = ok ? pa[a_off[rep][e] + (int64_t)(k0 + j) * p.lda] : 0u;
         }
+        a_reg[rep][j] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                                   h[6] | (h[7] << 16));
       }
     }
 #pragma unroll
     for (int rep = 0; rep < B_REP; ++rep) {
       const int32_t k0 = kk + b_kc[rep] * 8;
-      if (!GENERIC) {
-        b_reg[rep] = load8(pb + b_off[rep] + k0, b_ok[rep] && k0 < p.k, aligned);
-      } else {
-        uint32_t h[8];
+      uint32_t h[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const bool ok = b_ok[rep] && (k0 + e) < p.k;
-          h[e] = ok ? pb[b_off[rep] + k0 + e] : 0u;
-        }
-        b_reg[rep] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
-                                h[6] | (h[7] << 16));
+      for (int e = 0; e < 8; ++e) {
+        const bool ok = b_ok[rep] && (k0 + e) < p.k;
+        h[e] = ok ? pb[b_off[rep] + k0 + e] : 0u;
       }
+      b_reg[rep] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                              h[6] | (h[7] << 16));
     }
   };
 
@@ -373,7 +346,7 @@ __global__ __launch_bounds__(NT) void brgemm_bf16_kernel(BrgemmParams p) {
         const int32_t R0 = tc.row0 + wm * WTM + tm * 32 + q * 8 + (lane >> 5) * 4;
         const float v[4] = {acc[tm][tn][q * 4 + 0], acc[tm][tn][q * 4 + 1],
                             acc[tm][tn][q * 4 + 2], acc[tm][tn][q * 4 + 3]};
-        store_group<GENERIC>(p, in, R0, C, v);
+        store_group<true>(p, in, R0, C, v);
       }
     }
 }
@@ -1379,10 +1352,10 @@ hipError_t launch_brgemm(BrgemmParams& p, int32_t id, hipStream_t stream, std::s
     }
     case K_BF16_GENERIC:
       if (name_out) {
-        *name_out = "brgemm_bf16_kernel<64, 64, 2, 2, true>";
+        *name_out = "brgemm_bf16_kernel<64, 64, 2, 2>";
         return hipSuccess;
       }
-      hipLaunchKernelGGL((brgemm_bf16_kernel<64, 64, 2, 2, true>), grid, block, 0, stream, p);
+      hipLaunchKernelGGL((brgemm_bf16_kernel<64, 64, 2, 2>), grid, block, 0, stream, p);
       break;
     default: {
       // windows of four rows and four k inside every block (plan_launch pads p.vm to match)

@@ -13,7 +13,8 @@
 
 namespace tpp {
 
-// Division of values below 2^31 by a divisor known to the host: a / d = a * mul >> sh, with
+// Division of values below 2^31 by a divisor known to the host, by multiplication (Granlund and
+// Montgomery, "Division by Invariant Integers using Multiplication", 1994): a / d = a * mul >> sh, with
 // mul = floor(2^sh / d) + 1 and sh = 31 + ceil(log2 d), so that mul * d - 2^sh <= 2^ceil(log2 d) and
 // the quotient is exact.  A multiply and a shift where a division by a run-time value is a chain of
 // about 25 dependent instructions: the tile, row and column decoding of a BRGEMM kernel has some
@@ -71,10 +72,10 @@ struct BrgemmParams {
   int32_t tiles_m, tiles_n;  // tiles per group
   int64_t groups;            // 1 (strided) or G (explicit)
   int64_t total_tiles;
-  // Split over the pair list (grids too small to fill the GPU): split > 1 chunks of each
-  // instance's pairs (fp32 kernel) or stages (direct-to-LDS kernels) are reduced by separate
-  // workgroups into ws (split x total_tiles fp32 tiles), then summed in chunk order by a
-  // finishing kernel that applies the epilogue.
+  // Split over the stage list (grids too small to fill the GPU): split > 1 chunks of each
+  // instance's stages (fp32 and direct-to-LDS kernels) are reduced by separate workgroups into ws
+  // (split x total_tiles fp32 tiles), then summed in chunk order by a finishing kernel that applies
+  // the epilogue.
   int32_t split;             // 1: no split
   int32_t split_base, split_rem;   // chunk c has split_base stages, and one more if c < split_rem
   float* ws;
@@ -162,8 +163,7 @@ int64_t reduce_work_floats(const ReduceParams& p);
 hipError_t launch_reduce(const ReduceParams& p, float* work, hipStream_t stream);
 
 // Transform TPP launcher (transform_kernels.hip).  kind: 0 transpose, 1 VNNI, 2 VNNI to
-// VNNI-transpose; es: entry bytes (2 or 4); vec: both operands 16-byte aligned with leading
-// dimensions of whole 16-byte units (the vector paths).  tiles_m is filled by the launcher.
+// VNNI-transpose; es: entry bytes (2 or 4).
 // hipErrorInvalidConfiguration when one launch would need more than 2^31 - 1 workgroups.
 struct TransformParams {
   const void* in;

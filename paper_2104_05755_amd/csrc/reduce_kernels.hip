@@ -122,8 +122,8 @@ __device__ __forceinline__ int64_t batch_of(ReduceParams& p, int64_t per, float*
   return bid - g * per;
 }
 
-// BY_ROWS: wavefront wid folds rows [s*seg_rows, min(m, (s+1)*seg_rows)) of column c, where
-// c = wid % n, s = wid / n.
+// BY_ROWS with several segments per column: wavefront wid folds rows [s*seg_rows, min(m,
+// (s+1)*seg_rows)) of column c, where c = wid % n, s = wid / n, into the work buffer.
 template <int OP, bool BF16, int V, bool X2>
 __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t seg_rows,
                                                          int32_t nseg, float* work, int64_t per) {
@@ -135,7 +135,6 @@ __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t
   const int32_t r_lo = s * seg_rows;
   const int32_t rows = min(p.m - r_lo, seg_rows);   // r_lo + seg_rows may pass 2^31 - 1
   const int64_t col = (int64_t)c * p.ld;
-  const bool want_x = (p.flags & TPP_RED_X) != 0, want_x2 = (p.flags & TPP_RED_X2) != 0;
   float ax = fold_identity<OP>(), ax2 = fold_identity<OP>();
   const int32_t nv = rows / V;   // full V-chunks
   for (int32_t j = lane; j < nv; j += 64) {
@@ -155,13 +154,8 @@ __global__ __launch_bounds__(RT) void reduce_rows_kernel(ReduceParams p, int32_t
   ax = wave_fold<OP>(ax);
   if (X2) ax2 = wave_fold<OP>(ax2);
   if (lane == 0) {
-    if (nseg == 1) {
-      if (want_x) p.out_x[c] = ax;
-      if (want_x2) p.out_x2[c] = ax2;
-    } else {
-      work[(int64_t)s * p.n + c] = ax;
-      if (X2) work[(int64_t)nseg * p.n + (int64_t)s * p.n + c] = ax2;
-    }
+    work[(int64_t)s * p.n + c] = ax;
+    if (X2) work[(int64_t)nseg * p.n + (int64_t)s * p.n + c] = ax2;
   }
 }
 

@@ -22,7 +22,7 @@
 struct tpp_brgemm_kernel_s {
   tpp_brgemm_desc desc;
   bool bf16;         // A/B are bf16 (else fp32)
-  bool vec_ok;       // descriptor allows the 16-byte load path
+  bool vec_ok;       // bf16, and the descriptor keeps every 8-element chunk aligned
   char name[96];
 };
 
