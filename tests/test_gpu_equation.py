@@ -110,8 +110,8 @@ MIXED = [("leaf", 0), ("leaf", 1), ("sub", 0, 1), ("leaf", 2), ("leaf", 3), ("le
 @pytest.mark.parametrize("out_type", ["f32", "bf16"])
 @pytest.mark.parametrize("pad", [8, 1])
 def test_all_leaf_kinds_in_one_tree(out_type, pad):
-    # m a multiple of 8: with pad 8 every column starts 16-byte aligned (16-byte loads and
-    # stores of 8 rows per thread); with pad 1 the same tree runs element by element
+    # with pad 8 every column starts 16-byte aligned, with pad 1 at any element; 16-byte loads and
+    # stores of 8 rows per thread on both
     say(f"equation mixed leaves pad {pad} {out_type}")
     g, r, got, init = one(MIXED, 7, 248, 23,
                           [(-8, 8, "bf16", "none", pad), (-8, 8, "f32", "col", 0),
@@ -166,7 +166,7 @@ def test_layernorm_chain_matches_oracle():
 
 @pytest.mark.parametrize("keys,columns", [(512, 300), (77, 50)])
 def test_softmax_chain_matches_oracle(keys, columns):
-    # 512 keys: both equations on the vector path; 77: element path
+    # 512 keys: whole chunks of 8 rows; 77: windows at the ends of the columns
     wl = wk.softmax(seed=92, keys=keys, columns=columns)
     say(f"softmax chain {keys} x {columns}")
     got = gpu_steps(wl.steps, wl.arrays, ["mx", "xe", "s", "y"])
@@ -197,8 +197,8 @@ def _balanced(depth):
 @pytest.mark.parametrize("depth", [3, 5])
 @pytest.mark.parametrize("m", [256, 100])
 def test_deep_trees_use_more_temporaries(depth, m):
-    # 3 and 5 temporaries: the vector kernel's 4- and 8-temporary variants (m = 256) and the
-    # element path (m = 100); small integers keep every result exact
+    # 3 and 5 temporaries: the vector kernel's 4- and 8-temporary variants, on whole chunks of 8
+    # rows (m = 256) and with a window (m = 100); small integers keep every result exact
     nodes, root = _balanced(depth)
     from paper_2104_05755_amd import tpp_equation_plan
     assert tpp_equation_plan(nodes, root)[3] == depth
@@ -208,16 +208,21 @@ def test_deep_trees_use_more_temporaries(depth, m):
     assert np.array_equal(g, r)
 
 
-@pytest.mark.parametrize("m,n", [(65537, 65537), (65544, 65536)], ids=["element", "vector"])
-def test_equation_past_2_pow_32_elements(m, n):
-    """m * n just past 2^32 (8.6 GB per bf16 tensor): 64-bit element indices on the element path
-    (odd m) and on the vector path.  X is the closed-form pattern x(e) = (e mod 251) - 125 built
-    on the device in chunks, and Y = muladd(X, 2, row[c]) with row[c] = (c mod 7) - 3 is checked
-    against the same closed form at every element (small integers: exact in bf16)."""
+@pytest.mark.parametrize("m,n,ldo,tree", [(65537, 65537, 65537, "chain"), (65544, 65536, 65544, "chain"),
+                                          (65537, 65537, 65537, "max"), (65544, 65536, 65544, "max"),
+                                          (3, 1431655800, 4, "max")],
+                         ids=["chain_ragged", "chain_whole", "vector_ragged", "vector_whole", "few_rows"])
+def test_equation_past_2_pow_32_elements(m, n, ldo, tree):
+    """m * n just past 2^32 (8.6 GB per bf16 tensor): 64-bit element indices in the chain kernel, in
+    the vector kernel (the tree ends in a max of the value and X, which is no chain) and in the
+    element kernel (fewer than 8 rows, not contiguous).  X is the closed-form pattern x(e) = (e mod
+    251) - 125 built on the device in chunks, and Y = muladd(X, 2, row[c]) with row[c] = (c mod 7)
+    - 3, or its maximum with X, is checked against the same closed form at every element (small
+    integers: exact in bf16)."""
     from paper_2104_05755_amd import TPP_DT_BF16, TPP_DT_F32, current_stream, tpp_equation_execute
     total = m * n
     assert total > 2 ** 32
-    say(f"equation past 2^32: {m} x {n}")
+    say(f"equation past 2^32: {m} x {n} {tree}")
     dev = torch.device("cuda:0")
     chunk = 1 << 28
     x = torch.empty(total, dtype=torch.bfloat16, device=dev)
@@ -226,18 +231,23 @@ def test_equation_past_2_pow_32_elements(m, n):
         x[s:s + e.numel()] = ((e % 251) - 125).to(torch.bfloat16)
     row = ((torch.arange(n, dtype=torch.int64, device=dev) % 7) - 3).to(torch.float32)
     two = torch.full((1,), 2.0, dtype=torch.float32, device=dev)
-    y = torch.full((total,), float("nan"), dtype=torch.bfloat16, device=dev)
+    y = torch.full((ldo * n,), float("nan"), dtype=torch.bfloat16, device=dev)
     nodes = [("leaf", 0), ("leaf", 1), ("leaf", 2), ("muladd", 0, 1, 2)]
-    tpp_equation_execute(nodes, 3, m, n, [(x, m, TPP_DT_BF16, "none"), (two, 1, TPP_DT_F32, "scalar"),
-                                          (row, 1, TPP_DT_F32, "row")],
-                         y, m, TPP_DT_BF16, current_stream())
+    if tree == "max":
+        nodes += [("leaf", 0), ("max", 3, 4)]
+    tpp_equation_execute(nodes, len(nodes) - 1, m, n,
+                         [(x, m, TPP_DT_BF16, "none"), (two, 1, TPP_DT_F32, "scalar"),
+                          (row, 1, TPP_DT_F32, "row")], y, ldo, TPP_DT_BF16, current_stream())
     torch.cuda.synchronize()
     del x
     bad = 0
     for s in range(0, total, chunk):
         e = torch.arange(s, min(s + chunk, total), dtype=torch.int64, device=dev)
         want = (2 * ((e % 251) - 125) + ((e // m) % 7) - 3).to(torch.float32)
-        bad += int((y[s:s + e.numel()].to(torch.float32) != want).sum().item())
+        if tree == "max":
+            want = torch.maximum(want, ((e % 251) - 125).to(torch.float32))
+        got = y[s:s + e.numel()] if ldo == m else y[e // m * ldo + e % m]
+        bad += int((got.to(torch.float32) != want).sum().item())
     assert bad == 0, f"{bad} wrong elements"
 
 
@@ -253,14 +263,13 @@ def test_single_row_equations(n, pad):
     assert np.array_equal(g, r)
 
 
-# Outputs of at most 2^16 elements that the vector path does not take run one element per
-# thread with every leaf loaded up front; the cases above (a few thousand elements) exercise that
-# kernel.  Larger outputs off the vector path run the element kernel: the same trees past the
-# small-output limit (m odd, so never the vector path).
+# Outputs of fewer than 8 rows run one element per thread with every leaf loaded up front, up to 2^16
+# elements; past that the element kernel, eight elements per thread, unless their rows are contiguous.
+# Outputs of 8 rows and more run the chain or the vector kernel, whatever their size and alignment.
 @pytest.mark.parametrize("out_type", ["f32", "bf16"])
-def test_element_path_past_small_outputs(out_type):
-    say(f"equation element path, mixed leaves, {out_type}")
-    m, n = 251, 300   # 75,300 elements
+@pytest.mark.parametrize("m,n", [(251, 300), (1, 70001), (3, 22000), (7, 10000), (7, 9000), (2, 257)])
+def test_mixed_leaves_by_rows_and_size(m, n, out_type):
+    say(f"equation {m} x {n}, mixed leaves, {out_type}")
     g, r, got, init = one(MIXED, 7, m, n,
                           [(-8, 8, "bf16", "none", 1), (-8, 8, "f32", "col", 0),
                            (-4, 4, "bf16", "row", 0), (-4, 4, "f32", "scalar", 0),
@@ -272,9 +281,26 @@ def test_element_path_past_small_outputs(out_type):
     assert np.array_equal(gaps(got), gaps(init))
 
 
+# ragged rows of a chain; fewer than 8 rows past 2^16 elements, not contiguous, and below
+@pytest.mark.parametrize("m,n,pad", [(201, 400, 0), (5, 14000, 1), (3, 200, 0)])
 @pytest.mark.parametrize("op,lo,hi", UNARY, ids=[u[0] for u in UNARY])
-def test_every_unary_op_element_path(op, lo, hi):
-    g, r, _, _ = one([("leaf", 0), (op, 0)], 1, 201, 400, [(lo, hi, "f32", "none", 0)], seed=12)
+def test_every_unary_op_by_rows(op, lo, hi, m, n, pad):
+    g, r, _, _ = one([("leaf", 0), (op, 0)], 1, m, n, [(lo, hi, "f32", "none", pad)], ldo=m + pad,
+                     seed=12)
     assert rel_fro(g, r) <= 1e-5
     if op in ("identity", "neg", "relu", "square"):
+        assert np.array_equal(g, r)
+
+
+@pytest.mark.parametrize("m,n,pad", [(201, 400, 0), (5, 14000, 1), (3, 200, 0)])
+@pytest.mark.parametrize("op", BINARY + ["muladd"])
+def test_every_other_op_by_rows(op, m, n, pad):
+    # the trailing max keeps the tree off the chain kernel where m is large
+    nodes = [("leaf", 0), ("leaf", 1)]
+    nodes += [("leaf", 2), (op, 0, 1, 2)] if op == "muladd" else [(op, 0, 1)]
+    nodes += [("leaf", 0), ("max", len(nodes) - 1, len(nodes))]
+    g, r, _, _ = one(nodes, len(nodes) - 1, m, n, [(-3, 3, "f32", "none", pad), (0.5, 2, "f32", "none", 1),
+                                                   (-2, 2, "f32", "row", 0)], ldo=m + pad, seed=13)
+    assert rel_fro(g, r) <= 1e-5
+    if op in ("add", "sub", "mul", "max", "min"):
         assert np.array_equal(g, r)

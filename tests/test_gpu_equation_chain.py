@@ -77,6 +77,21 @@ def test_random_chains_exact(m, n):
         assert np.array_equal(bits(got)[:, m:], bits(init)[:, m:])   # gaps untouched
 
 
+@pytest.mark.parametrize("m,n", [(256, 20000), (64, 70001), (8, 600003), (520, 20003), (33, 130000)])
+def test_several_steps_per_wavefront(m, n):
+    """Enough columns that a wavefront takes several steps of them, one or more columns each (64 /
+    chunks of 8 rows), and loads the full leaves of the next step ahead; the last column tile is
+    partial."""
+    specs = [(-2, 2, "bf16", "none", 1), (-2, 2, "f32", "row", 0), (-2, 2, "f32", "col", 0),
+             (-2, 2, "f32", "none", 0), (-2, 2, "bf16", "row", 0)]
+    nodes = [("leaf", 0), ("leaf", 1), ("sub", 0, 1), ("leaf", 2), ("leaf", 3), ("muladd", 2, 3, 4),
+             ("leaf", 4), ("mul", 5, 6), ("relu", 7)]
+    for out_type in ("f32", "bf16"):
+        print(f"chain {m}x{n} {out_type}", flush=True)
+        g, r, _, _ = one(nodes, 8, m, n, specs, out_type=out_type, ldo=m + 1, seed=m, integer=True)
+        assert np.array_equal(g, r)
+
+
 @pytest.mark.parametrize("m", [9, 64, 517])
 def test_chain_in_place(m):
     # out is the full leaf exactly: the window of a column's last rows re-reads rows that other

@@ -89,12 +89,15 @@ def test_pointer_lists_at_any_alignment(m, n, k):
     assert_bits_equal(got["c"], ref, names[0])
 
 
-def test_ragged_aux_steps_match_elementwise():
+@pytest.mark.parametrize("ab_type,c_type,k", [("bf16", "bf16", 45), ("bf16", "f32", 45), ("f32", "f32", 45),
+                                              ("f32", "bf16", 45), ("f32", "f32", 20)])
+def test_ragged_aux_steps_match_elementwise(ab_type, c_type, k):
     """SAVE_PREACT and RELU_INV on a ragged m: aux has C's layout, the last chunk row by row."""
-    wl = grid_case(27, 19, 45, 2, "stride", "bf16", 0.0, ("bias", "relu", "save_preact"), 3, 2, 1, 5)
+    wl = grid_case(27, 19, k, 2, "stride", c_type, 0.0, ("bias", "relu", "save_preact"), 3, 2, 1, 5, ab_type)
     call = wl.calls[0]
     call.aux = "z"
-    wl.arrays["z"] = np.full_like(wl.arrays["c"], 0x7FC0)
+    gap = np.float32(-77) if c_type == "f32" else np.uint16(0x7FC0)
+    wl.arrays["z"] = np.full_like(wl.arrays["c"], gap)
     plain = wk.Workload("plain", wl.arrays, [wk.Call(**dict(call.__dict__, flags={"bias"}, aux=None))])
     print("ragged save_preact", flush=True)
     got, names = run_gpu(wl)
@@ -106,13 +109,14 @@ def test_ragged_aux_steps_match_elementwise():
         for c in range(call.n):
             stored[base + c * call.ldc: base + c * call.ldc + call.m] = True
     assert_bits_equal(got["z"][stored], z[stored], names[0])
-    assert (got["z"][~stored] == 0x7FC0).all()
+    assert (got["z"][~stored] == gap).all()
     inv = wk.Call(**dict(call.__dict__, flags={"relu_inv"}, bias=None))
     wl2 = wk.Workload("inv", dict(wl.arrays, z=z), [inv])
     nobias = wk.Call(**dict(call.__dict__, flags=set(), aux=None, bias=None))
     v = run_oracle(wk.Workload("v", wl.arrays, [nobias]))[0]
     got2, _ = run_gpu(wl2)
-    want = np.where(wk.bf16_values(z) > 0, v, 0).astype(np.uint16)
+    z32 = wk.bf16_values(z) if c_type == "bf16" else z
+    want = np.where(z32 > 0, v, 0).astype(v.dtype)
     assert_bits_equal(got2["c"][stored], want[stored], "relu_inv")
 
 
