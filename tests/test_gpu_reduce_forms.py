@@ -146,15 +146,24 @@ def test_extents_at_the_top_of_int32(by, m, n, captured):
             assert torch.equal(ox[s:s + e.numel()], want) and torch.equal(mx[s:s + e.numel()], want)
 
 
-def test_combine_of_2_pow_28_outputs():
+@pytest.mark.parametrize("captured", [False, True])
+def test_combine_of_2_pow_28_outputs(captured):
     """A batch whose partial results have so many outputs that 16 per workgroup of the combine pass
-    would pass a grid's 2^32 threads.  Every call reads the same block (in_stride 0)."""
+    would pass a grid's 2^32 threads.  Every call reads the same block (in_stride 0).  Captured, its
+    partials would pass the 4 GiB that captures may take, and it runs with one partial per output."""
     import paper_2104_05755_amd as tpp
     m, n, G = 512, 40, (1 << 19) + 3
     v = np.random.default_rng(5).integers(-8, 9, n * m)
     x = torch.from_numpy(v.astype(np.float32)).to(torch.bfloat16).cuda()
-    print(f"reduce by cols {m} x {n}, {G} calls", flush=True)
-    ox, _ = call(x, m, n, m, tpp.TPP_RED_SUM, "cols", flags="x", G=G)
+    print(f"reduce by cols {m} x {n}, {G} calls, captured {captured}", flush=True)
+    if captured:
+        s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            ox, _ = call(x, m, n, m, tpp.TPP_RED_SUM, "cols", flags="x", G=G, stream=s.cuda_stream)
+        g.replay()
+    else:
+        ox, _ = call(x, m, n, m, tpp.TPP_RED_SUM, "cols", flags="x", G=G)
     torch.cuda.synchronize()
     want = torch.from_numpy(v.reshape(n, m).sum(axis=0).astype(np.float32)).cuda()
     assert bool((ox.view(G, m) == want).all())
