@@ -527,34 +527,38 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
 
   // k past the end becomes zero here, on the way to LDS, and not behind the loads: a use of their
   // values there would wait for them, a memory latency per partial stage (8 pairs of 64 x 64 x 16
-  // blocks on 16 x 16 instances: 12.5 us so, 10.7 here).
-  auto store_a = [&](int buf, Staged& r) {
-    uint16_t* As = lds + buf * STAGE + GUARD;
-    const bool ktail = !FULL && r.kk + BK > p.k;
+  // blocks on 16 x 16 instances: 12.5 us so, 10.7 here).  Before the MFMAs of the stage in front: between
+  // them, next to the stores, 4 pairs of 63 x 32 x 9 blocks on 32 x 32 instances took 13.8 us and not 12.6.
+  auto mask = [&](Staged& r) {
+    if (FULL || r.kk + BK <= p.k) return;   // uniform
 #pragma unroll
     for (int rep = 0; rep < A_REP; ++rep) {
       const int32_t k0 = r.kk + a_kc[rep] * SK;
-      if (ktail) {
 #pragma unroll
-        for (int j = 0; j < SK; ++j)
-          r.a[rep][j] = keep_if(r.a[rep][j], (RAGGED ? k0 + j : k0) < p.k);
-      }
+      for (int j = 0; j < SK; ++j)
+        r.a[rep][j] = keep_if(r.a[rep][j], (RAGGED ? k0 + j : k0) < p.k);
+    }
+#pragma unroll
+    for (int rep = 0; rep < B_REP; ++rep) {
+      const int32_t k0 = r.kk + b_kc[rep] * 8;
+      if constexpr (RAGGED)
+        r.b[rep] = shift_down(r.b[rep], k0 + 8 > p.k ? k0 + 8 - p.k : 0);
+      else
+        r.b[rep] = keep_if(r.b[rep], k0 < p.k);
+    }
+  };
+  auto store_a = [&](int buf, const Staged& r) {
+    uint16_t* As = lds + buf * STAGE + GUARD;
+#pragma unroll
+    for (int rep = 0; rep < A_REP; ++rep) {
       if (A_SUB % NTH == 0 || t + NTH * rep < A_SUB)
         store_a_transposed_v<SK>(As + a_row[rep] * LDS_ROW + a_kc[rep] * SK, r.a[rep]);
     }
   };
-  auto store_b = [&](int buf, Staged& r) {
+  auto store_b = [&](int buf, const Staged& r) {
     uint16_t* Bs = lds + buf * STAGE + GUARD + BM * LDS_ROW;
-    const bool ktail = !FULL && r.kk + BK > p.k;
 #pragma unroll
     for (int rep = 0; rep < B_REP; ++rep) {
-      const int32_t k0 = r.kk + b_kc[rep] * 8;
-      if (ktail) {
-        if constexpr (RAGGED)
-          r.b[rep] = shift_down(r.b[rep], k0 + 8 > p.k ? k0 + 8 - p.k : 0);
-        else
-          r.b[rep] = keep_if(r.b[rep], k0 < p.k);
-      }
       if (B_CH % NTH == 0 || t + NTH * rep < B_CH)
         *reinterpret_cast<u32x4*>(Bs + b_col[rep] * LDS_ROW + b_kc[rep] * 8) = r.b[rep];
     }
@@ -604,6 +608,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
   if (stages > 0) {
     load_stage(0, st0);
     if (DEPTH == 2 && stages > 1) load_stage(1, st1);
+    mask(st0);
     store_a(0, st0);
     store_b(0, st0);
     __syncthreads();
@@ -617,6 +622,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
         Staged& cur = PAR ? st1 : st0;   // stage s (already in LDS buffer PAR): free for s+2
         Staged& nxt = PAR ? st0 : st1;   // stage s+1, loaded one stage ago
         if (s + 2 < stages) load_stage(s + 2, cur);
+        if (more) mask(nxt);
         compute(PAR, [&](int kq) {
           if (more && kq == 1) store_a(PAR ^ 1, nxt);
           if (more && kq == 2) store_b(PAR ^ 1, nxt);
@@ -626,6 +632,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void brgemm_bf16_vec_kernel
         if (more) load_stage(s + 1, st0);
         compute(PAR, [&](int) {});
         if (more) {
+          mask(st0);
           store_a(PAR ^ 1, st0);
           store_b(PAR ^ 1, st0);
         }
